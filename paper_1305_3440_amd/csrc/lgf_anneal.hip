@@ -164,15 +164,7 @@ __global__ void __launch_bounds__(kSaBlock) anneal_kernel(void *__restrict__ fie
     set_zero(K);
 #pragma unroll
     for (int k = 0; k < NL; ++k) add_fwd_bwd(K, uf[k], ub[k]);
-    if constexpr (LANES == 2) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                K.e[i][j].re += shfl_xor_t(K.e[i][j].re, 1);
-                K.e[i][j].im += shfl_xor_t(K.e[i][j].im, 1);
-            }
-    }
+    lane_sum<LANES>(K);
 
     const SaKey key{lex_index(g, c), sweep, instance, k0, k1};
     mat3<double> G;

@@ -64,6 +64,9 @@ Geom make_geom(const int dims[4])
     g.hs[0] = g.L[1] * g.L[2] * g.hx;
     g.hs[1] = g.L[2] * g.hx;
     g.hs[2] = g.hx;
+    g.dx = make_fast_div(g.hx);
+    g.dy = make_fast_div(g.L[2]);
+    g.dz = make_fast_div(g.L[1]);
     return g;
 }
 

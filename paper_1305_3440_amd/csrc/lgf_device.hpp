@@ -129,6 +129,39 @@ __device__ __forceinline__ void convert(mat3<B> &dst, const mat3<A> &src)
         for (int j = 0; j < 3; ++j) dst.e[i][j] = {B(src.e[i][j].re), B(src.e[i][j].im)};
 }
 
+// The value of another lane of the same four (quad): lane i of a quad gets the
+// value of its lane P_i.  A DPP move inside the vector unit, where a shuffle
+// goes through LDS (18 or 36 of them sum one matrix over the lanes of a site).
+template <int P0, int P1, int P2, int P3> __device__ __forceinline__ float quad_perm(float v)
+{
+    constexpr int ctrl = P0 | (P1 << 2) | (P2 << 4) | (P3 << 6);
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xF, 0xF, true));
+}
+template <int P0, int P1, int P2, int P3> __device__ __forceinline__ double quad_perm(double v)
+{
+    constexpr int ctrl = P0 | (P1 << 2) | (P2 << 4) | (P3 << 6);
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xF, 0xF, true));
+}
+
+// m summed over the LPS (1, 2 or 4) lanes of a site, pairs first
+template <int LPS, typename T> __device__ __forceinline__ void lane_sum(mat3<T> &m)
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            if constexpr (LPS >= 2) {
+                m.e[i][j].re += quad_perm<1, 0, 3, 2>(m.e[i][j].re);
+                m.e[i][j].im += quad_perm<1, 0, 3, 2>(m.e[i][j].im);
+            }
+            if constexpr (LPS >= 4) {
+                m.e[i][j].re += quad_perm<2, 3, 0, 1>(m.e[i][j].re);
+                m.e[i][j].im += quad_perm<2, 3, 0, 1>(m.e[i][j].im);
+            }
+        }
+}
+
 // ----------------------------------------------------------------------------
 // Storage formats.  A field is split by parity; within a parity, direction
 // and vector slot, the Vh = V/2 sites form one contiguous stream of 8- or
@@ -152,6 +185,16 @@ template <> struct Fmt<kF64_12> { using T = double; using V = v2d; static conste
 template <> struct Fmt<kF32_18> { using T = float;  using V = v2f; static constexpr int R = 3, NV = 9, CPV = 1; };
 template <> struct Fmt<kF32_12> { using T = float;  using V = v4f; static constexpr int R = 2, NV = 3, CPV = 2; };
 template <> struct Fmt<kF64_12S> : Fmt<kF64_12> {};  // the site field g
+
+// A device pointer that was read from memory (a descriptor's) is generic to the
+// compiler, which then emits flat loads: their waits cover LDS and memory
+// together, so no two stay in flight across one.  Buffers of the library are
+// all global memory; this states it.
+template <typename T> __device__ __forceinline__ T *as_global(T *p)
+{
+    // (through an integer: a plain cast there and back is folded away)
+    return (T *)reinterpret_cast<__attribute__((address_space(1))) T *>(reinterpret_cast<uintptr_t>(p));
+}
 
 // vector load / store, optionally marked non-temporal (streamed past the
 // caches: every link is read and written once per half-sweep)
@@ -259,40 +302,52 @@ __device__ __forceinline__ void load_link_split(mat3<double> &u, void *field, ui
 constexpr uint32_t kRecTile = 32;
 __host__ __device__ inline uint32_t rec_tiles(uint32_t Vh) { return (Vh + kRecTile - 1) / kRecTile; }
 
-// first FP32 vector and first remainder vector of link `slot` of site h in
-// kF64_12S records
-__device__ __forceinline__ const v4f *rec_split_hi(const void *rec, uint32_t Vh, int parity, int slot, uint32_t h)
+// The tile of site h and its place in it.  UNIFORM: every active lane of the
+// wave holds a site of one tile (2 or 4 lanes per site and waves that start at
+// a multiple of 32 or 16 sites), so the tile's address is formed once per wave
+// in scalar registers: 64-bit addresses per lane cost the FP64 update 8 more
+// vector registers and its third wave per SIMD.
+struct RecPos {
+    uint32_t tile, pos;
+};
+
+template <bool UNIFORM> __device__ __forceinline__ RecPos rec_pos(uint32_t h)
 {
-    const size_t blk = ((size_t)parity * rec_tiles(Vh) + h / kRecTile) * 8 + (size_t)slot;
-    return reinterpret_cast<const v4f *>(reinterpret_cast<const char *>(rec) + blk * (kRecTile * 72)) +
-           h % kRecTile;
+    const uint32_t t = h / kRecTile;
+    return {UNIFORM ? (uint32_t)__builtin_amdgcn_readfirstlane((int)t) : t, h % kRecTile};
 }
-__device__ __forceinline__ const v4s *rec_split_lo(const void *rec, uint32_t Vh, int parity, int slot, uint32_t h)
+
+// first FP32 vector and first remainder vector of link `slot` of a site in
+// kF64_12S records
+__device__ __forceinline__ const v4f *rec_split_hi(const void *rec, uint32_t Vh, int parity, int slot, RecPos p)
 {
-    const size_t blk = ((size_t)parity * rec_tiles(Vh) + h / kRecTile) * 8 + (size_t)slot;
-    return reinterpret_cast<const v4s *>(reinterpret_cast<const char *>(rec) + blk * (kRecTile * 72) +
-                                         kRecTile * 48) +
-           h % kRecTile;
+    const char *b = reinterpret_cast<const char *>(rec) + ((size_t)parity * rec_tiles(Vh) + p.tile) * (8 * kRecTile * 72);
+    return reinterpret_cast<const v4f *>(b + (uint32_t)slot * (kRecTile * 72)) + p.pos;
+}
+__device__ __forceinline__ const v4s *rec_split_lo(const void *rec, uint32_t Vh, int parity, int slot, RecPos p)
+{
+    const char *b = reinterpret_cast<const char *>(rec) + ((size_t)parity * rec_tiles(Vh) + p.tile) * (8 * kRecTile * 72);
+    return reinterpret_cast<const v4s *>(b + (uint32_t)slot * (kRecTile * 72) + kRecTile * 48) + p.pos;
 }
 
 template <int F>
 __device__ __forceinline__ const typename Fmt<F>::V *rec_ptr(const void *rec, uint32_t Vh, int parity, int slot,
-                                                             uint32_t h)
+                                                             RecPos p)
 {
-    return reinterpret_cast<const typename Fmt<F>::V *>(rec) +
-           (((size_t)parity * rec_tiles(Vh) + h / kRecTile) * 8 + (size_t)slot) * Fmt<F>::NV * kRecTile +
-           h % kRecTile;
+    const typename Fmt<F>::V *b = reinterpret_cast<const typename Fmt<F>::V *>(rec) +
+                                  ((size_t)parity * rec_tiles(Vh) + p.tile) * (8 * Fmt<F>::NV * kRecTile);
+    return b + ((uint32_t)slot * (Fmt<F>::NV * kRecTile) + p.pos);
 }
 
-// link `slot` of site h's record, rows 0 and 1 (streamed past the caches)
+// link `slot` of a site's record, rows 0 and 1 (streamed past the caches)
 template <int F>
 __device__ __forceinline__ void load_link_rec(mat3<typename Fmt<F>::T> &u, const void *rec, uint32_t Vh, int parity,
-                                              int slot, uint32_t h)
+                                              int slot, RecPos p)
 {
     static_assert(Fmt<F>::R == 2, "records hold 12-real links");
     if constexpr (F == kF64_12S) {
-        const v4f *hb = rec_split_hi(rec, Vh, parity, slot, h);
-        const v4s *qb = rec_split_lo(rec, Vh, parity, slot, h);
+        const v4f *hb = rec_split_hi(rec, Vh, parity, slot, p);
+        const v4s *qb = rec_split_lo(rec, Vh, parity, slot, p);
         v4f a[3];
         v4s q[3];
 #pragma unroll
@@ -308,7 +363,7 @@ __device__ __forceinline__ void load_link_rec(mat3<typename Fmt<F>::T> &u, const
                                                      (double)a[k].w + (double)q[k].w * kSplitUnit};
         }
     } else {
-        const typename Fmt<F>::V *b = rec_ptr<F>(rec, Vh, parity, slot, h);
+        const typename Fmt<F>::V *b = rec_ptr<F>(rec, Vh, parity, slot, p);
         typename Fmt<F>::V v[Fmt<F>::NV];
 #pragma unroll
         for (int k = 0; k < Fmt<F>::NV; ++k) v[k] = vload<true>(b + (size_t)k * kRecTile);
@@ -344,54 +399,81 @@ __device__ __forceinline__ void store_link(typename Fmt<F>::V *blk, uint32_t Vh,
 // h -/+ the half strides, the x neighbours at the same row position or one off.
 // ----------------------------------------------------------------------------
 
+// Exact division of n < 2^31 by a divisor fixed on the host:
+// n / d = floor(2n m / 2^32) >> l with l = ceil(log2 d), m = floor(2^(31+l) / d) + 1
+// (Granlund and Montgomery, PLDI'94; the factor 2 keeps d = 1 inside 32 bits).
+struct FastDiv {
+    uint32_t m, l;
+};
+
+inline FastDiv make_fast_div(uint32_t d)
+{
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;
+    return {(uint32_t)((1ull << (31 + l)) / d + 1), l};
+}
+
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f) { return __umulhi(2 * n, f.m) >> f.l; }
+
 struct Geom {
     uint32_t L[4];   // Lt, Lz, Ly, Lx
     uint32_t hx;     // Lx / 2
     uint32_t Vh;     // V / 2
     uint32_t hs[3];  // half strides of t, z, y: Lz*Ly*hx, Ly*hx, hx
+    FastDiv dx, dy, dz;  // division by hx, Ly, Lz
 };
 
 struct Site {
     uint32_t t, z, y, x;
     uint32_t row;  // (t*Lz + z)*Ly + y
+    uint32_t xh;   // position in the row's half: x / 2
 };
 
 __device__ __forceinline__ Site decode(const Geom &g, int parity, uint32_t h)
 {
     Site c;
-    c.row = h / g.hx;
-    const uint32_t xh = h - c.row * g.hx;
-    uint32_t r = c.row;
-    c.y = r % g.L[2];
-    r /= g.L[2];
-    c.z = r % g.L[1];
-    c.t = r / g.L[1];
-    c.x = 2 * xh + ((parity + c.t + c.z + c.y) & 1u);
+    c.row = fast_div(h, g.dx);
+    c.xh = h - c.row * g.hx;
+    const uint32_t tz = fast_div(c.row, g.dy);
+    c.y = c.row - tz * g.L[2];
+    c.t = fast_div(tz, g.dz);
+    c.z = tz - c.t * g.L[1];
+    c.x = 2 * c.xh + ((parity + c.t + c.z + c.y) & 1u);
     return c;
 }
 
-// half index (in the other parity) of the site x - mu
+// Coordinate, extent and half stride of a site along mu (mu = 3: positions in
+// the row's half).  Selects, not an indexed read of g: mu depends on the lane
+// in the kernels with several lanes per site, and an index would put a memory
+// access in front of every neighbour's address.
+struct Axis {
+    uint32_t c, e, s;
+};
+
+__device__ __forceinline__ Axis axis_of(const Geom &g, const Site &c, int mu)
+{
+    Axis a;
+    a.c = (mu == 0) ? c.t : (mu == 1) ? c.z : (mu == 2) ? c.y : c.xh;
+    a.e = (mu == 0) ? g.L[0] : (mu == 1) ? g.L[1] : (mu == 2) ? g.L[2] : g.hx;
+    a.s = (mu == 0) ? g.hs[0] : (mu == 1) ? g.hs[1] : (mu == 2) ? g.hs[2] : 1u;
+    return a;
+}
+
+// half index (in the other parity) of the site x - mu (along x, the site at
+// an odd x has its left neighbour at its own position of the other half)
 __device__ __forceinline__ uint32_t back_half(const Geom &g, const Site &c, uint32_t h, int mu)
 {
-    if (mu == 3) {
-        const uint32_t xb = (c.x == 0) ? g.L[3] - 1 : c.x - 1;
-        return c.row * g.hx + (xb >> 1);
-    }
-    const uint32_t coord = (mu == 0) ? c.t : (mu == 1) ? c.z : c.y;
-    const uint32_t ext = g.L[mu];
-    const uint32_t hs = g.hs[mu];
-    return (coord == 0) ? h + (ext - 1) * hs : h - hs;
+    const Axis a = axis_of(g, c, mu);
+    const uint32_t n = (a.c == 0) ? h + (a.e - 1) * a.s : h - a.s;
+    return (mu == 3 && (c.x & 1u)) ? h : n;
 }
 
 // half index (in the other parity) of the site x + mu
 __device__ __forceinline__ uint32_t fwd_half(const Geom &g, const Site &c, uint32_t h, int mu)
 {
-    if (mu == 3) {
-        const uint32_t xf = (c.x + 1 == g.L[3]) ? 0 : c.x + 1;
-        return c.row * g.hx + (xf >> 1);
-    }
-    const uint32_t coord = (mu == 0) ? c.t : (mu == 1) ? c.z : c.y;
-    return (coord + 1 == g.L[mu]) ? h - (g.L[mu] - 1) * g.hs[mu] : h + g.hs[mu];
+    const Axis a = axis_of(g, c, mu);
+    const uint32_t n = (a.c + 1 == a.e) ? h - (a.e - 1) * a.s : h + a.s;
+    return (mu == 3 && !(c.x & 1u)) ? h : n;
 }
 
 __device__ __forceinline__ uint32_t lex_index(const Geom &g, const Site &c) { return c.row * g.L[3] + c.x; }

@@ -24,7 +24,7 @@ __device__ __forceinline__ void ensemble_site(const EnsCfg &c, int parity, uint3
 {
     using T = typename Fmt<F>::T;
     const RelaxArgs<T> a{(T)r.omega, r.overrelax, r.sr_threshold, r.key0, r.key1, sweep, c.instance};
-    update_site<F, 1, SR, NT, 0, false, false, MEAS>(c.field, c.g, parity, h, 0, active, a, nullptr, nullptr, acc);
+    update_site<F, 1, SR, NT, 0, false, false, MEAS>(as_global(c.field), c.g, parity, h, 0, active, a, nullptr, nullptr, acc);
 }
 
 // FA, FB: the (at most two) storage formats the launch may meet.  MEAS: the
@@ -69,8 +69,8 @@ __global__ void __launch_bounds__(kEnsMaxTile) ensemble_measure_kernel(const Ens
     const bool active = h0 < c.g.Vh;
     const uint32_t h = active ? h0 : c.g.Vh - 1;
     double f = 0.0, th = 0.0;
-    if (c.fmt == FA) measure_site<FA>(c.field, c.g, parity, h, active, reunit_fwd, reunit_bwd, f, th);
-    else if (FB != FA && c.fmt == FB) measure_site<FB>(c.field, c.g, parity, h, active, reunit_fwd, reunit_bwd, f, th);
+    if (c.fmt == FA) measure_site<FA>(as_global(c.field), c.g, parity, h, active, reunit_fwd, reunit_bwd, f, th);
+    else if (FB != FA && c.fmt == FB) measure_site<FB>(as_global(c.field), c.g, parity, h, active, reunit_fwd, reunit_bwd, f, th);
     block_sum2_any(f, th, partials + 2 * blockIdx.x);
 }
 
@@ -109,8 +109,8 @@ __device__ __forceinline__ void ensemble_site_fixed(const EnsCfg &c, int parity,
 {
     using T = typename Fmt<F>::T;
     const RelaxArgs<T> a{(T)r.omega, r.overrelax, r.sr_threshold, r.key0, r.key1, sweep, c.instance};
-    update_site_fixed<F, kEnsFixedLanes, SR, POST, 0, REC>(REC ? c.rec : c.field, c.gf, c.g, parity, h, lane, active,
-                                                          a, acc);
+    update_site_fixed<F, kEnsFixedLanes, SR, POST, 0, REC>(as_global(REC ? c.rec : c.field), as_global(c.gf), c.g,
+                                                          parity, h, lane, active, a, acc);
 }
 
 template <int FA, int FB, bool SR, int POST, bool REC>
@@ -153,10 +153,10 @@ __global__ void __launch_bounds__(kEnsMaxTile) ensemble_fixed_measure_kernel(con
     const bool active = h0 < c.g.Vh;
     const uint32_t h = active ? h0 : c.g.Vh - 1;
     double f = 0.0, th = 0.0;
-    const void *links = REC ? c.rec : c.field;
-    if (c.fmt == FA) measure_site_fixed<FA, kEnsFixedLanes, 0, REC>(links, c.gf, c.g, parity, h, lane, active, f, th);
+    const void *links = as_global(REC ? c.rec : c.field);
+    if (c.fmt == FA) measure_site_fixed<FA, kEnsFixedLanes, 0, REC>(links, as_global(c.gf), c.g, parity, h, lane, active, f, th);
     else if (FB != FA && c.fmt == FB)
-        measure_site_fixed<FB, kEnsFixedLanes, 0, REC>(links, c.gf, c.g, parity, h, lane, active, f, th);
+        measure_site_fixed<FB, kEnsFixedLanes, 0, REC>(links, as_global(c.gf), c.g, parity, h, lane, active, f, th);
     block_sum2_any(f, th, partials + 2 * blockIdx.x);
 }
 

@@ -49,7 +49,7 @@ struct TileOrder {
 // when POST == 2.  MU0 = 1: Coulomb gauge, with the timeslice flags
 // slice_active.  REC: the links are per-site link records.
 template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false>
-__global__ void __launch_bounds__(256) fixed_sweep_kernel(const void *__restrict__ links, void *__restrict__ gf,
+__global__ void __launch_bounds__(256, (fixed_waves<F, LPS, POST>())) fixed_sweep_kernel(const void *__restrict__ links, void *__restrict__ gf,
                                                           Geom g, int parity, RelaxArgs<typename Fmt<F>::T> a,
                                                           TileOrder o, uint32_t n_groups,
                                                           double *__restrict__ partials,
@@ -305,7 +305,8 @@ __global__ void __launch_bounds__(kMeasureBlock) measure_coulomb_fixed_kernel(co
     const bool active = i < g.hs[0];
     const uint32_t h = t * g.hs[0] + (active ? i : g.hs[0] - 1);
     double f, th;
-    measure_site_fixed<F, kMeasureFixedLanes, 1, REC>(links, gf, g, parity, h, (int)(tid % kMeasureFixedLanes),
+    // (a slice need not start at a record tile, so a wave may straddle two)
+    measure_site_fixed<F, kMeasureFixedLanes, 1, REC, false>(links, gf, g, parity, h, (int)(tid % kMeasureFixedLanes),
                                                       active, f, th);
     block_sum2<kMeasureBlock>(f, th, partials + 2 * ((size_t)t * gridDim.x + blockIdx.x));
 }
@@ -392,7 +393,7 @@ __global__ void __launch_bounds__(256) record_links_kernel(const void *__restric
     const int parity = blockIdx.y;
     const Site c = decode(g, parity, h);
     void *L = const_cast<void *>(src);
-    V *out = const_cast<V *>(rec_ptr<F>(rec, g.Vh, parity, 0, h));
+    V *out = const_cast<V *>(rec_ptr<F>(rec, g.Vh, parity, 0, rec_pos<false>(h)));
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
         const V *f = block_ptr<F>(L, g.Vh, parity, mu) + h;
@@ -415,6 +416,7 @@ __global__ void __launch_bounds__(256) record_split_links_kernel(const void *__r
     const int parity = blockIdx.y;
     const Site c = decode(g, parity, h);
     void *L = const_cast<void *>(src);
+    const RecPos rp = rec_pos<false>(h);
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
         const uint32_t hb = back_half(g, c, h, mu);
@@ -422,10 +424,10 @@ __global__ void __launch_bounds__(256) record_split_links_kernel(const void *__r
         const v4s *fq = split_res_ptr(L, g.Vh, parity, mu) + h;
         const v4f *bh = block_ptr<kF32_12>(L, g.Vh, parity ^ 1, mu) + hb;
         const v4s *bq = split_res_ptr(L, g.Vh, parity ^ 1, mu) + hb;
-        v4f *ofh = const_cast<v4f *>(rec_split_hi(rec, g.Vh, parity, mu, h));
-        v4s *ofq = const_cast<v4s *>(rec_split_lo(rec, g.Vh, parity, mu, h));
-        v4f *obh = const_cast<v4f *>(rec_split_hi(rec, g.Vh, parity, 4 + mu, h));
-        v4s *obq = const_cast<v4s *>(rec_split_lo(rec, g.Vh, parity, 4 + mu, h));
+        v4f *ofh = const_cast<v4f *>(rec_split_hi(rec, g.Vh, parity, mu, rp));
+        v4s *ofq = const_cast<v4s *>(rec_split_lo(rec, g.Vh, parity, mu, rp));
+        v4f *obh = const_cast<v4f *>(rec_split_hi(rec, g.Vh, parity, 4 + mu, rp));
+        v4s *obq = const_cast<v4s *>(rec_split_lo(rec, g.Vh, parity, 4 + mu, rp));
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             ofh[(size_t)k * kRecTile] = fh[(size_t)k * g.Vh];

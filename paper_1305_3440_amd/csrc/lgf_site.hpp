@@ -54,8 +54,6 @@ __device__ __forceinline__ void su2_step(mat3<T> &W, mat3<T> &G, T omega, bool o
 }
 
 
-template <typename T> __device__ __forceinline__ T shfl_xor_t(T v, int m) { return __shfl_xor(v, m); }
-
 // u <- u as stored in format F and read back; o receives the stored value
 template <int F>
 __device__ __forceinline__ void round_to_format(mat3<double> &u, mat3<typename Fmt<F>::T> &o)
@@ -164,15 +162,7 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
 #pragma unroll
     for (int k = 0; k < NL; ++k)
         if (lane + k * LPS >= MU0) add_fwd_bwd(K, uf[k], ub[k]);
-#pragma unroll
-    for (int m = 1; m < LPS; m <<= 1)
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                K.e[i][j].re += shfl_xor_t(K.e[i][j].re, m);
-                K.e[i][j].im += shfl_xor_t(K.e[i][j].im, m);
-            }
+    lane_sum<LPS>(K);
 
     bool sq0 = false, sq1 = false, sq2 = false;
     if constexpr (SR) {
@@ -225,15 +215,7 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
         store_link<F, NT>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity ^ 1, mu), g.Vh, hb[k], rb);
     }
     if constexpr (MEAS) {
-#pragma unroll
-        for (int m = 1; m < LPS; m <<= 1)
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    Kn.e[i][j].re += shfl_xor_t(Kn.e[i][j].re, m);
-                    Kn.e[i][j].im += shfl_xor_t(Kn.e[i][j].im, m);
-                }
+        lane_sum<LPS>(Kn);
         if (lane == 0) acc->th += theta_of_K(Kn);
     }
 }
@@ -385,19 +367,6 @@ __device__ __forceinline__ void meas_term_bwd(mat3<double> &acc, const mat3<T> &
     add_dag_to(acc, pd);
 }
 
-template <int LPS, typename T> __device__ __forceinline__ void lane_sum(mat3<T> &m)
-{
-#pragma unroll
-    for (int s = 1; s < LPS; s <<= 1)
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                m.e[i][j].re += shfl_xor_t(m.e[i][j].re, s);
-                m.e[i][j].im += shfl_xor_t(m.e[i][j].im, s);
-            }
-}
-
 // link mu of parity-`parity` site h for the fixed-link sweep in format F
 // (kF64_12S: from the split storage; row 2 left unset)
 template <int F>
@@ -406,6 +375,14 @@ __device__ __forceinline__ void load_fixed_link(mat3<typename Fmt<F>::T> &u, voi
 {
     if constexpr (F == kF64_12S) load_link_split<true>(u, links, Vh, parity, mu, h);
     else load_link<F, true, false>(u, block_ptr<F>(links, Vh, parity, mu), Vh, h);
+}
+
+// Waves per SIMD that a fixed-link sweep kernel is compiled for: three for
+// the FP64 12-real update with two lanes per site (168 registers hold it
+// without spills; left alone the allocator takes a few more and loses a wave).
+template <int F, int LPS, int POST> constexpr int fixed_waves()
+{
+    return (Fmt<F>::R == 2 && sizeof(typename Fmt<F>::T) == 8 && LPS == 2 && POST < 2) ? 3 : 1;
 }
 
 // The update of site h of the given parity in the fixed-link form, LPS lanes
@@ -436,6 +413,7 @@ __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links
     void *U = const_cast<void *>(links);
     const typename S::V *gn = site_field_ptr<F>(gf, g.Vh, parity ^ 1);
     const Site c = decode(g, parity, h);
+    const RecPos rp = rec_pos<(LPS > 1)>(h);
     if (slice_active && !slice_active[c.t]) return;
 
     mat3<T> M;
@@ -453,7 +431,7 @@ __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links
         const int mu = lane + k * LPS;
         if (mu < MU0) continue;
         mat3<T> u, y, p;
-        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, h);
+        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, rp);
         else load_fixed_link<F>(u, U, g.Vh, parity, mu, h);
         load_link<F, false, false>(y, gn, g.Vh, fwd_half(g, c, h, mu));
         if constexpr (R == 2) row2_fma(y);
@@ -465,7 +443,7 @@ __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links
             else meas_term_fwd<R>(Mf, u, y);
         }
         const uint32_t hb = back_half(g, c, h, mu);
-        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, h);
+        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, rp);
         else load_fixed_link<F>(u, U, g.Vh, parity ^ 1, mu, hb);
         load_link<F, false, false>(y, gn, g.Vh, hb);
         if constexpr (R == 2) row2_fma(u);
@@ -534,7 +512,8 @@ __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links
 // the same terms.  Only lane 0 of an active site returns non-zero sums.
 // MU0 = 1: the Coulomb-gauge F_C and theta_C contributions (spatial links).
 // REC: links holds the per-site link records (as in update_site_fixed).
-template <int F, int LPS, int MU0 = 0, bool REC = false>
+// UNIFORM: the wave's sites lie in one record tile (rec_pos).
+template <int F, int LPS, int MU0 = 0, bool REC = false, bool UNIFORM = (LPS > 1)>
 __device__ __forceinline__ void measure_site_fixed(const void *__restrict__ links, const void *__restrict__ gf,
                                                    const Geom &g, int parity, uint32_t h, int lane, bool active,
                                                    double &f, double &th)
@@ -546,6 +525,7 @@ __device__ __forceinline__ void measure_site_fixed(const void *__restrict__ link
     void *G = const_cast<void *>(gf);
     const typename S::V *gn = site_field_ptr<F>(G, g.Vh, parity ^ 1);
     const Site c = decode(g, parity, h);
+    const RecPos rp = rec_pos<UNIFORM>(h);
     mat3<double> Mf, Mb;
     set_zero(Mf);
     set_zero(Mb);
@@ -554,13 +534,13 @@ __device__ __forceinline__ void measure_site_fixed(const void *__restrict__ link
         const int mu = lane + k * LPS;
         if (mu < MU0) continue;
         mat3<T> u, y;
-        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, h);
+        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, rp);
         else load_fixed_link<F>(u, U, g.Vh, parity, mu, h);
         load_link<F, false, false>(y, gn, g.Vh, fwd_half(g, c, h, mu));
         if constexpr (R == 2) row2_fma(y);
         meas_term_fwd<R>(Mf, u, y);
         const uint32_t hb = back_half(g, c, h, mu);
-        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, h);
+        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, rp);
         else load_fixed_link<F>(u, U, g.Vh, parity ^ 1, mu, hb);
         load_link<F, false, false>(y, gn, g.Vh, hb);
         if constexpr (R == 2) row2_fma(u);
