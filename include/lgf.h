@@ -89,7 +89,7 @@ typedef struct {
     int separate_measure;  /* 1: reunitarize and measure in two passes of their own after each
                               chunk; 0 (default): inside the chunk's last half-sweep plus one
                               read-only pass over the other parity, where the sweep allows it
-                              (overrelaxation, non-temporal, not the t-slice pipeline).  The links
+                              (overrelaxation, not the t-slice pipeline).  The links
                               are the same; F and theta differ only in the summation order */
     int fixed_links;       /* 1: the sweeps keep the links at their input values and update the
                               gauge transformation g instead (a site field in the sweep format),
@@ -328,7 +328,10 @@ lgf_status lgf_synchronize(lgf_lattice *h);
  * (lgf_sweep with parity 0 or 1) always run in place.  A new handle starts at 1
  * lane, 1 tile, 128 lanes, no remap, non-temporal, in place -- except FP64-12,
  * which starts out of place (its second buffer allocated before its first full
- * sweep; without memory for it the format falls back to in place).
+ * sweep; without memory for it the format falls back to in place).  Until a
+ * tuning is set or autotuned, that start is what lgf_get_tuning reports, and
+ * launches choose lanes, workgroup, remap, non-temporal access and schedule by
+ * the size of the field, with the same bits.
  * lgf_set_tuning copies *tuning (LGF_EINVAL on a value outside these sets);
  * lgf_get_tuning fills *tuning with the current values. */
 typedef struct {
@@ -385,15 +388,17 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials);
  * records; FP32-12 1 lane, 128-lane workgroups, order 0, records (all three
  * on the link field for lattices of fewer than 2^18 sites); FP64-18 2
  * lanes, 64-lane workgroups, order 2, layout 0; FP32-18 2 lanes, 256-lane
- * workgroups, order 0, layout 0.  LGF_EINVAL on other values.  Setting a
+ * workgroups, order 0, layout 0.  Until a tuning is set or autotuned, launches on
+ * lattices of up to 2 million sites choose workgroup, order 1 and lanes by the
+ * size, with the same bits.  LGF_EINVAL on other values.  Setting a
  * tuning closes an open stepwise session (lgf_fix_begin) without applying g. */
 lgf_status lgf_set_fixed_tuning(lgf_lattice *h, int format, const lgf_sweep_tuning *tuning);
 lgf_status lgf_get_fixed_tuning(const lgf_lattice *h, int format, lgf_sweep_tuning *tuning);
 
 /* Pick the fastest fixed-link sweep variant for `format` on this lattice
  * (lanes 1 (FP32 formats)/2/4 x block 64/128/256 x tile order 0-3 x link
- * layout 0/1 (FP32-12, FP64-12, LGF_FP64_12S); the FP64 formats keep tile order 2
- * wherever the lattice admits it; orders the lattice does not admit are
+ * layout 0/1 (FP32-12, FP64-12, LGF_FP64_12S); beyond 2 million sites the FP64
+ * formats keep tile order 2 wherever the lattice admits it; orders the lattice does not admit are
  * left out): each timed over `trials` full sweeps, the fastest again over ten
  * times as many in five interleaved rounds; the default stays unless another
  * is 1 % faster.  The sweeps read the handle's links (or their copy in

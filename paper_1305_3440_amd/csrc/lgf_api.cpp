@@ -138,6 +138,7 @@ struct lgf_lattice {
     uint64_t *d_sweep_base;               // device copy of a chunk's first SR counter
     const uint64_t *sweep_base_active;    // passed to the sweeps while a chunk is captured
     lgf::SweepTuning tune[4];
+    bool tuned[4];        // set or autotuned; else launches choose by size (launch_tuning)
     std::vector<GraphEntry> graphs;
     hipEvent_t ev0, ev1;
     // Coulomb gauge: timeslice flags and per-timeslice reductions (lazily)
@@ -154,6 +155,7 @@ struct lgf_lattice {
     // fields) and the tuning of its sweep
     void *gfix[4];
     lgf::SweepTuning tune_fixed[5];  // per sweep format, LGF_FP64_12S included
+    bool tuned_fixed[5];
     void *split;       // the links in the split storage of LGF_FP64_12S (owned)
     void *rec[5];      // per-site link records of the 12-real formats (owned)
     // stepwise fixed-link gauge fixing (lgf_fix_begin .. lgf_fix_end)
@@ -274,12 +276,58 @@ lgf::SweepTuning default_tuning(int format)
     return t;
 }
 
+// The tuning of the link sweeps' launches: the handle's where it was set or
+// autotuned, else chosen by the size of the field.  The bits do not depend on
+// it.  Measured per half-sweep launch, defaults above -> chosen:
+//  - Fields of up to 380 MB stay in the 256 MB last-level cache from one
+//    half-sweep to the next (a little beyond it too: each half-sweep starts with
+//    what the last one left), but only if they are not streamed past it, and a
+//    contiguous range of the workgroups per XCD keeps each range's lines in one
+//    L2 and its pages in one TLB: 24^4 FP64-18 (191 MB) 80 -> 60 us, 28^4
+//    FP64-12 (236 MB) 100 -> 71, 32^4 FP32-12 (201 MB) 80 -> 59, 36^4 FP32-12 (322
+//    MB) 127 -> 102; streamed is better again at 403 MB (32^4 FP64-12, 143 against
+//    147 us) and 484 MB.
+//  - Between 22 and 48 MB, around the L2s' 32 MB, streaming the links keeps
+//    what L2 has: 16^4 FP64-18 (38 MB) 11.5 against 12.6 us, FP64-12 (25 MB) 9.3
+//    against 10.5; below, 12^4 FP64-18 (12 MB) 7.9 against 7.5.
+//  - Two lanes per site where the launch is too small to fill the chip (up to
+//    40000 sites, 65536 in FP32-12) and the time is one wave's: 8^4 FP64-18 7.0
+//    (one lane, 64-lane workgroups; 8.1 in 128) -> 5.4 us, 12^4 FP32-12 5.9 -> 5.2,
+//    14^4 FP64-18 10.0 -> 9.0; 16^4 FP64-18 11.5 against 11.8.  FP64-12 keeps
+//    them throughout, two waves per SIMD instead of one: 24^4 42.3 -> 39.4 us.
+//  - Larger fields on up to 1.2 million sites: XCD ranges in 256-lane
+//    workgroups, 32^4 FP64-18 250 -> 214 us, FP64-12 162 -> 143; at 36^4 (1.68
+//    million) 387 against 388, beyond it the plain order wins by 2-5 %.
+//  - Beyond: 256-lane workgroups in FP32 (64^4 FP32-18 1749 -> 1695 us) and two
+//    lanes per site in FP32-12 (1157 -> 1111, 48^4 382 -> 374).
+lgf::SweepTuning launch_tuning(const lgf_lattice *h, int format)
+{
+    lgf::SweepTuning t = h->tune[format];
+    if (h->tuned[format]) return t;
+    const double mb = 4e-6 * (double)h->V * (double)lgf::link_bytes(format);
+    if (mb <= 380.0) {
+        t.schedule = lgf::kScheduleInPlace;
+        t.nontemporal = (mb > 22.0 && mb <= 48.0) ? 1 : 0;
+        t.xcd_remap = 1;
+        t.block = 64;
+        if (format == LGF_FP64_12 || h->V <= (format == LGF_FP32_12 ? 65536 : 40000)) t.lanes_per_site = 2;
+    } else if (h->V <= 1200000) {
+        t.schedule = lgf::kScheduleInPlace;
+        t.xcd_remap = 1;
+        t.block = 256;
+    } else if (format == LGF_FP32_18 || format == LGF_FP32_12) {
+        t.block = 256;
+        if (format == LGF_FP32_12) t.lanes_per_site = 2;
+    }
+    return t;
+}
+
 // Before sweeps in a format: the out-of-place schedule needs its partner
 // buffer (allocated here, never inside a graph capture); without memory for
 // it the format falls back to in place.
 void prepare_schedule(lgf_lattice *h, int format)
 {
-    if (h->tune[format].schedule != lgf::kScheduleOutOfPlace || h->partner[format]) return;
+    if (launch_tuning(h, format).schedule != lgf::kScheduleOutOfPlace || h->partner[format]) return;
     if (ensure_partner(h, format) != LGF_OK) {
         h->tune[format].schedule = lgf::kScheduleInPlace;
         drop_graphs(h);
@@ -311,10 +359,9 @@ lgf_status sweep_launch(lgf_lattice *h, int format, void *field, int parity, dou
     a.meas = meas;
     a.sweep_base = h->sweep_base_active;
     if (coulomb)
-        LGF_HIP(lgf::launch_sweep_coulomb(format, field, h->geom, a, h->d_mask, h->tune[format].nontemporal != 0,
-                                          h->stream));
+        LGF_HIP(lgf::launch_sweep_coulomb(format, field, h->geom, a, h->d_mask, launch_tuning(h, format), h->stream));
     else
-        LGF_HIP(lgf::launch_sweep(format, field, h->geom, a, h->tune[format], h->stream));
+        LGF_HIP(lgf::launch_sweep(format, field, h->geom, a, launch_tuning(h, format), h->stream));
     return LGF_OK;
 }
 
@@ -331,7 +378,8 @@ lgf_status full_sweep(lgf_lattice *h, int format, void *field, double omega, dou
                       uint64_t sweep_index, bool coulomb = false, double *meas = nullptr)
 {
     const int Lt = h->dims[0];
-    const int sched = h->tune[format].schedule;
+    const lgf::SweepTuning tune = launch_tuning(h, format);
+    const int sched = tune.schedule;
     if (!coulomb && sched == lgf::kScheduleOutOfPlace) {
         // parity 0 moves every link into the partner buffer, parity 1 moves them back
         void *partner = h->partner[format];
@@ -340,11 +388,11 @@ lgf_status full_sweep(lgf_lattice *h, int format, void *field, double omega, dou
         a.gacc = h->gacc_active;
         a.sweep_base = h->sweep_base_active;
         a.out = partner;
-        LGF_HIP(lgf::launch_sweep(format, field, h->geom, a, h->tune[format], h->stream));
+        LGF_HIP(lgf::launch_sweep(format, field, h->geom, a, tune, h->stream));
         a.parity = 1;
         a.out = field;
         a.meas = meas;
-        LGF_HIP(lgf::launch_sweep(format, partner, h->geom, a, h->tune[format], h->stream));
+        LGF_HIP(lgf::launch_sweep(format, partner, h->geom, a, tune, h->stream));
         return LGF_OK;
     }
     // (the pipeline gives the two-launch result bit for bit, so a sweep that
@@ -361,7 +409,7 @@ lgf_status full_sweep(lgf_lattice *h, int format, void *field, double omega, dou
         a.sweep_base = h->sweep_base_active;
         a.h_begin = (uint32_t)t * hs;
         a.h_end = (uint32_t)(t + 1) * hs;
-        LGF_HIP(lgf::launch_sweep(format, field, h->geom, a, h->tune[format], h->stream));
+        LGF_HIP(lgf::launch_sweep(format, field, h->geom, a, tune, h->stream));
         return LGF_OK;
     };
     LGF_TRY(slice(0, 0));
@@ -424,12 +472,8 @@ lgf_status measure_coulomb_field(lgf_lattice *h, int format, void *field, bool r
 // into a hipGraph and replayed; stochastic relaxation launches directly since
 // its counter changes every sweep.
 // Whether the chunk's last half-sweep can carry the reunitarization and the
-// measurement (kernel variants exist for overrelaxation with non-temporal
-// access, Landau gauge).
-bool can_fuse(const lgf_lattice *h, int format, double p_sr, bool coulomb)
-{
-    return !coulomb && p_sr == 0.0 && h->tune[format].nontemporal != 0;
-}
+// measurement (kernel variants exist for overrelaxation, Landau gauge).
+bool can_fuse(double p_sr, bool coulomb) { return !coulomb && p_sr == 0.0; }
 
 // room for the fused sweep's partial sums followed by those of the parity-0
 // measurement pass; graphs that hold the old buffer are dropped on growth
@@ -451,7 +495,7 @@ lgf_status ensure_fused_cap(lgf_lattice *h, size_t need)
 
 lgf_status ensure_fused(lgf_lattice *h, int format)
 {
-    return ensure_fused_cap(h, (size_t)lgf::sweep_groups(h->geom, h->tune[format]) +
+    return ensure_fused_cap(h, (size_t)lgf::sweep_groups(h->geom, launch_tuning(h, format)) +
                                    (size_t)lgf::measure_blocks(h->geom));
 }
 
@@ -460,7 +504,7 @@ lgf_status ensure_fused(lgf_lattice *h, int format)
 // reunitarized and stored) plus a read-only pass over the parity-0 sites.
 lgf_status measure_fused(lgf_lattice *h, int format, void *field, double *F, double *theta)
 {
-    const int ng = (int)lgf::sweep_groups(h->geom, h->tune[format]);
+    const int ng = (int)lgf::sweep_groups(h->geom, launch_tuning(h, format));
     int n0 = 0;
     LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, false, false, h->d_fused + 2 * (size_t)ng, &n0,
                                 h->stream));
@@ -531,7 +575,7 @@ lgf_status run_chunk(lgf_lattice *h, int format, void *field, int n, double omeg
     // and read the chunk's first counter from the device, set here outside
     // the graph, so one graph serves every chunk
     const bool sr = p_sr > 0.0;
-    GraphEntry key{format, field, n, omega, h->tune[format], coulomb ? 1 : 0, h->gacc_active, fused ? 1 : 0,
+    GraphEntry key{format, field, n, omega, launch_tuning(h, format), coulomb ? 1 : 0, h->gacc_active, fused ? 1 : 0,
                    p_sr, seed, 0, nullptr};
     return run_captured(h, key, sweep0, [&]() -> lgf_status {
         for (int k = 0; k < n; ++k)
@@ -631,6 +675,27 @@ lgf::SweepTuning default_fixed_tuning(int format, int64_t V)
         t.lanes_per_site = 1;
         t.block = 128;
         t.schedule = layout;
+    }
+    return t;
+}
+
+// The tuning of the fixed-link sweeps' launches: the handle's where it was
+// set or autotuned, else chosen by the lattice's size, with the same bits.  Up
+// to 2 million sites a contiguous range of tiles per XCD (order 1) beats the
+// other orders, as it does for the link sweeps: 12^4 FP64-12 7.0 -> 6.3 us per
+// launch, 28^4 67.2 -> 61.6, 32^4 105.3 -> 102.3, 36^4 FP32-12 93.4 -> 82.2, 32^4
+// FP64-18 181 -> 147; at 40^4 (2.56 million) 251 against 245 us.  Small lattices
+// take 64-lane workgroups to reach more CUs, and FP32-12 two lanes per site up
+// to 80000 sites, adding the terms of M in the order of one: 12^4 6.7 -> 5.4 us.
+lgf::SweepTuning launch_fixed_tuning(const lgf_lattice *h, int format)
+{
+    lgf::SweepTuning t = h->tune_fixed[format];
+    if (h->tuned_fixed[format] || h->V > 2000000) return t;
+    t.xcd_remap = 1;
+    t.block = (h->V <= kRecordsMinSites) ? 64 : 128;
+    if (format == LGF_FP32_12 && h->V <= 80000) {
+        t.lanes_per_site = 2;
+        t.in_order = 1;
     }
     return t;
 }
@@ -737,7 +802,7 @@ lgf_status run_chunk_fixed(lgf_lattice *h, int format, const void *links, void *
                            double p_sr, uint64_t seed, uint64_t sweep0, bool use_graph, bool fused,
                            bool coulomb = false)
 {
-    const lgf::SweepTuning &t = h->tune_fixed[format];
+    const lgf::SweepTuning t = launch_fixed_tuning(h, format);
     if (fused)
         LGF_TRY(ensure_fused_cap(h, (size_t)lgf::fixed_sweep_groups(h->geom, t) +
                                         (size_t)lgf::fixed_measure_blocks(h->geom)));
@@ -777,7 +842,7 @@ lgf_status measure_fixed_field(lgf_lattice *h, int format, const void *links, co
 {
     int n0 = 0, n1 = 0;
     if (fused) {
-        const int ng = (int)lgf::fixed_sweep_groups(h->geom, h->tune_fixed[format]);
+        const int ng = (int)lgf::fixed_sweep_groups(h->geom, launch_fixed_tuning(h, format));
         LGF_HIP(lgf::launch_measure_fixed(format, links, gf, h->geom, 0, h->d_fused + 2 * (size_t)ng, &n0, h->stream,
                                           fixed_records(h, format)));
         LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->d_out, h->stream));
@@ -1487,7 +1552,7 @@ lgf_status lgf_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_fix_resul
         const int64_t left = p.max_sweeps - sweeps;
         const int n = (int)(left < p.check_every ? left : p.check_every);
         // reunitarize + measure inside the chunk's last half-sweep where possible
-        const bool fuse = !p.separate_measure && can_fuse(h, cur_fmt, p.p_sr, false);
+        const bool fuse = !p.separate_measure && can_fuse(p.p_sr, false);
         LGF_HIP(hipEventRecord(h->ev0, h->stream));
         LGF_TRY(run_chunk(h, cur_fmt, cur, n, p.omega, p.p_sr, p.seed, ctr, p.use_graph != 0, false, fuse));
         LGF_HIP(hipEventRecord(h->ev1, h->stream));
@@ -2009,6 +2074,7 @@ lgf_status lgf_set_tuning(lgf_lattice *h, int format, const lgf_sweep_tuning *t)
     }
     h->tune[format] = lgf::SweepTuning{u.lanes_per_site, u.block,      u.xcd_remap ? 1 : 0, u.nontemporal ? 1 : 0,
                                        u.schedule,       u.sites_per_thread};
+    h->tuned[format] = true;
     drop_graphs(h);
     return LGF_OK;
 }
@@ -2050,6 +2116,7 @@ lgf_status lgf_set_fixed_tuning(lgf_lattice *h, int format, const lgf_sweep_tuni
     // tuning: it is closed (without applying g)
     h->fix_on = false;
     h->tune_fixed[format] = n;
+    h->tuned_fixed[format] = true;
     drop_graphs(h);
     if (h->rec[format] && n.schedule != lgf::kLayoutRecords) {
         // the link field from now on: the records' memory goes back
@@ -2114,8 +2181,15 @@ lgf_status lgf_autotune_fixed(lgf_lattice *h, int format, int trials)
         *ms = elapsed_ms(h->ev0, h->ev1) / n;
         return true;
     };
-    lgf::SweepTuning dflt = default_fixed_tuning(format, h->V);
-    if (!records) dflt.schedule = lgf::kLayoutPlanes;
+    // the default: what untuned launches of this lattice run
+    const lgf::SweepTuning saved = h->tune_fixed[format];
+    const bool was_tuned = h->tuned_fixed[format];
+    h->tune_fixed[format] = default_fixed_tuning(format, h->V);
+    if (!records) h->tune_fixed[format].schedule = lgf::kLayoutPlanes;
+    h->tuned_fixed[format] = false;
+    const lgf::SweepTuning untuned = h->tune_fixed[format], dflt = launch_fixed_tuning(h, format);
+    h->tune_fixed[format] = saved;
+    h->tuned_fixed[format] = was_tuned;
     // warm-up under the same sustained load, as for the link sweeps
     const auto w0 = std::chrono::steady_clock::now();
     for (int k = 0; k < 2000 && e == hipSuccess; k += 20) {
@@ -2137,7 +2211,7 @@ lgf_status lgf_autotune_fixed(lgf_lattice *h, int format, int trials)
             lgf::SweepTuning t{};
             t.lanes_per_site = lps;
             t.block = block;
-            const bool blocked = fp64 && lgf::fixed_order_admitted(h->geom, t, 2);
+            const bool blocked = fp64 && dflt.xcd_remap == 2 && lgf::fixed_order_admitted(h->geom, t, 2);
             for (int order = 0; order < 4; ++order) {
                 if (order >= 2 && !lgf::fixed_order_admitted(h->geom, t, order)) continue;
                 if (blocked && order != 2) continue;
@@ -2155,7 +2229,10 @@ lgf_status lgf_autotune_fixed(lgf_lattice *h, int format, int trials)
                     pick_variant(variants, dflt, trials, "lgf_autotune_fixed", format, time_variant, &best);
     (void)hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return fail(LGF_EHIP, "autotune_fixed: %s", hipGetErrorString(e));
-    if (ok) h->tune_fixed[format] = best;
+    if (ok) {
+        h->tuned_fixed[format] = !(best == dflt);
+        h->tune_fixed[format] = h->tuned_fixed[format] ? best : untuned;
+    }
     drop_graphs(h);
     if (h->rec[format] && !fixed_records(h, format)) {
         // the picked variant reads the link field: the records' memory goes back
@@ -2204,6 +2281,14 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials)
     if (!can_oop && h->tune[format].schedule == lgf::kScheduleOutOfPlace)
         h->tune[format].schedule = lgf::kScheduleInPlace;
     const lgf::SweepTuning saved = h->tune[format];
+    const bool was_tuned = h->tuned[format];
+    // the default: what untuned launches of this lattice run
+    h->tune[format] = default_tuning(format);
+    h->tuned[format] = false;
+    lgf::SweepTuning dflt = launch_tuning(h, format);
+    if (!can_oop && dflt.schedule == lgf::kScheduleOutOfPlace) dflt.schedule = lgf::kScheduleInPlace;
+    h->tune[format] = saved;
+    h->tuned[format] = true;  // while the variants are timed
     lgf_status st = LGF_OK;
     // time n full sweeps of one variant after one untimed full sweep
     auto time_variant = [&](const lgf::SweepTuning &t, int n, double *ms) {
@@ -2247,15 +2332,19 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials)
             }
     lgf::SweepTuning best = saved;
     if (e == hipSuccess && st == LGF_OK)
-        (void)pick_variant(variants, default_tuning(format), trials, "lgf_autotune", format, time_variant, &best);
+        (void)pick_variant(variants, dflt, trials, "lgf_autotune", format, time_variant, &best);
     h->tune[format] = saved;
+    h->tuned[format] = was_tuned;
     if (backup) {
         const hipError_t e2 = hipMemcpyAsync(h->field, backup, bytes, hipMemcpyDeviceToDevice, h->stream);
         if (e == hipSuccess) e = e2;
     }
     (void)hipStreamSynchronize(h->stream);
     if (backup) (void)hipFree(backup);
-    if (st == LGF_OK && e == hipSuccess) h->tune[format] = best;
+    if (st == LGF_OK && e == hipSuccess) {
+        h->tune[format] = best;
+        h->tuned[format] = true;
+    }
     if (!had_partner && h->partner[format] && h->tune[format].schedule != lgf::kScheduleOutOfPlace) {
         (void)hipFree(h->partner[format]);
         h->partner[format] = nullptr;

@@ -24,9 +24,9 @@ namespace lgf {
 // puts on another XCD, and the t-neighbours a whole t-slice of tiles away.
 //   mode 0: lexicographic;
 //   mode 1: contiguous ranges of tiles per XCD;
-//   mode 2: blocks of Bt t-slices x Bz z-planes (all y and x) per XCD, each
+//   mode 2: blocks of B t-slices x B z-planes (all y and x) per XCD, each
 //           walked with z fastest, then t, then the tiles of a plane, so that
-//           the t-, z- and y-neighbours of a tile are 1, Bz and Bt Bz tiles
+//           the t-, z- and y-neighbours of a tile are 1, B and B^2 tiles
 //           earlier or later on the same XCD.  Block k goes to XCD k % 8 (the
 //           dispatch deals workgroup b to XCD b % 8).
 //   mode 3: the (t, z) planes in lexicographic order on all XCDs at once, each
@@ -40,15 +40,17 @@ struct TileOrder {
     uint32_t tile;   // sites per tile
     uint32_t P;      // tiles per (t, z) plane
     uint32_t plane;  // sites per (t, z) plane, Ly Lx / 2
-    uint32_t Bt, Bz, nzb;  // block extents in t and z; Lz / Bz
-    uint32_t tpb;    // tiles per block, Bt Bz P
+    uint32_t lB, nzb;      // log2 of the block extents in t and z; Lz >> lB
+    uint32_t tpb;          // tiles per block, P << 2 lB
+    FastDiv dtpb, dnzb, dG;  // division by tpb, nzb and P / 8
 };
 
 // One half-sweep over all Vh sites of a parity, LPS lanes per site; POST as
 // in update_site_fixed, with workgroup b's (F, theta) sums in partials[2b]
 // when POST == 2.  MU0 = 1: Coulomb gauge, with the timeslice flags
-// slice_active.  REC: the links are per-site link records.
-template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false>
+// slice_active.  REC: the links are per-site link records.  SEQ: 2 lanes per
+// site with the sums of one lane per site.
+template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false, bool SEQ = false>
 __global__ void __launch_bounds__(256, (fixed_waves<F, LPS, POST>())) fixed_sweep_kernel(const void *__restrict__ links, void *__restrict__ gf,
                                                           Geom g, int parity, RelaxArgs<typename Fmt<F>::T> a,
                                                           TileOrder o, uint32_t n_groups,
@@ -60,15 +62,16 @@ __global__ void __launch_bounds__(256, (fixed_waves<F, LPS, POST>())) fixed_swee
     uint32_t slot = b;  // partial-sum slot: the tile's index, < n_groups, so
                         // that the final sum does not depend on the order
     if (o.mode == 2) {
-        const uint32_t s = b >> 3, blk = (s / o.tpb) * 8u + (b & 7u), i = s % o.tpb;
-        const uint32_t r = i % (o.Bt * o.Bz);
-        const uint32_t t = (blk / o.nzb) * o.Bt + r / o.Bz, z = (blk % o.nzb) * o.Bz + r % o.Bz;
-        h0 = (t * g.L[1] + z) * o.plane + (i / (o.Bt * o.Bz)) * o.tile;
-        slot = h0 / o.tile;
+        const uint32_t s = b >> 3, q = fast_div(s, o.dtpb), blk = q * 8u + (b & 7u), i = s - q * o.tpb;
+        const uint32_t tb = fast_div(blk, o.dnzb), zb = blk - tb * o.nzb, m = (1u << o.lB) - 1u;
+        const uint32_t t = (tb << o.lB) + ((i >> o.lB) & m), z = (zb << o.lB) + (i & m);
+        const uint32_t p = t * g.L[1] + z, j = i >> (2 * o.lB);
+        h0 = p * o.plane + j * o.tile;
+        slot = p * o.P + j;
     } else if (o.mode == 3) {
-        const uint32_t s = b >> 3, G = o.P >> 3;
-        h0 = (s / G) * o.plane + ((b & 7u) * G + s % G) * o.tile;
-        slot = h0 / o.tile;
+        const uint32_t s = b >> 3, G = o.P >> 3, p = fast_div(s, o.dG), j = (b & 7u) * G + (s - p * G);
+        h0 = p * o.plane + j * o.tile;
+        slot = p * o.P + j;
     } else if (o.mode == 1) {
         const uint32_t per = gridDim.x >> 3, w = (b & 7u) * per + (b >> 3);
         if (w >= n_groups) return;  // the whole workgroup: no tile
@@ -80,8 +83,8 @@ __global__ void __launch_bounds__(256, (fixed_waves<F, LPS, POST>())) fixed_swee
     const uint32_t grp = h0 + threadIdx.x / LPS;
     const bool active = grp < g.Vh;
     MeasAcc acc;
-    update_site_fixed<F, LPS, SR, POST, MU0, REC>(links, gf, g, parity, active ? grp : g.Vh - 1,
-                                             (int)(threadIdx.x % LPS), active, a, &acc, slice_active);
+    update_site_fixed<F, LPS, SR, POST, MU0, REC, SEQ>(
+        links, gf, g, parity, active ? grp : g.Vh - 1, (int)(threadIdx.x % LPS), active, a, &acc, slice_active);
     if constexpr (POST == 2) block_sum2_any(acc.f, acc.th, partials + 2 * slot);
 }
 
@@ -105,6 +108,7 @@ static TileOrder tile_order(const Geom &g, const SweepTuning &t)
         o.mode = 0;
         if (o.plane % o.tile != 0 || (o.plane / o.tile) % 8 != 0) return o;
         o.P = o.plane / o.tile;
+        o.dG = make_fast_div(o.P / 8);
         o.mode = 3;
         return o;
     }
@@ -112,14 +116,17 @@ static TileOrder tile_order(const Geom &g, const SweepTuning &t)
     o.mode = 0;
     if (o.plane % o.tile != 0) return o;
     o.P = o.plane / o.tile;
-    for (uint32_t B = 8; B >= 2; B >>= 1) {
+    for (uint32_t lB = 3; lB >= 1; --lB) {
+        const uint32_t B = 1u << lB;
         if (g.L[0] % B != 0 || g.L[1] % B != 0) continue;
         const uint32_t nb = (g.L[0] / B) * (g.L[1] / B);
         if (nb % 8 != 0) continue;
         o.mode = 2;
-        o.Bt = o.Bz = B;
+        o.lB = lB;
         o.nzb = g.L[1] / B;
         o.tpb = B * B * o.P;
+        o.dtpb = make_fast_div(o.tpb);
+        o.dnzb = make_fast_div(o.nzb);
         break;
     }
     return o;
@@ -132,7 +139,7 @@ bool fixed_order_admitted(const Geom &g, const SweepTuning &t, int order)
     return (int)tile_order(g, b).mode == order;
 }
 
-template <int F, int LPS, bool REC>
+template <int F, int LPS, bool REC, bool SEQ = false>
 static hipError_t launch_fixed_t(const void *links, void *gf, const Geom &g, const SweepArgs &a, const SweepTuning &t,
                                  int post, const uint8_t *slices, bool coulomb, hipStream_t s)
 {
@@ -147,10 +154,10 @@ static hipError_t launch_fixed_t(const void *links, void *gf, const Geom &g, con
     double *m = a.meas;
     if (post == 2 && (!m || coulomb)) return hipErrorInvalidValue;
 #define LGF_FIX_LAUNCH(SRV, P) \
-    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 0, REC>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
+    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 0, REC, SEQ>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
                        ng, m, nullptr)
 #define LGF_FIX_LAUNCH_C(SRV, P) \
-    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 1, REC>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
+    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 1, REC, SEQ>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
                        ng, nullptr, slices)
     if (coulomb) {
         if (sr) {
@@ -190,7 +197,14 @@ static hipError_t launch_fixed_r(const void *links, void *gf, const Geom &g, con
             return launch_fixed_t<F, 1, REC>(links, gf, g, a, t, post, slices, coulomb, s);
         else
             return hipErrorInvalidValue;
-    case 2: return launch_fixed_t<F, 2, REC>(links, gf, g, a, t, post, slices, coulomb, s);
+    case 2:
+        if (t.in_order) {
+            if constexpr (F == kF32_12)
+                return launch_fixed_t<F, 2, REC, true>(links, gf, g, a, t, post, slices, coulomb, s);
+            else
+                return hipErrorInvalidValue;
+        }
+        return launch_fixed_t<F, 2, REC>(links, gf, g, a, t, post, slices, coulomb, s);
     case 4: return launch_fixed_t<F, 4, REC>(links, gf, g, a, t, post, slices, coulomb, s);
     default: return hipErrorInvalidValue;
     }

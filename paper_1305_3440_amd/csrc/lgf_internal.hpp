@@ -22,6 +22,7 @@ struct SweepTuning {
                              // (parity 1 one slice behind), 2 out of place (ping-pong
                              // between the field and a second buffer of its format)
     int sites_per_thread = 1;  // tiles per workgroup (1, 2 or 4), strided over the launch
+    int in_order = 0;  // fixed-link sweep in FP32-12, 2 lanes per site: the sums, and so the bits, of 1 lane
 };
 
 constexpr int kScheduleInPlace = 0, kSchedulePipeline = 1, kScheduleOutOfPlace = 2;
@@ -31,7 +32,8 @@ constexpr int kLayoutPlanes = 0, kLayoutRecords = 1;
 inline bool operator==(const SweepTuning &a, const SweepTuning &b)
 {
     return a.lanes_per_site == b.lanes_per_site && a.block == b.block && a.xcd_remap == b.xcd_remap &&
-           a.nontemporal == b.nontemporal && a.schedule == b.schedule && a.sites_per_thread == b.sites_per_thread;
+           a.nontemporal == b.nontemporal && a.schedule == b.schedule && a.sites_per_thread == b.sites_per_thread &&
+           a.in_order == b.in_order;
 }
 
 struct SweepArgs {
@@ -88,9 +90,10 @@ hipError_t launch_field_to_canon(int format, const void *field, const int64_t *s
                                  int64_t n, double *canon, const Geom &g, hipStream_t s);
 
 // Coulomb gauge (K from the spatial links, per-timeslice masks and sums).
-// slice_active: device array of Lt flags (NULL = every timeslice).
+// slice_active: device array of Lt flags (NULL = every timeslice).  Of the
+// tuning: 2 lanes per site or (any other) 1, block, xcd_remap, nontemporal.
 hipError_t launch_sweep_coulomb(int format, void *field, const Geom &g, const SweepArgs &a,
-                                const uint8_t *slice_active, bool nt, hipStream_t s);
+                                const uint8_t *slice_active, const SweepTuning &t, hipStream_t s);
 // partials must hold 4 * Lt * coulomb_blocks_per_slice(g) doubles; pass 0
 // writes the first half (parity 0 at partials, parity 1 at the second half is
 // the caller's offset 2 * Lt * blocks)

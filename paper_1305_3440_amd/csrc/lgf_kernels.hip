@@ -39,8 +39,13 @@ size_t link_bytes(int format)
 // workgroups in flight always cover neighbouring tiles.  MEAS: the links are
 // reunitarized as they are written and workgroup b leaves the sums of its
 // sites' F and theta contributions in partials[2b], partials[2b + 1].
+// Two waves per SIMD for overrelaxation on FP64-12 with two lanes per site: its
+// state just fits 256 registers (with the coins of stochastic relaxation it
+// would spill).
+template <int F, int LPS, bool SR> constexpr int sweep_waves() { return (F == kF64_12 && LPS == 2 && !SR) ? 2 : 1; }
+
 template <int F, int LPS, bool SR, bool NT, bool OOP, bool ACC, bool MEAS>
-__global__ void __launch_bounds__(256) sweep_kernel(void *__restrict__ field, Geom g, int parity,
+__global__ void __launch_bounds__(256, (sweep_waves<F, LPS, SR>())) sweep_kernel(void *__restrict__ field, Geom g, int parity,
                                                      RelaxArgs<typename Fmt<F>::T> a, int xcd_remap,
                                                      uint32_t n_groups, uint32_t n_tiles, uint32_t spt,
                                                      uint32_t h_begin, uint32_t h_end,
@@ -112,25 +117,21 @@ static hipError_t launch_sweep_t(void *field, const Geom &g, const SweepArgs &a,
     const bool sr = a.p_sr > 0.0;
     if (sr) ra.sr_threshold = (uint64_t)floor(a.p_sr * 4294967296.0);
     if (a.meas) {
-        // the fused reunitarize + measure: overrelaxation, non-temporal, whole half-sweeps
+        // the fused reunitarize + measure: overrelaxation, whole half-sweeps
         if (sr || a.h_end != 0) return hipErrorInvalidValue;
-        if constexpr (NT) {
-            if (a.gacc) {
-                if constexpr (F == kF32_12 || F == kF32_18)
-                    launch_sweep_kernel<F, LPS, false, NT, OOP, true, true>(grid, t.block, s, field, g, a.parity,
-                                                                            ra, t.xcd_remap, ng, nb, spt, h_begin,
-                                                                            h_end, a.out, a.meas);
-                else
-                    return hipErrorInvalidValue;
-            } else {
-                launch_sweep_kernel<F, LPS, false, NT, OOP, false, true>(grid, t.block, s, field, g, a.parity, ra,
-                                                                         t.xcd_remap, ng, nb, spt, h_begin, h_end,
-                                                                         a.out, a.meas);
-            }
-            return hipGetLastError();
+        if (a.gacc) {
+            if constexpr (F == kF32_12 || F == kF32_18)
+                launch_sweep_kernel<F, LPS, false, NT, OOP, true, true>(grid, t.block, s, field, g, a.parity, ra,
+                                                                        t.xcd_remap, ng, nb, spt, h_begin, h_end,
+                                                                        a.out, a.meas);
+            else
+                return hipErrorInvalidValue;
         } else {
-            return hipErrorInvalidValue;
+            launch_sweep_kernel<F, LPS, false, NT, OOP, false, true>(grid, t.block, s, field, g, a.parity, ra,
+                                                                     t.xcd_remap, ng, nb, spt, h_begin, h_end, a.out,
+                                                                     a.meas);
         }
+        return hipGetLastError();
     }
     if (a.gacc) {
         // the accumulated gauge transformation belongs to the FP32 bulk only
@@ -593,60 +594,76 @@ hipError_t launch_field_to_canon(int format, const void *field, const int64_t *s
 
 namespace lgf {
 
-template <int F, bool SR, bool NT, bool ACC = false>
-__global__ void __launch_bounds__(128) sweep_coulomb_kernel(void *__restrict__ field, Geom g, int parity,
-                                                            RelaxArgs<typename Fmt<F>::T> a,
+template <int F, int LPS, bool SR, bool NT, bool ACC = false>
+__global__ void __launch_bounds__(256) sweep_coulomb_kernel(void *__restrict__ field, Geom g, int parity,
+                                                            RelaxArgs<typename Fmt<F>::T> a, int xcd_remap,
+                                                            uint32_t n_groups,
                                                             const uint8_t *__restrict__ slice_active)
 {
-    const uint32_t h0 = blockIdx.x * 128 + threadIdx.x;
+    uint32_t b = blockIdx.x;
+    if (xcd_remap) {
+        // a contiguous range of workgroups per XCD, as in sweep_kernel
+        b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
+        if (b >= n_groups) return;
+    }
+    const uint32_t tid = b * blockDim.x + threadIdx.x;
+    const uint32_t h0 = tid / LPS;
     const bool active = h0 < g.Vh;
-    update_site<F, 1, SR, NT, 1, false, ACC>(field, g, parity, active ? h0 : g.Vh - 1, 0, active, a, slice_active);
+    update_site<F, LPS, SR, NT, 1, false, ACC>(field, g, parity, active ? h0 : g.Vh - 1, (int)(tid % LPS), active, a,
+                                               slice_active);
 }
 
-template <int F, bool NT>
+template <int F, int LPS, bool NT>
 static hipError_t launch_sweep_coulomb_t(void *field, const Geom &g, const SweepArgs &a,
-                                         const uint8_t *slice_active, hipStream_t s)
+                                         const uint8_t *slice_active, const SweepTuning &t, hipStream_t s)
 {
     using T = typename Fmt<F>::T;
-    const dim3 grid((g.Vh + 127) / 128);
+    const uint32_t ng = (uint32_t)(((uint64_t)g.Vh * LPS + t.block - 1) / t.block);
+    const dim3 grid(t.xcd_remap ? ((ng + 7u) / 8u) * 8u : ng), block(t.block);
     RelaxArgs<T> ra{(T)a.omega, (a.omega != 1.0) ? 1 : 0, 0, (uint32_t)a.seed, (uint32_t)(a.seed >> 32),
                     (uint32_t)a.sweep_index, a.instance, a.gacc, a.sweep_base};
     const bool sr = a.p_sr > 0.0;
     if (sr) ra.sr_threshold = (uint64_t)floor(a.p_sr * 4294967296.0);
+#define LGF_SC(SRV, ACCV)                                                                                            \
+    hipLaunchKernelGGL((sweep_coulomb_kernel<F, LPS, SRV, NT, ACCV>), grid, block, 0, s, field, g, a.parity, ra,     \
+                       t.xcd_remap, ng, slice_active)
     if (a.gacc) {
         // the accumulated gauge transformation belongs to the FP32 bulk only
         if constexpr (F == kF32_12 || F == kF32_18) {
-            if (sr)
-                hipLaunchKernelGGL((sweep_coulomb_kernel<F, true, NT, true>), grid, dim3(128), 0, s, field, g,
-                                   a.parity, ra, slice_active);
-            else
-                hipLaunchKernelGGL((sweep_coulomb_kernel<F, false, NT, true>), grid, dim3(128), 0, s, field, g,
-                                   a.parity, ra, slice_active);
+            if (sr) LGF_SC(true, true);
+            else LGF_SC(false, true);
         } else {
             return hipErrorInvalidValue;
         }
     } else if (sr) {
-        hipLaunchKernelGGL((sweep_coulomb_kernel<F, true, NT>), grid, dim3(128), 0, s, field, g, a.parity, ra,
-                           slice_active);
+        LGF_SC(true, false);
     } else {
-        hipLaunchKernelGGL((sweep_coulomb_kernel<F, false, NT>), grid, dim3(128), 0, s, field, g, a.parity, ra,
-                           slice_active);
+        LGF_SC(false, false);
     }
+#undef LGF_SC
     return hipGetLastError();
 }
 
-hipError_t launch_sweep_coulomb(int format, void *field, const Geom &g, const SweepArgs &a,
-                                const uint8_t *slice_active, bool nt, hipStream_t s)
+template <int F>
+static hipError_t launch_sweep_coulomb_f(void *field, const Geom &g, const SweepArgs &a, const uint8_t *slice_active,
+                                         const SweepTuning &t, hipStream_t s)
 {
-    switch (format * 2 + (nt ? 1 : 0)) {
-    case 0: return launch_sweep_coulomb_t<kF64_18, false>(field, g, a, slice_active, s);
-    case 1: return launch_sweep_coulomb_t<kF64_18, true>(field, g, a, slice_active, s);
-    case 2: return launch_sweep_coulomb_t<kF32_18, false>(field, g, a, slice_active, s);
-    case 3: return launch_sweep_coulomb_t<kF32_18, true>(field, g, a, slice_active, s);
-    case 4: return launch_sweep_coulomb_t<kF32_12, false>(field, g, a, slice_active, s);
-    case 5: return launch_sweep_coulomb_t<kF32_12, true>(field, g, a, slice_active, s);
-    case 6: return launch_sweep_coulomb_t<kF64_12, false>(field, g, a, slice_active, s);
-    case 7: return launch_sweep_coulomb_t<kF64_12, true>(field, g, a, slice_active, s);
+    if (t.lanes_per_site == 2)
+        return t.nontemporal ? launch_sweep_coulomb_t<F, 2, true>(field, g, a, slice_active, t, s)
+                             : launch_sweep_coulomb_t<F, 2, false>(field, g, a, slice_active, t, s);
+    return t.nontemporal ? launch_sweep_coulomb_t<F, 1, true>(field, g, a, slice_active, t, s)
+                         : launch_sweep_coulomb_t<F, 1, false>(field, g, a, slice_active, t, s);
+}
+
+hipError_t launch_sweep_coulomb(int format, void *field, const Geom &g, const SweepArgs &a,
+                                const uint8_t *slice_active, const SweepTuning &t, hipStream_t s)
+{
+    if (t.block <= 0 || t.block > 256 || (t.block % 64) != 0) return hipErrorInvalidValue;
+    switch (format) {
+    case kF64_18: return launch_sweep_coulomb_f<kF64_18>(field, g, a, slice_active, t, s);
+    case kF32_18: return launch_sweep_coulomb_f<kF32_18>(field, g, a, slice_active, t, s);
+    case kF32_12: return launch_sweep_coulomb_f<kF32_12>(field, g, a, slice_active, t, s);
+    case kF64_12: return launch_sweep_coulomb_f<kF64_12>(field, g, a, slice_active, t, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -22,7 +22,7 @@ __device__ __forceinline__ void su2_step(mat3<T> &W, mat3<T> &G, T omega, bool o
     const T n2 = a0 * a0 + a1 * a1 + a2 * a2 + a3 * a3;
     T r0 = T(1), r1 = T(0), r2 = T(0), r3 = T(0);
     if (n2 > T(0)) {
-        const T inv = exact_rsqrt<T>(n2);
+        const T inv = inv_sqrt<T>(n2);
         const T b0 = a0 * inv, b1 = -a1 * inv, b2 = -a2 * inv, b3 = -a3 * inv;
         if (square) {
             r0 = b0 * b0 - (b1 * b1 + b2 * b2 + b3 * b3);
@@ -32,7 +32,7 @@ __device__ __forceinline__ void su2_step(mat3<T> &W, mat3<T> &G, T omega, bool o
         } else if (overrelax) {
             const T c0 = (T(1) - omega) + omega * b0;
             const T c1 = omega * b1, c2 = omega * b2, c3 = omega * b3;
-            const T ic = exact_rsqrt<T>(c0 * c0 + c1 * c1 + c2 * c2 + c3 * c3);
+            const T ic = inv_sqrt<T>(c0 * c0 + c1 * c1 + c2 * c2 + c3 * c3);
             r0 = c0 * ic; r1 = c1 * ic; r2 = c2 * ic; r3 = c3 * ic;
         } else {
             r0 = b0; r1 = b1; r2 = b2; r3 = b3;
@@ -53,6 +53,43 @@ __device__ __forceinline__ void su2_step(mat3<T> &W, mat3<T> &G, T omega, bool o
     }
 }
 
+
+// acc += p of the even lane, then p of the odd lane (pairs of lanes that share a site)
+template <typename T> __device__ __forceinline__ void add_pair(mat3<T> &acc, const mat3<T> &p)
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            acc.e[i][j].re = acc.e[i][j].re + pair_even(p.e[i][j].re);
+            acc.e[i][j].re = acc.e[i][j].re + pair_odd(p.e[i][j].re);
+            acc.e[i][j].im = acc.e[i][j].im + pair_even(p.e[i][j].im);
+            acc.e[i][j].im = acc.e[i][j].im + pair_odd(p.e[i][j].im);
+        }
+}
+
+// acc += f + b^dag of the even lane (EVEN), then of the odd lane
+template <bool EVEN, typename T>
+__device__ __forceinline__ void add_pair_fwd_bwd(mat3<T> &acc, const mat3<T> &f, const mat3<T> &b)
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            T re = acc.e[i][j].re, im = acc.e[i][j].im;
+            if constexpr (EVEN) {
+                re = re + pair_even(f.e[i][j].re);
+                im = im + pair_even(f.e[i][j].im);
+                re = re + pair_even(b.e[j][i].re);
+                im = im + -pair_even(b.e[j][i].im);
+            }
+            re = re + pair_odd(f.e[i][j].re);
+            im = im + pair_odd(f.e[i][j].im);
+            re = re + pair_odd(b.e[j][i].re);
+            im = im + -pair_odd(b.e[j][i].im);
+            acc.e[i][j] = {re, im};
+        }
+}
 
 // u <- u as stored in format F and read back; o receives the stored value
 template <int F>
@@ -140,12 +177,9 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
     using T = typename S::T;
     constexpr int NL = 4 / LPS;  // directions handled per lane
     const Site c = decode(g, parity, h);
-    if (slice_active) {
-        // a frozen timeslice is neither read nor written; with one lane per
-        // site no other lane waits on this one
-        if (LPS == 1 && !slice_active[c.t]) return;
-        active = active && slice_active[c.t];
-    }
+    // a frozen timeslice is neither read nor written; the lanes of a site
+    // share its timeslice, so they leave together
+    if (slice_active && !slice_active[c.t]) return;
 
     mat3<T> uf[NL], ub[NL];
     uint32_t hb[NL];
@@ -159,10 +193,28 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
 
     mat3<T> K;
     set_zero(K);
+    if constexpr (LPS == 2) {
+        // the directions in the order of one lane per site: the same bits
+        const bool first = MU0 == 0 || lane != 0;  // the lane's first direction counts
 #pragma unroll
-    for (int k = 0; k < NL; ++k)
-        if (lane + k * LPS >= MU0) add_fwd_bwd(K, uf[k], ub[k]);
-    lane_sum<LPS>(K);
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                T re = first ? uf[0].e[i][j].re + ub[0].e[j][i].re : T(0);
+                T im = first ? uf[0].e[i][j].im - ub[0].e[j][i].im : T(0);
+                re = re + quad_perm<1, 0, 3, 2>(re);
+                im = im + quad_perm<1, 0, 3, 2>(im);
+                const T r1 = uf[1].e[i][j].re + ub[1].e[j][i].re, i1 = uf[1].e[i][j].im - ub[1].e[j][i].im;
+                re = re + pair_even(r1);
+                im = im + pair_even(i1);
+                K.e[i][j] = {re + pair_odd(r1), im + pair_odd(i1)};
+            }
+    } else {
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (lane + k * LPS >= MU0) add_fwd_bwd(K, uf[k], ub[k]);
+        lane_sum<LPS>(K);
+    }
 
     bool sq0 = false, sq1 = false, sq2 = false;
     if constexpr (SR) {
@@ -192,8 +244,13 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
     }
     mat3<double> Kn;
     if constexpr (MEAS) set_zero(Kn);
+    // The store addresses are formed anew: kept from the loads, the 64-bit
+    // addresses of the in-place update take more registers than the links.
+    uint32_t hs = h;
+    forget(hs);
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
+        forget(hb[k]);
         const int mu = lane + k * LPS;
         mat3<T> r, rb;
         left_mul<S::R>(r, G, uf[k]);
@@ -209,13 +266,20 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
             round_to_format<F>(df, r);
             round_to_format<F>(db, rb);
             acc->f += df.e[0][0].re + df.e[1][1].re + df.e[2][2].re;
-            add_fwd_bwd(Kn, df, db);
+            if constexpr (LPS == 2) {
+                mat3<double> d;
+                set_zero(d);
+                add_fwd_bwd(d, df, db);
+                add_pair(Kn, d);
+            } else {
+                add_fwd_bwd(Kn, df, db);
+            }
         }
-        store_link<F, NT>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity, mu), g.Vh, h, r);
+        store_link<F, NT>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity, mu), g.Vh, hs, r);
         store_link<F, NT>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity ^ 1, mu), g.Vh, hb[k], rb);
     }
     if constexpr (MEAS) {
-        lane_sum<LPS>(Kn);
+        if constexpr (LPS != 2) lane_sum<LPS>(Kn);
         if (lane == 0) acc->th += theta_of_K(Kn);
     }
 }
@@ -400,13 +464,17 @@ template <int F, int LPS, int POST> constexpr int fixed_waves()
 // a site share its timeslice, so they leave together.
 // REC: links holds the per-site link records of format F (12-real or split; the
 // same values, so the same arithmetic and bits as from the link field).
-template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false>
+// SEQ (2 lanes, FP32): the terms of M are added direction by direction, as one
+// lane per site adds them, so the two forms give the same bits; otherwise each
+// lane adds its own terms and the lanes' sums are added.
+template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false, bool SEQ = false>
 __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links, void *__restrict__ gf,
                                                   const Geom &g, int parity, uint32_t h, int lane, bool active,
                                                   const RelaxArgs<typename Fmt<F>::T> &a, MeasAcc *acc,
                                                   const uint8_t *__restrict__ slice_active = nullptr)
 {
     static_assert(!(POST == 2 && MU0 != 0), "the fused measurement is the Landau one");
+    static_assert(!SEQ || (LPS == 2 && sizeof(typename Fmt<F>::T) == sizeof(float)), "SEQ: 2 lanes in FP32");
     using S = Fmt<F>;
     using T = typename S::T;
     constexpr int NL = 4 / LPS;
@@ -429,34 +497,53 @@ __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
         const int mu = lane + k * LPS;
-        if (mu < MU0) continue;
-        mat3<T> u, y, p;
-        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, rp);
-        else load_fixed_link<F>(u, U, g.Vh, parity, mu, h);
-        load_link<F, false, false>(y, gn, g.Vh, fwd_half(g, c, h, mu));
-        if constexpr (R == 2) row2_fma(y);
-        mul_dag_fma<R>(p, u, y);  // U_mu(x) g(x+mu)^dag
-        if constexpr (R == 2) row2_fma(p);
-        add_to(M, p);
-        if constexpr (POST == 2) {
-            if constexpr (sizeof(T) == sizeof(double)) add_to(Mf, p);
-            else meas_term_fwd<R>(Mf, u, y);
+        mat3<T> pf, pb;          // U_mu(x) g(x+mu)^dag and g(x-mu) U_mu(x-mu)
+        mat3<double> mf, mb;     // POST == 2, FP32: the same in FP64
+        if constexpr (SEQ) {
+            set_zero(pf);
+            set_zero(pb);
+            set_zero(mf);
+            set_zero(mb);
         }
-        const uint32_t hb = back_half(g, c, h, mu);
-        if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, rp);
-        else load_fixed_link<F>(u, U, g.Vh, parity ^ 1, mu, hb);
-        load_link<F, false, false>(y, gn, g.Vh, hb);
-        if constexpr (R == 2) row2_fma(u);
-        mul_fma<R>(p, y, u);  // g(x-mu) U_mu(x-mu)
-        if constexpr (R == 2) row2_fma(p);
-        add_dag_to(M, p);
-        // (FP64 formats: the backward terms are in M already; see below)
-        if constexpr (POST == 2 && sizeof(T) != sizeof(double)) meas_term_bwd<R>(Mb, y, u);
+        if (mu >= MU0) {
+            mat3<T> u, y;
+            if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, rp);
+            else load_fixed_link<F>(u, U, g.Vh, parity, mu, h);
+            load_link<F, false, false>(y, gn, g.Vh, fwd_half(g, c, h, mu));
+            if constexpr (R == 2) row2_fma(y);
+            mul_dag_fma<R>(pf, u, y);
+            if constexpr (R == 2) row2_fma(pf);
+            if constexpr (!SEQ) add_to(M, pf);
+            if constexpr (POST == 2) {
+                if constexpr (sizeof(T) == sizeof(double)) add_to(Mf, pf);
+                else meas_term_fwd<R>(SEQ ? mf : Mf, u, y);
+            }
+            const uint32_t hb = back_half(g, c, h, mu);
+            if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, rp);
+            else load_fixed_link<F>(u, U, g.Vh, parity ^ 1, mu, hb);
+            load_link<F, false, false>(y, gn, g.Vh, hb);
+            if constexpr (R == 2) row2_fma(u);
+            mul_fma<R>(pb, y, u);
+            if constexpr (R == 2) row2_fma(pb);
+            if constexpr (!SEQ) add_dag_to(M, pb);
+            // (FP64 formats: the backward terms are in M already; see below)
+            if constexpr (POST == 2 && sizeof(T) != sizeof(double)) meas_term_bwd<R>(SEQ ? mb : Mb, y, u);
+        }
+        if constexpr (SEQ) {
+            if (k * LPS >= MU0) add_pair_fwd_bwd<true>(M, pf, pb);
+            else add_pair_fwd_bwd<false>(M, pf, pb);
+            if constexpr (POST == 2) {
+                add_pair(Mf, mf);
+                add_pair(Mb, mb);
+            }
+        }
     }
-    lane_sum<LPS>(M);
-    if constexpr (POST == 2) {
-        lane_sum<LPS>(Mf);
-        if constexpr (sizeof(T) != sizeof(double)) lane_sum<LPS>(Mb);
+    if constexpr (!SEQ) {
+        lane_sum<LPS>(M);
+        if constexpr (POST == 2) {
+            lane_sum<LPS>(Mf);
+            if constexpr (sizeof(T) != sizeof(double)) lane_sum<LPS>(Mb);
+        }
     }
 
     bool sq0 = false, sq1 = false, sq2 = false;
