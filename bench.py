@@ -213,8 +213,8 @@ def summarize_traffic(fetch_dir, write_dir, dims, command):
     import csv
     per = {}
     fixed_seq = {}  # (counter, format, lanes, layout) -> plain fixed-sweep readings in dispatch order
-    # fixed_sweep_kernel<format, lanes, SR, post, mu0, records>: the plain Landau instances
-    fixed_pat = re.compile(r"fixed_sweep_kernel<(\d+),\s*(\d+),\s*false,\s*0,\s*0,\s*(true|false)>")
+    # fixed_sweep_kernel<format, lanes, SR, post, mu0, records (, in order)>: the plain Landau instances
+    fixed_pat = re.compile(r"fixed_sweep_kernel<(\d+),\s*(\d+),\s*false,\s*0,\s*0,\s*(true|false)(?:,\s*false)?>")
     for counter, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         with open(_find(d, "counter_collection.csv")) as f:
             rows = [r for r in csv.DictReader(f) if r.get("Counter_Name") == counter]
