@@ -125,8 +125,7 @@ struct lgf_lattice {
     bool own_stream;
     int device;
     double *d_partials;
-    double *d_out;
-    double *h_out;  // pinned, 2 doubles
+    double *h_out;  // pinned, 2 doubles: the final sums write F and theta there
     double *d_stage;
     int64_t *d_sites;
     int64_t sites_cap;
@@ -141,12 +140,12 @@ struct lgf_lattice {
     bool tuned[4];        // set or autotuned; else launches choose by size (launch_tuning)
     std::vector<GraphEntry> graphs;
     hipEvent_t ev0, ev1;
+    lgf::PhaseClock clock;
     // Coulomb gauge: timeslice flags and per-timeslice reductions (lazily)
     uint8_t *d_mask;
     uint8_t *h_mask;   // pinned, Lt flags
     double *d_cpart;
-    double *d_cout;
-    double *h_cout;    // pinned, 2 Lt doubles
+    double *h_cout;    // pinned, 2 Lt doubles: the per-timeslice sums are written there
     // accumulated gauge transformation of the mixed-precision bulk
     void *gacc;        // site field in the bulk format (owned), or NULL
     size_t gacc_bytes;
@@ -337,17 +336,14 @@ void prepare_schedule(lgf_lattice *h, int format)
 // F and theta of a field; with reunit the links are first projected onto
 // SU(3) in FP64 (fused: parity 0 reunitarizes its forward links and, in
 // registers, its backward links; parity 1 then reads the already stored ones).
-lgf_status measure_field(lgf_lattice *h, int format, void *field, bool reunit, double *F, double *theta)
+// Enqueued only: F and theta are in h->h_out once the stream has been waited for.
+lgf_status measure_field(lgf_lattice *h, int format, void *field, bool reunit)
 {
     int n0 = 0, n1 = 0;
     LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, reunit, reunit, h->d_partials, &n0, h->stream));
     LGF_HIP(lgf::launch_measure(format, field, h->geom, 1, reunit, false, h->d_partials + 2 * n0, &n1,
                                 h->stream));
-    LGF_HIP(lgf::launch_finish_measure(h->d_partials, n0 + n1, (double)h->V, h->d_out, h->stream));
-    LGF_HIP(hipMemcpyAsync(h->h_out, h->d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    LGF_HIP(hipStreamSynchronize(h->stream));
-    if (F) *F = h->h_out[0];
-    if (theta) *theta = h->h_out[1];
+    LGF_HIP(lgf::launch_finish_measure(h->d_partials, n0 + n1, (double)h->V, h->h_out, h->stream));
     return LGF_OK;
 }
 
@@ -435,7 +431,6 @@ lgf_status ensure_coulomb(lgf_lattice *h)
     if ((e = hipMalloc(&h->d_mask, Lt)) != hipSuccess ||
         (e = hipHostMalloc((void **)&h->h_mask, Lt, hipHostMallocDefault)) != hipSuccess ||
         (e = hipMalloc(&h->d_cpart, parts * sizeof(double))) != hipSuccess ||
-        (e = hipMalloc(&h->d_cout, 2 * Lt * sizeof(double))) != hipSuccess ||
         (e = hipHostMalloc((void **)&h->h_cout, 2 * Lt * sizeof(double), hipHostMallocDefault)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(LGF_ENOMEM, "Coulomb scratch allocation failed: %s", hipGetErrorString(e));
@@ -443,27 +438,25 @@ lgf_status ensure_coulomb(lgf_lattice *h)
     return LGF_OK;
 }
 
-// copy the host flags (NULL = all active) to the device mask; synchronises
+// copy the host flags (NULL = all active) to the device mask; the caller waits
+// for the stream before the next call (the copy reads h->h_mask)
 lgf_status upload_mask(lgf_lattice *h, const unsigned char *flags)
 {
     for (int t = 0; t < h->dims[0]; ++t) h->h_mask[t] = flags ? (flags[t] ? 1 : 0) : 1;
     LGF_HIP(hipMemcpyAsync(h->d_mask, h->h_mask, h->dims[0], hipMemcpyHostToDevice, h->stream));
-    LGF_HIP(hipStreamSynchronize(h->stream));
     return LGF_OK;
 }
 
-// per-timeslice F_C(t), theta_C(t) into h->h_cout (2 Lt doubles); with reunit
-// the fused FP64 reunitarization of every link first
+// per-timeslice F_C(t), theta_C(t) into h->h_cout (2 Lt doubles, there once the
+// stream has been waited for); with reunit the fused FP64 reunitarization of
+// every link first
 lgf_status measure_coulomb_field(lgf_lattice *h, int format, void *field, bool reunit)
 {
     const size_t half = (size_t)2 * h->dims[0] * lgf::coulomb_blocks_per_slice(h->geom);
     LGF_HIP(lgf::launch_measure_coulomb(format, field, h->geom, 0, reunit, reunit, h->d_cpart, h->stream));
     LGF_HIP(lgf::launch_measure_coulomb(format, field, h->geom, 1, reunit, false, h->d_cpart + half, h->stream));
-    LGF_HIP(lgf::launch_finish_coulomb(h->d_cpart, h->geom, lgf::coulomb_blocks_per_slice(h->geom), h->d_cout,
+    LGF_HIP(lgf::launch_finish_coulomb(h->d_cpart, h->geom, lgf::coulomb_blocks_per_slice(h->geom), h->h_cout,
                                        h->stream));
-    LGF_HIP(hipMemcpyAsync(h->h_cout, h->d_cout, 2 * h->dims[0] * sizeof(double), hipMemcpyDeviceToHost,
-                           h->stream));
-    LGF_HIP(hipStreamSynchronize(h->stream));
     return LGF_OK;
 }
 
@@ -502,17 +495,14 @@ lgf_status ensure_fused(lgf_lattice *h, int format)
 // F and theta after a chunk whose last half-sweep was fused: its partial sums
 // (parity-1 sites' theta, parity-1 forward links' Re tr, from the links as
 // reunitarized and stored) plus a read-only pass over the parity-0 sites.
-lgf_status measure_fused(lgf_lattice *h, int format, void *field, double *F, double *theta)
+// Enqueued only, as measure_field.
+lgf_status measure_fused(lgf_lattice *h, int format, void *field)
 {
     const int ng = (int)lgf::sweep_groups(h->geom, launch_tuning(h, format));
     int n0 = 0;
     LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, false, false, h->d_fused + 2 * (size_t)ng, &n0,
                                 h->stream));
-    LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->d_out, h->stream));
-    LGF_HIP(hipMemcpyAsync(h->h_out, h->d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    LGF_HIP(hipStreamSynchronize(h->stream));
-    if (F) *F = h->h_out[0];
-    if (theta) *theta = h->h_out[1];
+    LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->h_out, h->stream));
     return LGF_OK;
 }
 
@@ -837,15 +827,15 @@ lgf_status run_chunk_fixed(lgf_lattice *h, int format, const void *links, void *
 // F and theta of the links g(x) U_mu(x) g(x+mu)^dag: after a fused chunk its
 // partial sums plus a read-only pass over the parity-0 sites, else a pass
 // over each parity
-lgf_status measure_fixed_field(lgf_lattice *h, int format, const void *links, const void *gf, bool fused,
-                               double *F, double *theta)
+// (enqueued only, as measure_field)
+lgf_status measure_fixed_field(lgf_lattice *h, int format, const void *links, const void *gf, bool fused)
 {
     int n0 = 0, n1 = 0;
     if (fused) {
         const int ng = (int)lgf::fixed_sweep_groups(h->geom, launch_fixed_tuning(h, format));
         LGF_HIP(lgf::launch_measure_fixed(format, links, gf, h->geom, 0, h->d_fused + 2 * (size_t)ng, &n0, h->stream,
                                           fixed_records(h, format)));
-        LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->d_out, h->stream));
+        LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->h_out, h->stream));
     } else {
         // the two passes' partial sums in the fused-measurement buffer
         LGF_TRY(ensure_fused_cap(h, 2 * (size_t)lgf::fixed_measure_blocks(h->geom)));
@@ -853,16 +843,13 @@ lgf_status measure_fixed_field(lgf_lattice *h, int format, const void *links, co
                                           fixed_records(h, format)));
         LGF_HIP(lgf::launch_measure_fixed(format, links, gf, h->geom, 1, h->d_fused + 2 * (size_t)n0, &n1,
                                           h->stream, fixed_records(h, format)));
-        LGF_HIP(lgf::launch_finish_measure(h->d_fused, n0 + n1, (double)h->V, h->d_out, h->stream));
+        LGF_HIP(lgf::launch_finish_measure(h->d_fused, n0 + n1, (double)h->V, h->h_out, h->stream));
     }
-    LGF_HIP(hipMemcpyAsync(h->h_out, h->d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    LGF_HIP(hipStreamSynchronize(h->stream));
-    if (F) *F = h->h_out[0];
-    if (theta) *theta = h->h_out[1];
     return LGF_OK;
 }
 
 // per-timeslice F_C(t), theta_C(t) of the links g U g^dag into h->h_cout
+// (enqueued only)
 lgf_status measure_coulomb_fixed_field(lgf_lattice *h, int format, const void *links, const void *gf)
 {
     const int bps = lgf::coulomb_fixed_blocks(h->geom);
@@ -870,10 +857,7 @@ lgf_status measure_coulomb_fixed_field(lgf_lattice *h, int format, const void *l
     const bool rec = fixed_records(h, format);
     LGF_HIP(lgf::launch_measure_coulomb_fixed(format, links, gf, h->geom, 0, h->d_cpart, h->stream, rec));
     LGF_HIP(lgf::launch_measure_coulomb_fixed(format, links, gf, h->geom, 1, h->d_cpart + half, h->stream, rec));
-    LGF_HIP(lgf::launch_finish_coulomb(h->d_cpart, h->geom, bps, h->d_cout, h->stream));
-    LGF_HIP(hipMemcpyAsync(h->h_cout, h->d_cout, 2 * h->dims[0] * sizeof(double), hipMemcpyDeviceToHost,
-                           h->stream));
-    LGF_HIP(hipStreamSynchronize(h->stream));
+    LGF_HIP(lgf::launch_finish_coulomb(h->d_cpart, h->geom, bps, h->h_cout, h->stream));
     return LGF_OK;
 }
 
@@ -895,17 +879,25 @@ lgf_status gauge_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, in
             ++nh;
         }
     };
+    lgf::PhaseClock &clock = h->clock;
+    clock.reset();
+    // work whose time goes to acc_ms, enqueued only
     auto timed = [&](double &acc_ms, auto &&body) -> lgf_status {
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
         LGF_TRY(body());
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        acc_ms += elapsed_ms(h->ev0, h->ev1);
+        LGF_HIP(clock.mark(&acc_ms, h->stream));
         return LGF_OK;
     };
 
     double F = 0.0, theta = 0.0;
-    LGF_TRY(timed(res->t_measure_ms, [&]() { return measure_field(h, h->format, h->field, false, &F, &theta); }));
+    auto read_out = [&]() -> lgf_status {
+        LGF_HIP(clock.wait());
+        F = h->h_out[0];
+        theta = h->h_out[1];
+        return LGF_OK;
+    };
+    LGF_TRY(timed(res->t_measure_ms, [&]() { return measure_field(h, h->format, h->field, false); }));
+    LGF_TRY(read_out());
     record(0, F, theta);
 
     int64_t sweeps = 0, sweeps_bulk = 0;
@@ -940,7 +932,8 @@ lgf_status gauge_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, in
             sweeps += n;
             ctr += (uint64_t)n;
             LGF_TRY(timed(res->t_measure_ms,
-                          [&]() { return measure_fixed_field(h, cur, links, gfix_of(h, cur), fuse, &F, &theta); }));
+                          [&]() { return measure_fixed_field(h, cur, links, gfix_of(h, cur), fuse); }));
+            LGF_TRY(read_out());
             record(sweeps, F, theta);
             if (!std::isfinite(F) || !std::isfinite(theta)) {
                 status = LGF_ENUMERIC;
@@ -964,8 +957,9 @@ lgf_status gauge_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, in
                 in_bulk = false;
                 if (theta < p.theta_target) {
                     LGF_TRY(timed(res->t_measure_ms, [&]() {
-                        return measure_fixed_field(h, cur, links, gfix_of(h, cur), false, &F, &theta);
+                        return measure_fixed_field(h, cur, links, gfix_of(h, cur), false);
                     }));
+                    LGF_TRY(read_out());
                     record(sweeps, F, theta);
                 } else {
                     continue;
@@ -985,7 +979,8 @@ lgf_status gauge_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, in
                 // the sweeps measured on the split links (within 2^-40 of the
                 // input's): F and theta of the result from the FP64 links themselves
                 LGF_TRY(timed(res->t_measure_ms,
-                              [&]() { return measure_field(h, h->format, h->field, false, &F, &theta); }));
+                              [&]() { return measure_field(h, h->format, h->field, false); }));
+                LGF_TRY(read_out());
                 record(sweeps, F, theta);
                 if (!std::isfinite(F) || !std::isfinite(theta)) {
                     status = LGF_ENUMERIC;
@@ -1010,6 +1005,7 @@ lgf_status gauge_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, in
         }
         break;
     }
+    LGF_HIP(clock.wait());
     res->sweeps = sweeps;
     res->sweeps_bulk = sweeps_bulk;
     res->theta = theta;
@@ -1038,20 +1034,23 @@ lgf_status coulomb_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, 
     const auto t_start = std::chrono::steady_clock::now();
     std::vector<double> sw(Lt, 0.0), F(Lt), th(Lt);
     std::vector<unsigned char> act(Lt, 1);
+    lgf::PhaseClock &clock = h->clock;
+    clock.reset();
+    // work whose time goes to acc_ms, enqueued only
     auto timed = [&](double &acc_ms, auto &&body) -> lgf_status {
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
         LGF_TRY(body());
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        acc_ms += elapsed_ms(h->ev0, h->ev1);
+        LGF_HIP(clock.mark(&acc_ms, h->stream));
         return LGF_OK;
     };
-    auto read_out = [&](bool only_active) {
+    auto read_out = [&](bool only_active) -> lgf_status {
+        LGF_HIP(clock.wait());
         for (int t = 0; t < Lt; ++t)
             if (!only_active || act[t]) {
                 F[t] = h->h_cout[2 * t];
                 th[t] = h->h_cout[2 * t + 1];
             }
+        return LGF_OK;
     };
     auto n_live = [&] {
         int n = 0;
@@ -1066,7 +1065,7 @@ lgf_status coulomb_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, 
     };
     // the input itself (g = 1)
     LGF_TRY(timed(res->t_measure_ms, [&]() { return measure_coulomb_field(h, h->format, h->field, false); }));
-    read_out(false);
+    LGF_TRY(read_out(false));
     lgf_status status = LGF_ENOTCONV;
     for (int t = 0; t < Lt; ++t) {
         if (!std::isfinite(F[t]) || !std::isfinite(th[t])) status = LGF_ENUMERIC;
@@ -1088,6 +1087,7 @@ lgf_status coulomb_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, 
         started = true;
     }
     while (status != LGF_ENUMERIC && n_live() > 0 && sweeps < p.max_sweeps) {
+        // (the last measurement's wait covers the last chunk's copy)
         LGF_TRY(upload_mask(h, act.data()));
         const int64_t left = p.max_sweeps - sweeps;
         const int n = (int)(left < p.check_every ? left : p.check_every);
@@ -1099,7 +1099,7 @@ lgf_status coulomb_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, 
         sweeps += n;
         ctr += (uint64_t)n;
         LGF_TRY(timed(res->t_measure_ms, [&]() { return measure_coulomb_fixed_field(h, cur, links, gfix_of(h, cur)); }));
-        read_out(true);
+        LGF_TRY(read_out(true));
         ++nh;
         for (int t = 0; t < Lt; ++t) {
             if (!act[t]) continue;
@@ -1136,12 +1136,13 @@ lgf_status coulomb_fix_fixed(lgf_lattice *h, const lgf_fix_params &p, int bulk, 
             // the sweeps measured on the split links: every timeslice's F_C and
             // theta_C of the result from the FP64 links themselves
             LGF_TRY(timed(res->t_measure_ms, [&]() { return measure_coulomb_field(h, h->format, h->field, false); }));
-            read_out(false);
+            LGF_TRY(read_out(false));
             if (status == LGF_OK)
                 for (int t = 0; t < Lt; ++t)
                     if (!(th[t] < p.theta_target)) status = LGF_ENOTCONV;
         }
     }
+    LGF_HIP(clock.wait());
     double tmax = 0.0, fsum = 0.0;
     for (int t = 0; t < Lt; ++t) {
         tmax = th[t] > tmax ? th[t] : tmax;
@@ -1254,10 +1255,10 @@ lgf_status lgf_create(const int dims[4], int format, void *stream, void *device_
     }
     const int nb = lgf::measure_blocks(h->geom);
     if ((e = hipMalloc(&h->d_partials, (size_t)4 * nb * sizeof(double))) != hipSuccess ||
-        (e = hipMalloc(&h->d_out, 2 * sizeof(double))) != hipSuccess ||
         (e = hipMalloc(&h->d_sweep_base, sizeof(uint64_t))) != hipSuccess ||
         (e = hipHostMalloc((void **)&h->h_out, 2 * sizeof(double), hipHostMallocDefault)) != hipSuccess ||
-        (e = hipEventCreate(&h->ev0)) != hipSuccess || (e = hipEventCreate(&h->ev1)) != hipSuccess) {
+        (e = hipEventCreate(&h->ev0)) != hipSuccess || (e = hipEventCreate(&h->ev1)) != hipSuccess ||
+        (e = h->clock.create()) != hipSuccess) {
         (void)hipGetLastError();
         return bail(fail(LGF_ENOMEM, "handle scratch allocation failed: %s", hipGetErrorString(e)));
     }
@@ -1284,7 +1285,6 @@ lgf_status lgf_destroy(lgf_lattice *h)
     if (h->d_fused) (void)hipFree(h->d_fused);
     if (h->d_sweep_base) (void)hipFree(h->d_sweep_base);
     if (h->d_trials) (void)hipFree(h->d_trials);
-    if (h->d_out) (void)hipFree(h->d_out);
     if (h->h_out) (void)hipHostFree(h->h_out);
     if (h->d_stage) (void)hipFree(h->d_stage);
     if (h->d_sites) (void)hipFree(h->d_sites);
@@ -1292,10 +1292,10 @@ lgf_status lgf_destroy(lgf_lattice *h)
     if (h->gacc) (void)hipFree(h->gacc);
     if (h->h_mask) (void)hipHostFree(h->h_mask);
     if (h->d_cpart) (void)hipFree(h->d_cpart);
-    if (h->d_cout) (void)hipFree(h->d_cout);
     if (h->h_cout) (void)hipHostFree(h->h_cout);
     if (h->ev0) (void)hipEventDestroy(h->ev0);
     if (h->ev1) (void)hipEventDestroy(h->ev1);
+    h->clock.destroy();
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
     return LGF_OK;
@@ -1442,7 +1442,11 @@ lgf_status lgf_measure(lgf_lattice *h, double *F, double *theta)
 {
     if (!h) return fail(LGF_EINVAL, "handle is NULL");
     LGF_TRY(use_device(h));
-    return measure_field(h, h->format, h->field, false, F, theta);
+    LGF_TRY(measure_field(h, h->format, h->field, false));
+    LGF_HIP(hipStreamSynchronize(h->stream));
+    if (F) *F = h->h_out[0];
+    if (theta) *theta = h->h_out[1];
+    return LGF_OK;
 }
 
 lgf_status lgf_synchronize(lgf_lattice *h)
@@ -1502,6 +1506,8 @@ lgf_status lgf_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_fix_resul
             ++nh;
         }
     };
+    lgf::PhaseClock &clock = h->clock;
+    clock.reset();
     // the field the sweeps run on, and a timed conversion between fields
     int cur_fmt = h->format;
     void *cur = h->field;
@@ -1512,26 +1518,27 @@ lgf_status lgf_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_fix_resul
             dst = h->work[fmt];
         }
         if (dst == cur) return LGF_OK;
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
         LGF_HIP(lgf::launch_convert(cur_fmt, cur, fmt, dst, h->geom, reunit, h->stream));
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        res->t_convert_ms += elapsed_ms(h->ev0, h->ev1);
+        LGF_HIP(clock.mark(&res->t_convert_ms, h->stream));
         cur = dst;
         cur_fmt = fmt;
         return LGF_OK;
     };
-    auto measure_timed = [&](bool reunit, double *F, double *th) -> lgf_status {
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
-        LGF_TRY(measure_field(h, cur_fmt, cur, reunit, F, th));
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        res->t_measure_ms += elapsed_ms(h->ev0, h->ev1);
+    double F = 0.0, theta = 0.0;
+    // reunit: with the reunitarization; fused: after a chunk that carried it
+    auto measure_timed = [&](bool reunit, bool fused) -> lgf_status {
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
+        if (fused) LGF_TRY(measure_fused(h, cur_fmt, cur));
+        else LGF_TRY(measure_field(h, cur_fmt, cur, reunit));
+        LGF_HIP(clock.mark(&res->t_measure_ms, h->stream));
+        LGF_HIP(clock.wait());
+        F = h->h_out[0];
+        theta = h->h_out[1];
         return LGF_OK;
     };
 
-    double F = 0.0, theta = 0.0;
-    LGF_TRY(measure_timed(false, &F, &theta));
+    LGF_TRY(measure_timed(false, false));
     record(0, F, theta);
 
     int64_t sweeps = 0, sweeps_bulk = 0;
@@ -1553,30 +1560,15 @@ lgf_status lgf_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_fix_resul
         const int n = (int)(left < p.check_every ? left : p.check_every);
         // reunitarize + measure inside the chunk's last half-sweep where possible
         const bool fuse = !p.separate_measure && can_fuse(p.p_sr, false);
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
         LGF_TRY(run_chunk(h, cur_fmt, cur, n, p.omega, p.p_sr, p.seed, ctr, p.use_graph != 0, false, fuse));
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        const double ms = elapsed_ms(h->ev0, h->ev1);
-        if (in_bulk) {
-            res->t_sweep_bulk_ms += ms;
-            sweeps_bulk += n;
-        } else {
-            res->t_sweep_finish_ms += ms;
-        }
+        LGF_HIP(clock.mark(in_bulk ? &res->t_sweep_bulk_ms : &res->t_sweep_finish_ms, h->stream));
+        if (in_bulk) sweeps_bulk += n;
         sweeps += n;
         ctr += (uint64_t)n;
 
         if (h->gacc_active) LGF_HIP(lgf::launch_site_field(bulk, h->gacc, h->geom, 1, h->stream));
-        if (fuse) {
-            LGF_HIP(hipEventRecord(h->ev0, h->stream));
-            LGF_TRY(measure_fused(h, cur_fmt, cur, &F, &theta));
-            LGF_HIP(hipEventRecord(h->ev1, h->stream));
-            LGF_HIP(hipEventSynchronize(h->ev1));
-            res->t_measure_ms += elapsed_ms(h->ev0, h->ev1);
-        } else {
-            LGF_TRY(measure_timed(true, &F, &theta));
-        }
+        LGF_TRY(measure_timed(true, fuse));
         record(sweeps, F, theta);
         if (!std::isfinite(F) || !std::isfinite(theta)) {
             status = LGF_ENUMERIC;
@@ -1591,11 +1583,9 @@ lgf_status lgf_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_fix_resul
                     LGF_TRY(ensure_work(h, finish));
                     dst = h->work[finish];
                 }
-                LGF_HIP(hipEventRecord(h->ev0, h->stream));
+                LGF_HIP(clock.mark(nullptr, h->stream));
                 LGF_TRY(gacc_apply(h, bulk, finish, dst));
-                LGF_HIP(hipEventRecord(h->ev1, h->stream));
-                LGF_HIP(hipEventSynchronize(h->ev1));
-                res->t_convert_ms += elapsed_ms(h->ev0, h->ev1);
+                LGF_HIP(clock.mark(&res->t_convert_ms, h->stream));
                 cur = dst;
                 cur_fmt = finish;
             } else {
@@ -1604,7 +1594,7 @@ lgf_status lgf_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_fix_resul
             }
             in_bulk = false;
             if (theta < p.theta_target) {
-                LGF_TRY(measure_timed(false, &F, &theta));
+                LGF_TRY(measure_timed(false, false));
                 record(sweeps, F, theta);
             } else {
                 continue;
@@ -1620,6 +1610,8 @@ lgf_status lgf_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_fix_resul
     }
     // hand the links back in the handle's own format
     LGF_TRY(move_to(h->format, false));
+    LGF_HIP(clock.wait());
+    LGF_HIP(hipStreamSynchronize(h->stream));
 
     res->sweeps = sweeps;
     res->sweeps_bulk = sweeps_bulk;
@@ -1669,8 +1661,9 @@ lgf_status lgf_fix_chunk(lgf_lattice *h, int n, double omega, double p_sr, uint6
     LGF_HIP(hipEventRecord(h->ev0, h->stream));
     LGF_TRY(run_chunk_fixed(h, fmt, h->fix_links, gf, n, omega, p_sr, seed, sweep0, use_graph != 0, true));
     LGF_HIP(hipEventRecord(h->ev1, h->stream));
-    double f = 0.0, th = 0.0;
-    LGF_TRY(measure_fixed_field(h, fmt, h->fix_links, gf, true, &f, &th));
+    LGF_TRY(measure_fixed_field(h, fmt, h->fix_links, gf, true));
+    LGF_HIP(hipStreamSynchronize(h->stream));
+    const double f = h->h_out[0], th = h->h_out[1];
     if (sweep_ms) *sweep_ms = elapsed_ms(h->ev0, h->ev1);
     if (F) *F = f;
     if (theta) *theta = th;
@@ -1835,8 +1828,7 @@ lgf_status lgf_plaquette(lgf_lattice *h, double *P)
     LGF_TRY(use_device(h));
     int n = 0;
     LGF_HIP(lgf::launch_plaquette(h->format, h->field, h->geom, h->d_partials, &n, h->stream));
-    LGF_HIP(lgf::launch_finish_measure(h->d_partials, n, (double)h->V, h->d_out, h->stream));
-    LGF_HIP(hipMemcpyAsync(h->h_out, h->d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    LGF_HIP(lgf::launch_finish_measure(h->d_partials, n, (double)h->V, h->h_out, h->stream));
     LGF_HIP(hipStreamSynchronize(h->stream));
     *P = h->h_out[0] * 12.0 / 18.0;  // the final sum divides by 12 V; the plaquette by 18 V
     return LGF_OK;
@@ -1853,6 +1845,7 @@ lgf_status lgf_sweep_coulomb(lgf_lattice *h, int parity, double omega, double p_
     LGF_TRY(use_device(h));
     LGF_TRY(ensure_coulomb(h));
     LGF_TRY(upload_mask(h, slice_active));
+    LGF_HIP(hipStreamSynchronize(h->stream));  // (the next call rewrites the mask's mirror)
     for (int par = (parity == 1 ? 1 : 0); par <= (parity == 0 ? 0 : 1); ++par)
         LGF_TRY(sweep_launch(h, h->format, h->field, par, omega, p_sr, seed, sweep_index, true));
     return LGF_OK;
@@ -1864,6 +1857,7 @@ lgf_status lgf_measure_coulomb(lgf_lattice *h, double *F_t, double *theta_t)
     LGF_TRY(use_device(h));
     LGF_TRY(ensure_coulomb(h));
     LGF_TRY(measure_coulomb_field(h, h->format, h->field, false));
+    LGF_HIP(hipStreamSynchronize(h->stream));
     for (int t = 0; t < h->dims[0]; ++t) {
         if (F_t) F_t[t] = h->h_cout[2 * t];
         if (theta_t) theta_t[t] = h->h_cout[2 * t + 1];
@@ -1914,6 +1908,8 @@ lgf_status lgf_coulomb_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_f
     std::vector<unsigned char> act(Lt, 1);
     int cur_fmt = h->format;
     void *cur = h->field;
+    lgf::PhaseClock &clock = h->clock;
+    clock.reset();
     auto move_to = [&](int fmt, bool reunit) -> lgf_status {
         void *dst = h->field;
         if (fmt != h->format) {
@@ -1921,21 +1917,18 @@ lgf_status lgf_coulomb_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_f
             dst = h->work[fmt];
         }
         if (dst == cur) return LGF_OK;
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
         LGF_HIP(lgf::launch_convert(cur_fmt, cur, fmt, dst, h->geom, reunit, h->stream));
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        res->t_convert_ms += elapsed_ms(h->ev0, h->ev1);
+        LGF_HIP(clock.mark(&res->t_convert_ms, h->stream));
         cur = dst;
         cur_fmt = fmt;
         return LGF_OK;
     };
     auto measure = [&](bool reunit, bool only_active) -> lgf_status {
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
         LGF_TRY(measure_coulomb_field(h, cur_fmt, cur, reunit));
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        res->t_measure_ms += elapsed_ms(h->ev0, h->ev1);
+        LGF_HIP(clock.mark(&res->t_measure_ms, h->stream));
+        LGF_HIP(clock.wait());
         for (int t = 0; t < Lt; ++t)
             if (!only_active || act[t]) {
                 F[t] = h->h_cout[2 * t];
@@ -1970,20 +1963,14 @@ lgf_status lgf_coulomb_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_f
         if (acc && in_bulk) LGF_TRY(gacc_begin(h, bulk));
     }
     while (status != LGF_ENUMERIC && n_live() > 0 && sweeps < p.max_sweeps) {
+        // (the last measurement's wait covers the last chunk's copy)
         LGF_TRY(upload_mask(h, act.data()));
         const int64_t left = p.max_sweeps - sweeps;
         const int n = (int)(left < p.check_every ? left : p.check_every);
-        LGF_HIP(hipEventRecord(h->ev0, h->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, h->stream));
         LGF_TRY(run_chunk(h, cur_fmt, cur, n, p.omega, p.p_sr, p.seed, ctr, p.use_graph != 0, true));
-        LGF_HIP(hipEventRecord(h->ev1, h->stream));
-        LGF_HIP(hipEventSynchronize(h->ev1));
-        const double ms = elapsed_ms(h->ev0, h->ev1);
-        if (in_bulk) {
-            res->t_sweep_bulk_ms += ms;
-            sweeps_bulk += n;
-        } else {
-            res->t_sweep_finish_ms += ms;
-        }
+        LGF_HIP(clock.mark(in_bulk ? &res->t_sweep_bulk_ms : &res->t_sweep_finish_ms, h->stream));
+        if (in_bulk) sweeps_bulk += n;
         sweeps += n;
         ctr += (uint64_t)n;
         if (h->gacc_active) LGF_HIP(lgf::launch_site_field(bulk, h->gacc, h->geom, 1, h->stream));
@@ -2005,11 +1992,9 @@ lgf_status lgf_coulomb_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_f
                         LGF_TRY(ensure_work(h, finish));
                         dst = h->work[finish];
                     }
-                    LGF_HIP(hipEventRecord(h->ev0, h->stream));
+                    LGF_HIP(clock.mark(nullptr, h->stream));
                     LGF_TRY(gacc_apply(h, bulk, finish, dst));
-                    LGF_HIP(hipEventRecord(h->ev1, h->stream));
-                    LGF_HIP(hipEventSynchronize(h->ev1));
-                    res->t_convert_ms += elapsed_ms(h->ev0, h->ev1);
+                    LGF_HIP(clock.mark(&res->t_convert_ms, h->stream));
                     cur = dst;
                     cur_fmt = finish;
                 } else {
@@ -2030,6 +2015,8 @@ lgf_status lgf_coulomb_gauge_fix(lgf_lattice *h, const lgf_fix_params *pp, lgf_f
         cur_fmt = h->format;
     }
     LGF_TRY(move_to(h->format, false));
+    LGF_HIP(clock.wait());
+    LGF_HIP(hipStreamSynchronize(h->stream));
     double tmax = 0.0, fsum = 0.0;
     for (int t = 0; t < Lt; ++t) {
         tmax = th[t] > tmax ? th[t] : tmax;

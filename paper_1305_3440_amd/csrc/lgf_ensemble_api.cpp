@@ -70,12 +70,11 @@ struct lgf_ensemble {
     uint64_t *d_sweep_base = nullptr;
     lgf::EnsSpan *d_spans = nullptr;
     double *d_partials = nullptr;
-    double *d_out = nullptr;
     lgf::EnsCfg *h_cfgs = nullptr;
     lgf::EnsTile *h_tiles = nullptr;
     uint32_t *h_n_tiles = nullptr;
     lgf::EnsSpan *h_spans = nullptr;
-    double *h_out = nullptr;
+    double *h_out = nullptr;              // pinned: the final sums write every F, theta there
     uint32_t max_tiles = 0;
     // tuning: sites per tile (= lanes per workgroup), persistent workgroups
     // per CU as a multiple of the occupancy limit, non-temporal link access
@@ -88,6 +87,7 @@ struct lgf_ensemble {
     std::vector<size_t> scratch_off;
     std::vector<EnsGraph> graphs;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    lgf::PhaseClock clock;
 };
 
 namespace {
@@ -260,8 +260,8 @@ lgf::EnsRelax relax_args(double omega, double p_sr, uint64_t seed)
 lgf_status run_chunk(lgf_ensemble *e, int fa, int fb, int n, double omega, double p_sr, uint64_t seed,
                      uint64_t sweep0, bool use_graph, bool fused = false)
 {
-    LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep0, e->stream));
     const bool sr = p_sr > 0.0;
+    if (sr) LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep0, e->stream));
     const lgf::EnsRelax r = relax_args(omega, p_sr, seed);
     const lgf::EnsLaunch L = launch_desc(e, fa, fb, sr);
     const bool nt = e->nontemporal != 0;
@@ -306,15 +306,14 @@ lgf_status run_chunk(lgf_ensemble *e, int fa, int fb, int n, double omega, doubl
 
 // F, theta of the listed configurations (work list already uploaded); with
 // reunit the fused FP64 reunitarization of the single-lattice measurement.
+// Enqueued only: the results are in e->h_out once the stream has been waited for.
 lgf_status measure_listed(lgf_ensemble *e, int fa, int fb, uint32_t nt, const std::vector<int> &listed, bool reunit)
 {
     if (nt == 0) return LGF_OK;
     const lgf::EnsLaunch L = launch_desc(e, fa, fb, false);
     LGF_HIP(lgf::launch_ensemble_measure(fa, fb, L, nt, 0, reunit, reunit, e->d_partials, e->stream));
     LGF_HIP(lgf::launch_ensemble_measure(fa, fb, L, nt, 1, reunit, false, e->d_partials + 2 * (size_t)nt, e->stream));
-    LGF_HIP(lgf::launch_ensemble_finish(e->d_partials, nt, e->d_spans, (uint32_t)listed.size(), e->d_out, e->stream));
-    LGF_HIP(hipMemcpyAsync(e->h_out, e->d_out, sizeof(double) * 2 * e->n, hipMemcpyDeviceToHost, e->stream));
-    LGF_HIP(hipStreamSynchronize(e->stream));
+    LGF_HIP(lgf::launch_ensemble_finish(e->d_partials, nt, e->d_spans, (uint32_t)listed.size(), e->h_out, e->stream));
     return LGF_OK;
 }
 
@@ -326,9 +325,7 @@ lgf_status measure_listed_fused(lgf_ensemble *e, int fa, int fb, uint32_t nt, co
     if (nt == 0) return LGF_OK;
     const lgf::EnsLaunch L = launch_desc(e, fa, fb, false);
     LGF_HIP(lgf::launch_ensemble_measure(fa, fb, L, nt, 0, false, false, e->d_partials, e->stream));
-    LGF_HIP(lgf::launch_ensemble_finish(e->d_partials, nt, e->d_spans, (uint32_t)listed.size(), e->d_out, e->stream));
-    LGF_HIP(hipMemcpyAsync(e->h_out, e->d_out, sizeof(double) * 2 * e->n, hipMemcpyDeviceToHost, e->stream));
-    LGF_HIP(hipStreamSynchronize(e->stream));
+    LGF_HIP(lgf::launch_ensemble_finish(e->d_partials, nt, e->d_spans, (uint32_t)listed.size(), e->h_out, e->stream));
     return LGF_OK;
 }
 
@@ -339,8 +336,8 @@ lgf_status measure_listed_fused(lgf_ensemble *e, int fa, int fb, uint32_t nt, co
 lgf_status run_chunk_fixed(lgf_ensemble *e, int fa, int fb, int n, double omega, double p_sr, uint64_t seed,
                            uint64_t sweep0, bool use_graph, bool fused)
 {
-    LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep0, e->stream));
     const bool sr = p_sr > 0.0;
+    if (sr) LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep0, e->stream));
     const lgf::EnsRelax r = relax_args(omega, p_sr, seed);
     const bool rec = fixed_on_records(e, fa, fb);
     lgf::EnsLaunch L = launch_desc(e, fa, fb, sr);
@@ -401,9 +398,7 @@ lgf_status measure_listed_fixed(lgf_ensemble *e, int fa, int fb, uint32_t nt, co
     LGF_HIP(lgf::launch_ensemble_fixed_measure(fa, fb, L, nt, 0, e->d_partials, e->stream, rec));
     if (!fused)
         LGF_HIP(lgf::launch_ensemble_fixed_measure(fa, fb, L, nt, 1, e->d_partials + 2 * (size_t)nt, e->stream, rec));
-    LGF_HIP(lgf::launch_ensemble_finish(e->d_partials, nt, e->d_spans, (uint32_t)listed.size(), e->d_out, e->stream));
-    LGF_HIP(hipMemcpyAsync(e->h_out, e->d_out, sizeof(double) * 2 * e->n, hipMemcpyDeviceToHost, e->stream));
-    LGF_HIP(hipStreamSynchronize(e->stream));
+    LGF_HIP(lgf::launch_ensemble_finish(e->d_partials, nt, e->d_spans, (uint32_t)listed.size(), e->h_out, e->stream));
     return LGF_OK;
 }
 
@@ -491,12 +486,13 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
     };
     std::memset(results, 0, sizeof(lgf_fix_result) * e->n);
     double t_bulk = 0.0, t_finish = 0.0, t_meas = 0.0, t_conv = 0.0;
+    lgf::PhaseClock &clock = e->clock;
+    clock.reset();
+    // work whose time goes to acc_ms, enqueued only
     auto timed = [&](double &acc_ms, auto &&body) -> lgf_status {
-        LGF_HIP(hipEventRecord(e->ev0, e->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, e->stream));
         LGF_TRY(body());
-        LGF_HIP(hipEventRecord(e->ev1, e->stream));
-        LGF_HIP(hipEventSynchronize(e->ev1));
-        acc_ms += lgf::elapsed_ms(e->ev0, e->ev1);
+        LGF_HIP(clock.mark(&acc_ms, e->stream));
         return LGF_OK;
     };
     auto links_to = [&](int i, int f) { return fixed_links_to(e, i, f); };
@@ -506,6 +502,7 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
     uint32_t nt = build_work(e, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     LGF_TRY(timed(t_meas, [&]() { return measure_listed(e, e->format, e->format, nt, listed, false); }));
+    LGF_HIP(clock.wait());
     for (int i = 0; i < e->n; ++i) {
         lgf_fix_result &r = results[i];
         r.F = e->h_out[2 * i];
@@ -542,9 +539,13 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
     };
     const bool fuse = !p.separate_measure;
     const int sites = e->tile / lgf::kEnsFixedLanes;
+    bool changed = true;  // the work list, since its last upload
     while (live() && sweeps < p.max_sweeps) {
-        nt = build_work(e, phase, fmt, false, listed, sites, true);
-        LGF_TRY(upload_work(e, nt, listed.size()));
+        if (changed) {
+            nt = build_work(e, phase, fmt, false, listed, sites, true);
+            LGF_TRY(upload_work(e, nt, listed.size()));
+            changed = false;
+        }
         bool any_bulk = false, any_finish = false;
         for (int i : listed) (phase[i] == kBulk ? any_bulk : any_finish) = true;
         const int fa = any_bulk ? bulk : finish, fb = any_finish ? finish : bulk;
@@ -556,37 +557,41 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
         sweeps += n;
         ctr += (uint64_t)n;
         LGF_TRY(timed(t_meas, [&]() { return measure_listed_fixed(e, fa, fb, nt, listed, fuse); }));
-        LGF_TRY(timed(t_conv, [&]() -> lgf_status {
-            for (int i : listed) {
-                lgf_fix_result &r = results[i];
-                r.F = e->h_out[2 * i];
-                r.theta = e->h_out[2 * i + 1];
-                r.sweeps = sweeps;
-                if (phase[i] == kBulk) r.sweeps_bulk += n;
-                r.n_history += 1;
-                if (!std::isfinite(r.F) || !std::isfinite(r.theta)) {
-                    r.status = LGF_ENUMERIC;
-                    phase[i] = kDone;
-                    continue;
-                }
-                if (phase[i] == kBulk && (r.theta < p.theta_switch || r.theta < p.theta_target)) {
-                    // the finish starts from the bulk's g, reunitarized in FP64
+        LGF_HIP(clock.wait());
+        for (int i : listed) {
+            lgf_fix_result &r = results[i];
+            r.F = e->h_out[2 * i];
+            r.theta = e->h_out[2 * i + 1];
+            r.sweeps = sweeps;
+            if (phase[i] == kBulk) r.sweeps_bulk += n;
+            r.n_history += 1;
+            if (!std::isfinite(r.F) || !std::isfinite(r.theta)) {
+                r.status = LGF_ENUMERIC;
+                phase[i] = kDone;
+                changed = true;
+                continue;
+            }
+            if (phase[i] == kBulk && (r.theta < p.theta_switch || r.theta < p.theta_target)) {
+                // the finish starts from the bulk's g, reunitarized in FP64
+                LGF_TRY(timed(t_conv, [&]() -> lgf_status {
                     LGF_TRY(links_to(i, finish));
                     LGF_TRY(ensure_gfix(e, finish));
                     LGF_HIP(lgf::launch_site_convert(gf_format(bulk), gf_of(e, bulk, i), gf_format(finish),
                                                      gf_of(e, finish, i), e->geom[i], e->stream));
-                    fmt[i] = finish;
-                    phase[i] = kFinish;
-                    continue;  // the next measurement is taken in the finish format
-                }
-                if (phase[i] == kFinish && r.theta < p.theta_target) {
-                    r.status = LGF_OK;
-                    r.t_total_ms = now_ms();
-                    phase[i] = kDone;
-                }
+                    return LGF_OK;
+                }));
+                fmt[i] = finish;
+                phase[i] = kFinish;
+                changed = true;
+                continue;  // the next measurement is taken in the finish format
             }
-            return LGF_OK;
-        }));
+            if (phase[i] == kFinish && r.theta < p.theta_target) {
+                r.status = LGF_OK;
+                r.t_total_ms = now_ms();
+                phase[i] = kDone;
+                changed = true;
+            }
+        }
     }
     // the links in the final gauge, from the untouched home links (in place)
     LGF_TRY(timed(t_conv, [&]() -> lgf_status {
@@ -611,6 +616,7 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
             nt = build_work(e, ph, fh, false, listed);
             LGF_TRY(upload_work(e, nt, listed.size()));
             LGF_TRY(timed(t_meas, [&]() { return measure_listed(e, e->format, e->format, nt, listed, false); }));
+            LGF_HIP(clock.wait());
             for (int i : listed) {
                 lgf_fix_result &r = results[i];
                 r.F = e->h_out[2 * i];
@@ -620,6 +626,7 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
             }
         }
     }
+    LGF_HIP(clock.wait());
     bool any_bad = false;
     for (int i = 0; i < e->n; ++i) {
         lgf_fix_result &r = results[i];
@@ -695,13 +702,13 @@ lgf_status lgf_ensemble_create(int n, const int *dims, int format, void *stream,
         (err = hipMalloc(&e->d_sweep_base, sizeof(uint64_t))) != hipSuccess ||
         (err = hipMalloc(&e->d_spans, sizeof(lgf::EnsSpan) * n)) != hipSuccess ||
         (err = hipMalloc(&e->d_partials, sizeof(double) * 4 * T)) != hipSuccess ||
-        (err = hipMalloc(&e->d_out, sizeof(double) * 2 * n)) != hipSuccess ||
         (err = hipHostMalloc((void **)&e->h_cfgs, sizeof(lgf::EnsCfg) * n, hipHostMallocDefault)) != hipSuccess ||
         (err = hipHostMalloc((void **)&e->h_tiles, sizeof(lgf::EnsTile) * T, hipHostMallocDefault)) != hipSuccess ||
         (err = hipHostMalloc((void **)&e->h_n_tiles, sizeof(uint32_t), hipHostMallocDefault)) != hipSuccess ||
         (err = hipHostMalloc((void **)&e->h_spans, sizeof(lgf::EnsSpan) * n, hipHostMallocDefault)) != hipSuccess ||
         (err = hipHostMalloc((void **)&e->h_out, sizeof(double) * 2 * n, hipHostMallocDefault)) != hipSuccess ||
-        (err = hipEventCreate(&e->ev0)) != hipSuccess || (err = hipEventCreate(&e->ev1)) != hipSuccess) {
+        (err = hipEventCreate(&e->ev0)) != hipSuccess || (err = hipEventCreate(&e->ev1)) != hipSuccess ||
+        (err = e->clock.create()) != hipSuccess) {
         (void)hipGetLastError();
         return bail(fail(LGF_ENOMEM, "ensemble scratch allocation failed: %s", hipGetErrorString(err)));
     }
@@ -724,7 +731,7 @@ lgf_status lgf_ensemble_destroy(lgf_ensemble *e)
     for (int f = 0; f < 5; ++f)
         if (e->rec[f]) (void)hipFree(e->rec[f]);
     if (e->scratch) (void)hipFree(e->scratch);
-    void *dev[] = {e->d_cfgs, e->d_tiles, e->d_n_tiles, e->d_sweep_base, e->d_spans, e->d_partials, e->d_out};
+    void *dev[] = {e->d_cfgs, e->d_tiles, e->d_n_tiles, e->d_sweep_base, e->d_spans, e->d_partials};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     void *host[] = {e->h_cfgs, e->h_tiles, e->h_n_tiles, e->h_spans, e->h_out};
@@ -732,6 +739,7 @@ lgf_status lgf_ensemble_destroy(lgf_ensemble *e)
         if (p) (void)hipHostFree(p);
     if (e->ev0) (void)hipEventDestroy(e->ev0);
     if (e->ev1) (void)hipEventDestroy(e->ev1);
+    e->clock.destroy();
     if (e->own_stream && e->stream) (void)hipStreamDestroy(e->stream);
     delete e;
     return LGF_OK;
@@ -805,8 +813,8 @@ lgf_status lgf_ensemble_sweep(lgf_ensemble *e, int parity, double omega, double 
     std::vector<int> phase(e->n, kFinish), fmt(e->n, e->format), listed;
     const uint32_t nt = build_work(e, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
-    LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep_index, e->stream));
     const bool sr = p_sr > 0.0;
+    if (sr) LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep_index, e->stream));
     const lgf::EnsLaunch L = launch_desc(e, e->format, e->format, sr);
     const lgf::EnsRelax r = relax_args(omega, p_sr, seed);
     for (int par = (parity == 1 ? 1 : 0); par <= (parity == 0 ? 0 : 1); ++par)
@@ -824,6 +832,7 @@ lgf_status lgf_ensemble_measure(lgf_ensemble *e, double *F, double *theta)
     const uint32_t nt = build_work(e, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     LGF_TRY(measure_listed(e, e->format, e->format, nt, listed, false));
+    LGF_HIP(hipStreamSynchronize(e->stream));
     for (int i = 0; i < e->n; ++i) {
         if (F) F[i] = e->h_out[2 * i];
         if (theta) theta[i] = e->h_out[2 * i + 1];
@@ -867,10 +876,13 @@ lgf_status lgf_ensemble_gauge_fix(lgf_ensemble *e, const lgf_fix_params *pp, lgf
     double t_bulk = 0.0, t_finish = 0.0, t_meas = 0.0, t_conv = 0.0;
 
     std::vector<int> phase(e->n, mixed ? kBulk : kFinish), fmt(e->n, e->format), listed;
+    lgf::PhaseClock &clock = e->clock;
+    clock.reset();
     // measurement 0 on the home field
     uint32_t nt = build_work(e, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     LGF_TRY(measure_listed(e, e->format, e->format, nt, listed, false));
+    LGF_HIP(hipStreamSynchronize(e->stream));
     for (int i = 0; i < e->n; ++i) {
         lgf_fix_result &r = results[i];
         r.F = e->h_out[2 * i];
@@ -886,16 +898,14 @@ lgf_status lgf_ensemble_gauge_fix(lgf_ensemble *e, const lgf_fix_params *pp, lgf
         }
     }
     // move every live configuration to its first sweeping format
-    LGF_HIP(hipEventRecord(e->ev0, e->stream));
+    LGF_HIP(clock.mark(nullptr, e->stream));
     for (int i = 0; i < e->n; ++i) {
         if (phase[i] == kDone) continue;
         const int f = (phase[i] == kBulk) ? bulk : finish;
         LGF_TRY(convert_one(e, i, e->format, f, is_fp64(f) && !is_fp64(e->format)));
         fmt[i] = f;
     }
-    LGF_HIP(hipEventRecord(e->ev1, e->stream));
-    LGF_HIP(hipEventSynchronize(e->ev1));
-    t_conv += lgf::elapsed_ms(e->ev0, e->ev1);
+    LGF_HIP(clock.mark(&t_conv, e->stream));
 
     int64_t sweeps = 0;
     uint64_t ctr = p.sweep_offset;
@@ -904,9 +914,13 @@ lgf_status lgf_ensemble_gauge_fix(lgf_ensemble *e, const lgf_fix_params *pp, lgf
             if (phase[i] != kDone) return true;
         return false;
     };
+    bool changed = true;  // the work list, since its last upload
     while (live() && sweeps < p.max_sweeps) {
-        nt = build_work(e, phase, fmt, false, listed);
-        LGF_TRY(upload_work(e, nt, listed.size()));
+        if (changed) {
+            nt = build_work(e, phase, fmt, false, listed);
+            LGF_TRY(upload_work(e, nt, listed.size()));
+            changed = false;
+        }
         bool any_bulk = false, any_finish = false;
         for (int i : listed) (phase[i] == kBulk ? any_bulk : any_finish) = true;
         const int fa = any_bulk ? bulk : finish, fb = any_finish ? finish : bulk;
@@ -914,23 +928,17 @@ lgf_status lgf_ensemble_gauge_fix(lgf_ensemble *e, const lgf_fix_params *pp, lgf
         const int n = (int)(left < p.check_every ? left : p.check_every);
         // reunitarize + measure inside the chunk's last half-sweep where possible
         const bool fuse = !p.separate_measure && p.p_sr == 0.0 && e->nontemporal != 0;
-        LGF_HIP(hipEventRecord(e->ev0, e->stream));
+        if (clock.n == 0) LGF_HIP(clock.mark(nullptr, e->stream));
         LGF_TRY(run_chunk(e, fa, fb, n, p.omega, p.p_sr, p.seed, ctr, p.use_graph != 0, fuse));
-        LGF_HIP(hipEventRecord(e->ev1, e->stream));
-        LGF_HIP(hipEventSynchronize(e->ev1));
-        const double ms = lgf::elapsed_ms(e->ev0, e->ev1);
-        (any_bulk ? t_bulk : t_finish) += ms;
+        LGF_HIP(clock.mark(any_bulk ? &t_bulk : &t_finish, e->stream));
         sweeps += n;
         ctr += (uint64_t)n;
-        LGF_HIP(hipEventRecord(e->ev0, e->stream));
         if (fuse)
             LGF_TRY(measure_listed_fused(e, fa, fb, nt, listed));
         else
             LGF_TRY(measure_listed(e, fa, fb, nt, listed, true));
-        LGF_HIP(hipEventRecord(e->ev1, e->stream));
-        LGF_HIP(hipEventSynchronize(e->ev1));
-        t_meas += lgf::elapsed_ms(e->ev0, e->ev1);
-        LGF_HIP(hipEventRecord(e->ev0, e->stream));
+        LGF_HIP(clock.mark(&t_meas, e->stream));
+        LGF_HIP(clock.wait());
         for (int i : listed) {
             lgf_fix_result &r = results[i];
             r.F = e->h_out[2 * i];
@@ -941,24 +949,27 @@ lgf_status lgf_ensemble_gauge_fix(lgf_ensemble *e, const lgf_fix_params *pp, lgf
             if (!std::isfinite(r.F) || !std::isfinite(r.theta)) {
                 r.status = LGF_ENUMERIC;
                 phase[i] = kDone;
+                changed = true;
                 continue;
             }
             if (phase[i] == kBulk && (r.theta < p.theta_switch || r.theta < p.theta_target)) {
+                if (clock.n == 0) LGF_HIP(clock.mark(nullptr, e->stream));
                 LGF_TRY(convert_one(e, i, bulk, finish, true));
+                LGF_HIP(clock.mark(&t_conv, e->stream));
                 fmt[i] = finish;
                 phase[i] = kFinish;
+                changed = true;
                 continue;  // the next measurement is taken in the finish format
             }
             if (phase[i] == kFinish && r.theta < p.theta_target) {
                 r.status = LGF_OK;
                 r.t_total_ms = now_ms();
                 phase[i] = kDone;
+                changed = true;
             }
         }
-        LGF_HIP(hipEventRecord(e->ev1, e->stream));
-        LGF_HIP(hipEventSynchronize(e->ev1));
-        t_conv += lgf::elapsed_ms(e->ev0, e->ev1);
     }
+    LGF_HIP(clock.wait());
     // links back to the home format
     bool any_bad = false;
     for (int i = 0; i < e->n; ++i) {
