@@ -340,9 +340,12 @@ void prepare_schedule(lgf_lattice *h, int format)
 lgf_status measure_field(lgf_lattice *h, int format, void *field, bool reunit)
 {
     int n0 = 0, n1 = 0;
-    LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, reunit, reunit, h->d_partials, &n0, h->stream));
-    LGF_HIP(lgf::launch_measure(format, field, h->geom, 1, reunit, false, h->d_partials + 2 * n0, &n1,
-                                h->stream));
+    if (reunit) {
+        LGF_HIP(lgf::launch_measure_reunit(format, field, h->geom, 0, true, h->d_partials, &n0, h->stream));
+        LGF_HIP(lgf::launch_measure_reunit(format, field, h->geom, 1, false, h->d_partials + 2 * n0, &n1, h->stream));
+    } else {
+        LGF_HIP(lgf::launch_measure(format, field, h->geom, 2, h->d_partials, &n0, h->stream));
+    }
     LGF_HIP(lgf::launch_finish_measure(h->d_partials, n0 + n1, (double)h->V, h->h_out, h->stream));
     return LGF_OK;
 }
@@ -452,9 +455,13 @@ lgf_status upload_mask(lgf_lattice *h, const unsigned char *flags)
 // every link first
 lgf_status measure_coulomb_field(lgf_lattice *h, int format, void *field, bool reunit)
 {
-    const size_t half = (size_t)2 * h->dims[0] * lgf::coulomb_blocks_per_slice(h->geom);
-    LGF_HIP(lgf::launch_measure_coulomb(format, field, h->geom, 0, reunit, reunit, h->d_cpart, h->stream));
-    LGF_HIP(lgf::launch_measure_coulomb(format, field, h->geom, 1, reunit, false, h->d_cpart + half, h->stream));
+    if (reunit) {
+        const size_t half = (size_t)2 * h->dims[0] * lgf::coulomb_blocks_per_slice(h->geom);
+        LGF_HIP(lgf::launch_measure_coulomb_reunit(format, field, h->geom, 0, true, h->d_cpart, h->stream));
+        LGF_HIP(lgf::launch_measure_coulomb_reunit(format, field, h->geom, 1, false, h->d_cpart + half, h->stream));
+    } else {
+        LGF_HIP(lgf::launch_measure_coulomb(format, field, h->geom, h->d_cpart, h->stream));
+    }
     LGF_HIP(lgf::launch_finish_coulomb(h->d_cpart, h->geom, lgf::coulomb_blocks_per_slice(h->geom), h->h_cout,
                                        h->stream));
     return LGF_OK;
@@ -500,8 +507,7 @@ lgf_status measure_fused(lgf_lattice *h, int format, void *field)
 {
     const int ng = (int)lgf::sweep_groups(h->geom, launch_tuning(h, format));
     int n0 = 0;
-    LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, false, false, h->d_fused + 2 * (size_t)ng, &n0,
-                                h->stream));
+    LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, h->d_fused + 2 * (size_t)ng, &n0, h->stream));
     LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->h_out, h->stream));
     return LGF_OK;
 }
@@ -853,10 +859,8 @@ lgf_status measure_fixed_field(lgf_lattice *h, int format, const void *links, co
 lgf_status measure_coulomb_fixed_field(lgf_lattice *h, int format, const void *links, const void *gf)
 {
     const int bps = lgf::coulomb_fixed_blocks(h->geom);
-    const size_t half = (size_t)2 * h->dims[0] * bps;
-    const bool rec = fixed_records(h, format);
-    LGF_HIP(lgf::launch_measure_coulomb_fixed(format, links, gf, h->geom, 0, h->d_cpart, h->stream, rec));
-    LGF_HIP(lgf::launch_measure_coulomb_fixed(format, links, gf, h->geom, 1, h->d_cpart + half, h->stream, rec));
+    LGF_HIP(lgf::launch_measure_coulomb_fixed(format, links, gf, h->geom, h->d_cpart, h->stream,
+                                              fixed_records(h, format)));
     LGF_HIP(lgf::launch_finish_coulomb(h->d_cpart, h->geom, bps, h->h_cout, h->stream));
     return LGF_OK;
 }
@@ -1815,10 +1819,9 @@ lgf_status lgf_measure_noalloc(lgf_lattice *h, double *d_out)
     void *scr = nullptr;
     LGF_TRY(scratch_on(h->device, &scr));
     double *part = static_cast<double *>(scr);
-    int n0 = 0, n1 = 0;
-    LGF_HIP(lgf::launch_measure(h->format, h->field, h->geom, 0, false, false, part, &n0, h->stream));
-    LGF_HIP(lgf::launch_measure(h->format, h->field, h->geom, 1, false, false, part + 2 * n0, &n1, h->stream));
-    LGF_HIP(lgf::launch_finish_measure(part, n0 + n1, (double)h->V, d_out, h->stream));
+    int n = 0;
+    LGF_HIP(lgf::launch_measure(h->format, h->field, h->geom, 2, part, &n, h->stream));
+    LGF_HIP(lgf::launch_finish_measure(part, n, (double)h->V, d_out, h->stream));
     return LGF_OK;
 }
 

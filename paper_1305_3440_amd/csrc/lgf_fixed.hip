@@ -300,9 +300,10 @@ hipError_t launch_measure_fixed(int format, const void *links, const void *gf, c
     return hipGetLastError();
 }
 
-// Coulomb gauge, read only: per timeslice t and parity pass, partial (F_C,
-// theta_C) pairs at partials[2 (t bps + b)] for the bps = coulomb_fixed_blocks
-// workgroups of a slice (the layout finish_coulomb_kernel sums).
+// Coulomb gauge, read only, both parities: per parity and timeslice t, partial
+// (F_C, theta_C) pairs at partials[2 ((parity Lt + t) bps + b)] for the bps =
+// coulomb_fixed_blocks workgroups of a slice (the layout finish_coulomb_kernel
+// sums).  The items go as in measure_coulomb_kernel; what they share here is g.
 int coulomb_fixed_blocks(const Geom &g)
 {
     return (int)(((uint64_t)g.hs[0] * kMeasureFixedLanes + kMeasureBlock - 1) / kMeasureBlock);
@@ -311,10 +312,14 @@ int coulomb_fixed_blocks(const Geom &g)
 template <int F, bool REC = false>
 __global__ void __launch_bounds__(kMeasureBlock) measure_coulomb_fixed_kernel(const void *__restrict__ links,
                                                                               const void *__restrict__ gf, Geom g,
-                                                                              int parity, double *partials)
+                                                                              XcdRuns runs, uint32_t bps, FastDiv dbps,
+                                                                              double *partials)
 {
-    const uint32_t t = blockIdx.y;
-    const uint32_t tid = blockIdx.x * kMeasureBlock + threadIdx.x;
+    const uint32_t item = xcd_item(blockIdx.x, runs);
+    const uint32_t j = item >> 1, t = fast_div(j, dbps);
+    if (t >= g.L[0]) return;  // the whole workgroup: no partials slot
+    const int parity = (int)(item & 1u);
+    const uint32_t tid = (j - t * bps) * kMeasureBlock + threadIdx.x;
     const uint32_t i = tid / kMeasureFixedLanes;
     const bool active = i < g.hs[0];
     const uint32_t h = t * g.hs[0] + (active ? i : g.hs[0] - 1);
@@ -322,28 +327,32 @@ __global__ void __launch_bounds__(kMeasureBlock) measure_coulomb_fixed_kernel(co
     // (a slice need not start at a record tile, so a wave may straddle two)
     measure_site_fixed<F, kMeasureFixedLanes, 1, REC, false>(links, gf, g, parity, h, (int)(tid % kMeasureFixedLanes),
                                                       active, f, th);
-    block_sum2<kMeasureBlock>(f, th, partials + 2 * ((size_t)t * gridDim.x + blockIdx.x));
+    block_sum2<kMeasureBlock>(f, th, partials + 2 * ((size_t)(parity ? g.L[0] * bps : 0u) + j));
 }
 
-hipError_t launch_measure_coulomb_fixed(int format, const void *links, const void *gf, const Geom &g, int parity,
+hipError_t launch_measure_coulomb_fixed(int format, const void *links, const void *gf, const Geom &g,
                                         double *partials, hipStream_t s, bool records)
 {
-    const dim3 grid(coulomb_fixed_blocks(g), g.L[0]), block(kMeasureBlock);
+    const uint32_t bps = (uint32_t)coulomb_fixed_blocks(g);
+    uint32_t ng = 0;
+    const XcdRuns runs = xcd_runs(2 * bps * g.L[0], g, 0, &ng);
+    const FastDiv db = make_fast_div(bps);
+    const dim3 grid(ng), block(kMeasureBlock);
     if (records) {
         switch (format) {
-        case kF32_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF32_12, true>), grid, block, 0, s, links, gf, g, parity, partials); break;
-        case kF64_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12, true>), grid, block, 0, s, links, gf, g, parity, partials); break;
-        case kF64_12S: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12S, true>), grid, block, 0, s, links, gf, g, parity, partials); break;
+        case kF32_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF32_12, true>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
+        case kF64_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12, true>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
+        case kF64_12S: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12S, true>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
     }
     switch (format) {
-    case kF64_18: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_18>), grid, block, 0, s, links, gf, g, parity, partials); break;
-    case kF32_18: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF32_18>), grid, block, 0, s, links, gf, g, parity, partials); break;
-    case kF32_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF32_12>), grid, block, 0, s, links, gf, g, parity, partials); break;
-    case kF64_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12>), grid, block, 0, s, links, gf, g, parity, partials); break;
-    case kF64_12S: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12S>), grid, block, 0, s, links, gf, g, parity, partials); break;
+    case kF64_18: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_18>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
+    case kF32_18: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF32_18>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
+    case kF32_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF32_12>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
+    case kF64_12: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
+    case kF64_12S: hipLaunchKernelGGL((measure_coulomb_fixed_kernel<kF64_12S>), grid, block, 0, s, links, gf, g, runs, bps, db, partials); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -61,14 +61,17 @@ uint32_t sweep_groups(const Geom &g, const SweepTuning &t);
 hipError_t launch_sweep(int format, void *field, const Geom &g, const SweepArgs &a,
                         const SweepTuning &t, hipStream_t s);
 
-// Reunitarize (optional) + per-block partial sums of (sum Re tr U, sum |Delta|^2)
-// over the sites of one parity.  reunit_fwd: reunitarize the 4 forward links
-// of every site and store them; reunit_bwd: reunitarize the backward links in
-// registers only (for the first parity pass, whose backward links are the
-// other parity's not yet reunitarized forward links).
-// Returns the number of partial pairs written in *n_partials.
-hipError_t launch_measure(int format, void *field, const Geom &g, int parity, bool reunit_fwd,
-                          bool reunit_bwd, double *partials, int *n_partials, hipStream_t s);
+// Per-block partial sums of (sum Re tr U, sum |Delta|^2) over the sites of
+// parity 0, 1 or both (which = 2: parity 0's blocks first), read only; the number
+// of partial pairs in *n_partials.
+hipError_t launch_measure(int format, const void *field, const Geom &g, int which, double *partials, int *n_partials,
+                          hipStream_t s);
+// The same over one parity with the 4 forward links of every site reunitarized
+// and stored first; reunit_bwd: the backward links reunitarized in registers
+// only (for the first parity pass, whose backward links are the other parity's
+// not yet reunitarized forward links).
+hipError_t launch_measure_reunit(int format, void *field, const Geom &g, int parity, bool reunit_bwd,
+                                 double *partials, int *n_partials, hipStream_t s);
 int measure_blocks(const Geom &g);
 
 // out[0] = F, out[1] = theta from n partial pairs
@@ -94,12 +97,13 @@ hipError_t launch_field_to_canon(int format, const void *field, const int64_t *s
 // tuning: 2 lanes per site or (any other) 1, block, xcd_remap, nontemporal.
 hipError_t launch_sweep_coulomb(int format, void *field, const Geom &g, const SweepArgs &a,
                                 const uint8_t *slice_active, const SweepTuning &t, hipStream_t s);
-// partials must hold 4 * Lt * coulomb_blocks_per_slice(g) doubles; pass 0
-// writes the first half (parity 0 at partials, parity 1 at the second half is
-// the caller's offset 2 * Lt * blocks)
+// partials must hold 4 * Lt * coulomb_blocks_per_slice(g) doubles, parity 0's
+// half first; the reunitarizing pass over one parity (as launch_measure_reunit)
+// writes the half it is given
 int coulomb_blocks_per_slice(const Geom &g);
-hipError_t launch_measure_coulomb(int format, void *field, const Geom &g, int parity, bool reunit_fwd,
-                                  bool reunit_bwd, double *partials, hipStream_t s);
+hipError_t launch_measure_coulomb(int format, const void *field, const Geom &g, double *partials, hipStream_t s);
+hipError_t launch_measure_coulomb_reunit(int format, void *field, const Geom &g, int parity, bool reunit_bwd,
+                                         double *partials, hipStream_t s);
 // bps: partial pairs per timeslice and pass (coulomb_blocks_per_slice or
 // coulomb_fixed_blocks)
 hipError_t launch_finish_coulomb(const double *partials, const Geom &g, int bps, double *out, hipStream_t s);
@@ -114,7 +118,7 @@ hipError_t launch_gauge_transform(int fs, const void *src, int fg, const void *g
 
 // per-block partial sums of Re tr over the 6 plaquettes of every site (first
 // entry of each pair); finish with launch_finish_measure (out[0] * 12 V / 18 V)
-hipError_t launch_plaquette(int format, void *field, const Geom &g, double *partials, int *n_partials,
+hipError_t launch_plaquette(int format, const void *field, const Geom &g, double *partials, int *n_partials,
                             hipStream_t s);
 
 // Fixed-link form of the sweep (links read only, the site field gf of the
@@ -143,10 +147,10 @@ hipError_t launch_record_links(int format, const void *src, void *rec, const Geo
 // array of Lt flags)
 hipError_t launch_fixed_sweep_coulomb(int format, const void *links, void *gf, const Geom &g, const SweepArgs &a,
                                       const SweepTuning &t, int post, const uint8_t *slice_active, hipStream_t s);
-// per-timeslice partial (F_C, theta_C) pairs of one parity pass, fixed-link
-// form: Lt x coulomb_fixed_blocks(g) pairs, summed by launch_finish_coulomb
+// per-timeslice partial (F_C, theta_C) pairs of both parities, fixed-link
+// form: 2 x Lt x coulomb_fixed_blocks(g) pairs, summed by launch_finish_coulomb
 int coulomb_fixed_blocks(const Geom &g);
-hipError_t launch_measure_coulomb_fixed(int format, const void *links, const void *gf, const Geom &g, int parity,
+hipError_t launch_measure_coulomb_fixed(int format, const void *links, const void *gf, const Geom &g,
                                         double *partials, hipStream_t s, bool records);
 // per-block (F, theta) partial sums over one parity's sites, fixed-link form;
 // *n_partials = fixed_measure_blocks(g) pairs; records: links holds per-site

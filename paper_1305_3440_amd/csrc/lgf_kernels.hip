@@ -194,31 +194,74 @@ hipError_t launch_sweep(int format, void *field, const Geom &g, const SweepArgs 
 // F and theta: per-block partial sums, then one deterministic final sum.
 // ----------------------------------------------------------------------------
 
+// The reunitarizing pass over one parity.
 template <int F>
-__global__ void __launch_bounds__(kMeasureBlock) measure_kernel(void *__restrict__ field, Geom g,
-                                                                int parity, int reunit_fwd,
-                                                                int reunit_bwd, double *partials)
+__global__ void __launch_bounds__(kMeasureBlock) measure_reunit_kernel(void *__restrict__ field, Geom g, int parity,
+                                                                       int reunit_bwd, double *partials)
 {
     const uint32_t h0 = blockIdx.x * kMeasureBlock + threadIdx.x;
     const bool active = h0 < g.Vh;
     double f, th;
-    measure_site<F>(field, g, parity, active ? h0 : g.Vh - 1, active, reunit_fwd, reunit_bwd, f, th);
+    measure_site<F>(field, g, parity, active ? h0 : g.Vh - 1, active, 1, reunit_bwd, f, th);
     block_sum2<kMeasureBlock>(f, th, partials + 2 * blockIdx.x);
+}
+
+// The read-only pass over one parity (0, 1) or both (2).  HBM bound: every
+// link enters F once and theta at both of its ends, so a pass over both
+// parities needs it from memory once if the second end finds it in a cache.
+// Items 2k and 2k + 1 are tile k of the two parities, in runs per XCD: a link's
+// second use is then at most a z-plane away (x, y, z) in that XCD's L2 or a
+// t-slice away (t) in the last-level cache.  One launch instead of one per
+// parity in the order of dispatch, with the final sum and the wait: 32^4
+// FP64-18 258 -> 128 us (604 MB: the links take 96 us at a copy's rate), 64^4
+// 3095 -> 1896, 16^4 28 -> 22, FP32-12 at 32^4 84 -> 51.
+template <int F>
+__global__ void __launch_bounds__(kMeasureBlock, 2) measure_kernel(const void *__restrict__ field, Geom g, int which,
+                                                                   XcdRuns runs, uint32_t n_tiles, double *partials)
+{
+    const uint32_t b = xcd_item(blockIdx.x, runs);
+    const bool both = which == 2;
+    const uint32_t tile = both ? b >> 1 : b;
+    if (tile >= n_tiles) return;  // the whole workgroup: no partials slot
+    const int parity = both ? (int)(b & 1u) : which;
+    const uint32_t h0 = tile * kMeasureBlock + threadIdx.x;
+    const bool active = h0 < g.Vh;
+    double f, th;
+    measure_site<F>(const_cast<void *>(field), g, parity, active ? h0 : g.Vh - 1, active, 0, 0, f, th);
+    block_sum2<kMeasureBlock>(f, th, partials + 2 * ((both && parity ? n_tiles : 0u) + tile));
 }
 
 int measure_blocks(const Geom &g) { return (int)((g.Vh + kMeasureBlock - 1) / kMeasureBlock); }
 
-hipError_t launch_measure(int format, void *field, const Geom &g, int parity, bool reunit_fwd,
-                          bool reunit_bwd, double *partials, int *n_partials, hipStream_t s)
+hipError_t launch_measure(int format, const void *field, const Geom &g, int which, double *partials, int *n_partials,
+                          hipStream_t s)
 {
-    const int nb = measure_blocks(g);
-    *n_partials = nb;
-    const int rf = reunit_fwd ? 1 : 0, rb = reunit_bwd ? 1 : 0;
+    const uint32_t nb = (uint32_t)measure_blocks(g), n = which == 2 ? 2 * nb : nb;
+    *n_partials = (int)n;
+    uint32_t ng = 0;
+    const XcdRuns runs = xcd_runs(n, g, link_bytes(format) * 4, &ng);
+    const dim3 grid(ng), block(kMeasureBlock);
     switch (format) {
-    case kF64_18: hipLaunchKernelGGL((measure_kernel<kF64_18>), dim3(nb), dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
-    case kF32_18: hipLaunchKernelGGL((measure_kernel<kF32_18>), dim3(nb), dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
-    case kF32_12: hipLaunchKernelGGL((measure_kernel<kF32_12>), dim3(nb), dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
-    case kF64_12: hipLaunchKernelGGL((measure_kernel<kF64_12>), dim3(nb), dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
+    case kF64_18: hipLaunchKernelGGL((measure_kernel<kF64_18>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    case kF32_18: hipLaunchKernelGGL((measure_kernel<kF32_18>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    case kF32_12: hipLaunchKernelGGL((measure_kernel<kF32_12>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    case kF64_12: hipLaunchKernelGGL((measure_kernel<kF64_12>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_measure_reunit(int format, void *field, const Geom &g, int parity, bool reunit_bwd,
+                                 double *partials, int *n_partials, hipStream_t s)
+{
+    const int nb = measure_blocks(g), rb = reunit_bwd ? 1 : 0;
+    *n_partials = nb;
+    const dim3 grid(nb), block(kMeasureBlock);
+    switch (format) {
+    case kF64_18: hipLaunchKernelGGL((measure_reunit_kernel<kF64_18>), grid, block, 0, s, field, g, parity, rb, partials); break;
+    case kF32_18: hipLaunchKernelGGL((measure_reunit_kernel<kF32_18>), grid, block, 0, s, field, g, parity, rb, partials); break;
+    case kF32_12: hipLaunchKernelGGL((measure_reunit_kernel<kF32_12>), grid, block, 0, s, field, g, parity, rb, partials); break;
+    case kF64_12: hipLaunchKernelGGL((measure_reunit_kernel<kF64_12>), grid, block, 0, s, field, g, parity, rb, partials); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -668,33 +711,72 @@ hipError_t launch_sweep_coulomb(int format, void *field, const Geom &g, const Sw
     }
 }
 
-// grid (blocks per timeslice, Lt): every workgroup lies in one timeslice
+// The reunitarizing pass over one parity; grid (blocks per timeslice, Lt): every
+// workgroup lies in one timeslice
 template <int F>
-__global__ void __launch_bounds__(kMeasureBlock) measure_coulomb_kernel(void *__restrict__ field, Geom g,
-                                                                        int parity, int reunit_fwd,
-                                                                        int reunit_bwd, double *partials)
+__global__ void __launch_bounds__(kMeasureBlock) measure_coulomb_reunit_kernel(void *__restrict__ field, Geom g,
+                                                                               int parity, int reunit_bwd,
+                                                                               double *partials)
 {
     const uint32_t t = blockIdx.y;
     const uint32_t i = blockIdx.x * kMeasureBlock + threadIdx.x;
     const bool active = i < g.hs[0];
     const uint32_t h = t * g.hs[0] + (active ? i : g.hs[0] - 1);
     double f, th;
-    measure_site<F, 1>(field, g, parity, h, active, reunit_fwd, reunit_bwd, f, th);
+    measure_site<F, 1>(field, g, parity, h, active, 1, reunit_bwd, f, th);
     block_sum2<kMeasureBlock>(f, th, partials + 2 * ((size_t)t * gridDim.x + blockIdx.x));
+}
+
+// The read-only pass over both parities: as measure_kernel, with the workgroups
+// of a timeslice ending where it ends (bps per parity).  With the final sums and
+// the wait 32^4 FP64-18 takes 98 us (205 in two launches over blocks of a slice),
+// 64^4 1453 (2431), 48 x 24^3 FP64-12 45 (75).
+template <int F>
+__global__ void __launch_bounds__(kMeasureBlock, 2) measure_coulomb_kernel(const void *__restrict__ field, Geom g,
+                                                                           XcdRuns runs, uint32_t bps, FastDiv dbps,
+                                                                           double *partials)
+{
+    const uint32_t b = xcd_item(blockIdx.x, runs);
+    const uint32_t j = b >> 1, t = fast_div(j, dbps);
+    if (t >= g.L[0]) return;  // the whole workgroup: no partials slot
+    const int parity = (int)(b & 1u);
+    const uint32_t i = (j - t * bps) * kMeasureBlock + threadIdx.x;
+    const bool active = i < g.hs[0];
+    const uint32_t h = t * g.hs[0] + (active ? i : g.hs[0] - 1);
+    double f, th;
+    measure_site<F, 1>(const_cast<void *>(field), g, parity, h, active, 0, 0, f, th);
+    block_sum2<kMeasureBlock>(f, th, partials + 2 * ((size_t)(parity ? g.L[0] * bps : 0u) + j));
 }
 
 int coulomb_blocks_per_slice(const Geom &g) { return (int)((g.hs[0] + kMeasureBlock - 1) / kMeasureBlock); }
 
-hipError_t launch_measure_coulomb(int format, void *field, const Geom &g, int parity, bool reunit_fwd,
-                                  bool reunit_bwd, double *partials, hipStream_t s)
+hipError_t launch_measure_coulomb(int format, const void *field, const Geom &g, double *partials, hipStream_t s)
 {
-    const dim3 grid(coulomb_blocks_per_slice(g), g.L[0]);
-    const int rf = reunit_fwd ? 1 : 0, rb = reunit_bwd ? 1 : 0;
+    const uint32_t bps = (uint32_t)coulomb_blocks_per_slice(g);
+    uint32_t ng = 0;
+    const XcdRuns runs = xcd_runs(2 * bps * g.L[0], g, 0, &ng);
+    const FastDiv db = make_fast_div(bps);
+    const dim3 grid(ng), block(kMeasureBlock);
     switch (format) {
-    case kF64_18: hipLaunchKernelGGL((measure_coulomb_kernel<kF64_18>), grid, dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
-    case kF32_18: hipLaunchKernelGGL((measure_coulomb_kernel<kF32_18>), grid, dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
-    case kF32_12: hipLaunchKernelGGL((measure_coulomb_kernel<kF32_12>), grid, dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
-    case kF64_12: hipLaunchKernelGGL((measure_coulomb_kernel<kF64_12>), grid, dim3(kMeasureBlock), 0, s, field, g, parity, rf, rb, partials); break;
+    case kF64_18: hipLaunchKernelGGL((measure_coulomb_kernel<kF64_18>), grid, block, 0, s, field, g, runs, bps, db, partials); break;
+    case kF32_18: hipLaunchKernelGGL((measure_coulomb_kernel<kF32_18>), grid, block, 0, s, field, g, runs, bps, db, partials); break;
+    case kF32_12: hipLaunchKernelGGL((measure_coulomb_kernel<kF32_12>), grid, block, 0, s, field, g, runs, bps, db, partials); break;
+    case kF64_12: hipLaunchKernelGGL((measure_coulomb_kernel<kF64_12>), grid, block, 0, s, field, g, runs, bps, db, partials); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_measure_coulomb_reunit(int format, void *field, const Geom &g, int parity, bool reunit_bwd,
+                                         double *partials, hipStream_t s)
+{
+    const dim3 grid(coulomb_blocks_per_slice(g), g.L[0]), block(kMeasureBlock);
+    const int rb = reunit_bwd ? 1 : 0;
+    switch (format) {
+    case kF64_18: hipLaunchKernelGGL((measure_coulomb_reunit_kernel<kF64_18>), grid, block, 0, s, field, g, parity, rb, partials); break;
+    case kF32_18: hipLaunchKernelGGL((measure_coulomb_reunit_kernel<kF32_18>), grid, block, 0, s, field, g, parity, rb, partials); break;
+    case kF32_12: hipLaunchKernelGGL((measure_coulomb_reunit_kernel<kF32_12>), grid, block, 0, s, field, g, parity, rb, partials); break;
+    case kF64_12: hipLaunchKernelGGL((measure_coulomb_reunit_kernel<kF64_12>), grid, block, 0, s, field, g, parity, rb, partials); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -738,50 +820,104 @@ hipError_t launch_finish_coulomb(const double *partials, const Geom &g, int bps,
 
 namespace lgf {
 
+// r += a b in FP64
+template <typename T>
+__device__ __forceinline__ void add_cmul(cpx<double> &r, const cpx<T> &a, const cpx<T> &b)
+{
+    r.re = fmadd((double)a.re, (double)b.re, r.re);
+    r.re = fmadd(-(double)a.im, (double)b.im, r.re);
+    r.im = fmadd((double)a.re, (double)b.im, r.im);
+    r.im = fmadd((double)a.im, (double)b.re, r.im);
+}
+
+// Re tr[A B (C D)^dag] = sum_ij Re((AB)_ij conj((CD)_ij)), element by element
+template <typename T>
+__device__ __forceinline__ double plaq_term(const mat3<T> &A, const mat3<T> &B, const mat3<T> &C, const mat3<T> &D)
+{
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            cpx<double> ab = {0.0, 0.0}, cd = {0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                add_cmul(ab, A.e[i][k], B.e[k][j]);
+                add_cmul(cd, C.e[i][k], D.e[k][j]);
+            }
+            s = fmadd(ab.re, cd.re, s);
+            s = fmadd(ab.im, cd.im, s);
+        }
+    return s;
+}
+
+// v, which the compiler takes to depend on s (no instruction)
+__device__ __forceinline__ void after(uint32_t &v, double &s) { asm volatile("" : "+v"(v), "+v"(s)); }
+
+// Bound by the cache traffic of the 12 neighbouring links (each link is used
+// in 6 plaquettes, memory should see it once): the site's own 4 links are loaded
+// once, not once per plane, the next plane's two links are in flight while one
+// is summed, and the items go as in measure_kernel.  The products go element by
+// element, so that with the own links and two planes' neighbours in registers
+// nothing spills; FP64 runs one wave per SIMD (two waves that reload the own
+// links: 299 us at 32^4 FP64-18).  With the final sum and the wait: 32^4 FP64-18
+// 503 -> 271 us, 64^4 6561 -> 3968, FP32-12 164 -> 100 and 2125 -> 1600.
 template <int F>
-__global__ void __launch_bounds__(kMeasureBlock) plaquette_kernel(void *__restrict__ field, Geom g,
-                                                                  double *partials)
+__global__ void __launch_bounds__(kMeasureBlock) plaquette_kernel(const void *__restrict__ links, Geom g,
+                                                                  XcdRuns runs, uint32_t n_tiles, double *partials)
 {
     using T = typename Fmt<F>::T;
-    const int parity = blockIdx.y;
-    const uint32_t h0 = blockIdx.x * kMeasureBlock + threadIdx.x;
+    void *field = const_cast<void *>(links);
+    const uint32_t b = xcd_item(blockIdx.x, runs);
+    const uint32_t tile = b >> 1;
+    if (tile >= n_tiles) return;  // the whole workgroup: no partials slot
+    const int parity = (int)(b & 1u);
+    const uint32_t h0 = tile * kMeasureBlock + threadIdx.x;
     const bool active = h0 < g.Vh;
     const uint32_t h = active ? h0 : g.Vh - 1;
     const Site c = decode(g, parity, h);
+    mat3<T> own[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) load_link<F>(own[mu], block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
+    uint32_t hf[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) hf[mu] = fwd_half(g, c, h, mu);
     double sum = 0.0;
-    for (int mu = 0; mu < 4; ++mu)
-        for (int nu = mu + 1; nu < 4; ++nu) {
-            mat3<T> a, b, cc, d;
-            load_link<F>(a, block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
-            load_link<F>(b, block_ptr<F>(field, g.Vh, parity ^ 1, nu), g.Vh, fwd_half(g, c, h, mu));
-            load_link<F>(cc, block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, fwd_half(g, c, h, nu));
-            load_link<F>(d, block_ptr<F>(field, g.Vh, parity, nu), g.Vh, h);
-            mat3<double> A, B, C, D, AB, CD;
-            convert(A, a);
-            convert(B, b);
-            convert(C, cc);
-            convert(D, d);
-            left_mul<3>(AB, A, B);     // U_mu(x) U_nu(x+mu)
-            left_mul<3>(CD, D, C);     // U_nu(x) U_mu(x+nu); the loop is AB (CD)^dag
-            // Re tr[AB CD^dag] = sum_ij Re(AB_ij conj(CD_ij))
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j)
-                    sum += AB.e[i][j].re * CD.e[i][j].re + AB.e[i][j].im * CD.e[i][j].im;
+    // planes (mu, nu); the two neighbouring links of the next plane are in
+    // flight while this one is summed
+    constexpr int M[6] = {0, 0, 0, 1, 1, 2}, N[6] = {1, 2, 3, 2, 3, 3};
+    mat3<T> bl[2], cl[2];
+    load_link<F>(bl[0], block_ptr<F>(field, g.Vh, parity ^ 1, N[0]), g.Vh, hf[M[0]]);
+    load_link<F>(cl[0], block_ptr<F>(field, g.Vh, parity ^ 1, M[0]), g.Vh, hf[N[0]]);
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+        const int mu = M[p], nu = N[p];
+        if (p < 5) {
+            const int m1 = M[p + 1], n1 = N[p + 1];
+            after(hf[m1], sum);
+            after(hf[n1], sum);
+            load_link<F>(bl[(p + 1) & 1], block_ptr<F>(field, g.Vh, parity ^ 1, n1), g.Vh, hf[m1]);
+            load_link<F>(cl[(p + 1) & 1], block_ptr<F>(field, g.Vh, parity ^ 1, m1), g.Vh, hf[n1]);
         }
+        sum += plaq_term(own[mu], bl[p & 1], own[nu], cl[p & 1]);
+    }
     if (!active) sum = 0.0;
-    block_sum2<kMeasureBlock>(sum, 0.0, partials + 2 * ((size_t)parity * gridDim.x + blockIdx.x));
+    block_sum2<kMeasureBlock>(sum, 0.0, partials + 2 * ((parity ? n_tiles : 0u) + tile));
 }
 
-hipError_t launch_plaquette(int format, void *field, const Geom &g, double *partials, int *n_partials,
+hipError_t launch_plaquette(int format, const void *field, const Geom &g, double *partials, int *n_partials,
                             hipStream_t s)
 {
-    const dim3 grid(measure_blocks(g), 2);
-    *n_partials = 2 * (int)grid.x;
+    const uint32_t nb = (uint32_t)measure_blocks(g);
+    *n_partials = 2 * (int)nb;
+    uint32_t ng = 0;
+    const XcdRuns runs = xcd_runs(2 * nb, g, link_bytes(format) * 4, &ng);
+    const dim3 grid(ng), block(kMeasureBlock);
     switch (format) {
-    case kF64_18: hipLaunchKernelGGL((plaquette_kernel<kF64_18>), grid, dim3(kMeasureBlock), 0, s, field, g, partials); break;
-    case kF32_18: hipLaunchKernelGGL((plaquette_kernel<kF32_18>), grid, dim3(kMeasureBlock), 0, s, field, g, partials); break;
-    case kF32_12: hipLaunchKernelGGL((plaquette_kernel<kF32_12>), grid, dim3(kMeasureBlock), 0, s, field, g, partials); break;
-    case kF64_12: hipLaunchKernelGGL((plaquette_kernel<kF64_12>), grid, dim3(kMeasureBlock), 0, s, field, g, partials); break;
+    case kF64_18: hipLaunchKernelGGL((plaquette_kernel<kF64_18>), grid, block, 0, s, field, g, runs, nb, partials); break;
+    case kF32_18: hipLaunchKernelGGL((plaquette_kernel<kF32_18>), grid, block, 0, s, field, g, runs, nb, partials); break;
+    case kF32_12: hipLaunchKernelGGL((plaquette_kernel<kF32_12>), grid, block, 0, s, field, g, runs, nb, partials); break;
+    case kF64_12: hipLaunchKernelGGL((plaquette_kernel<kF64_12>), grid, block, 0, s, field, g, runs, nb, partials); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
