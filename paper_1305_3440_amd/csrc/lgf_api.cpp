@@ -278,14 +278,20 @@ lgf::SweepTuning default_tuning(int format)
 // The tuning of the link sweeps' launches: the handle's where it was set or
 // autotuned, else chosen by the size of the field.  The bits do not depend on
 // it.  Measured per half-sweep launch, defaults above -> chosen:
-//  - Fields of up to 380 MB stay in the 256 MB last-level cache from one
-//    half-sweep to the next (a little beyond it too: each half-sweep starts with
-//    what the last one left), but only if they are not streamed past it, and a
-//    contiguous range of the workgroups per XCD keeps each range's lines in one
-//    L2 and its pages in one TLB: 24^4 FP64-18 (191 MB) 80 -> 60 us, 28^4
-//    FP64-12 (236 MB) 100 -> 71, 32^4 FP32-12 (201 MB) 80 -> 59, 36^4 FP32-12 (322
-//    MB) 127 -> 102; streamed is better again at 403 MB (32^4 FP64-12, 143 against
-//    147 us) and 484 MB.
+//  - Fields of up to 420 MB stay in the 256 MB last-level cache from one
+//    half-sweep to the next, wholly or, since the odd half-sweep walks the lattice
+//    from its end and starts on what the even one read last, in part; but only if
+//    they are not streamed past it, and a contiguous range of the workgroups per
+//    XCD keeps each range's lines in one L2 and its pages in one TLB: 24^4 FP64-18
+//    (191 MB) 80 -> 60 us, 28^4 FP64-12 (236 MB) 100 -> 70, 32^4 FP32-12 (201 MB)
+//    80 -> 59, 28^4 FP64-18 (354 MB) 131 walked forwards -> 113, 32^4 FP64-12 (403
+//    MB) 141 -> 122.  Below 48 MB the direction makes no difference; 256-lane
+//    workgroups from 280 MB on (32^4 FP64-12 135 in 64 lanes).
+//  - Up to 1.6 GB the same, with the stores streamed, which leaves the cache to
+//    the links that are still to be read: 32^4 FP64-18 (604 MB) 202 -> 191 us (250
+//    in the defaults), 36^4 355 -> 339, FP64-12 223 -> 214 (251 best without), 40^4
+//    FP32-12 161 -> 150 (186).  At 1.5 GB 583 us against 598 (48^4 FP32-18), at 2 GB
+//    776 against 745 (48^4 FP64-12), at 64^4 3750 against 3380 (FP64-18).
 //  - Between 22 and 48 MB, around the L2s' 32 MB, streaming the links keeps
 //    what L2 has: 16^4 FP64-18 (38 MB) 11.5 against 12.6 us, FP64-12 (25 MB) 9.3
 //    against 10.5; below, 12^4 FP64-18 (12 MB) 7.9 against 7.5.
@@ -294,9 +300,6 @@ lgf::SweepTuning default_tuning(int format)
 //    (one lane, 64-lane workgroups; 8.1 in 128) -> 5.4 us, 12^4 FP32-12 5.9 -> 5.2,
 //    14^4 FP64-18 10.0 -> 9.0; 16^4 FP64-18 11.5 against 11.8.  FP64-12 keeps
 //    them throughout, two waves per SIMD instead of one: 24^4 42.3 -> 39.4 us.
-//  - Larger fields on up to 1.2 million sites: XCD ranges in 256-lane
-//    workgroups, 32^4 FP64-18 250 -> 214 us, FP64-12 162 -> 143; at 36^4 (1.68
-//    million) 387 against 388, beyond it the plain order wins by 2-5 %.
 //  - Beyond: 256-lane workgroups in FP32 (64^4 FP32-18 1749 -> 1695 us) and two
 //    lanes per site in FP32-12 (1157 -> 1111, 48^4 382 -> 374).
 lgf::SweepTuning launch_tuning(const lgf_lattice *h, int format)
@@ -304,15 +307,18 @@ lgf::SweepTuning launch_tuning(const lgf_lattice *h, int format)
     lgf::SweepTuning t = h->tune[format];
     if (h->tuned[format]) return t;
     const double mb = 4e-6 * (double)h->V * (double)lgf::link_bytes(format);
-    if (mb <= 380.0) {
+    if (mb <= 420.0) {
         t.schedule = lgf::kScheduleInPlace;
-        t.nontemporal = (mb > 22.0 && mb <= 48.0) ? 1 : 0;
+        t.nontemporal = (mb > 22.0 && mb <= 48.0) ? lgf::kStream : lgf::kCached;
         t.xcd_remap = 1;
-        t.block = 64;
+        t.backward = mb > 48.0;
+        t.block = mb > 280.0 ? 256 : 64;
         if (format == LGF_FP64_12 || h->V <= (format == LGF_FP32_12 ? 65536 : 40000)) t.lanes_per_site = 2;
-    } else if (h->V <= 1200000) {
+    } else if (mb <= 1600.0) {
         t.schedule = lgf::kScheduleInPlace;
+        t.nontemporal = lgf::kStreamStores;
         t.xcd_remap = 1;
+        t.backward = 1;
         t.block = 256;
     } else if (format == LGF_FP32_18 || format == LGF_FP32_12) {
         t.block = 256;
@@ -507,7 +513,8 @@ lgf_status measure_fused(lgf_lattice *h, int format, void *field)
 {
     const int ng = (int)lgf::sweep_groups(h->geom, launch_tuning(h, format));
     int n0 = 0;
-    LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, h->d_fused + 2 * (size_t)ng, &n0, h->stream));
+    LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, h->d_fused + 2 * (size_t)ng, &n0, h->stream,
+                                launch_tuning(h, format).nontemporal == lgf::kStream));
     LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->h_out, h->stream));
     return LGF_OK;
 }

@@ -217,6 +217,9 @@ template <typename T> __device__ __forceinline__ T *as_global(T *p)
 // the same value, of which the compiler knows nothing any more (no instruction)
 __device__ __forceinline__ void forget(uint32_t &v) { asm volatile("" : "+v"(v)); }
 
+// what of a link sweep goes past the caches: nothing, loads and stores, stores
+constexpr int kCached = 0, kStream = 1, kStreamStores = 2;
+
 // vector load / store, optionally marked non-temporal (streamed past the
 // caches: every link is read and written once per half-sweep)
 template <bool NT, typename V> __device__ __forceinline__ V vload(const V *p)
@@ -458,6 +461,13 @@ struct Geom {
     uint32_t hs[3];  // half strides of t, z, y: Lz*Ly*hx, Ly*hx, hx
     FastDiv dx, dy, dz;  // division by hx, Ly, Lz
 };
+
+// workgroup b's place when n workgroups are walked backwards, on the XCD that has
+// it forwards where n allows
+__device__ __forceinline__ uint32_t backwards(uint32_t b, uint32_t n)
+{
+    return (n & 7u) ? n - 1u - b : n - 8u - (b & ~7u) + (b & 7u);
+}
 
 // Runs for n items over the lattice g whose sites take site_bytes each (0 for
 // items that share nothing across t), and the grid they need (items at n and beyond are to be left out by the kernel).  One

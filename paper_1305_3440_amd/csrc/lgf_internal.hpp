@@ -17,12 +17,13 @@ struct SweepTuning {
     int lanes_per_site = 1;  // 1, 2 or 4
     int block = 128;         // threads per workgroup (fastest measured at 64^4)
     int xcd_remap = 0;       // contiguous workgroup ranges per XCD
-    int nontemporal = 1;     // stream links past the caches
+    int nontemporal = 1;     // kCached, kStream or kStreamStores
     int schedule = 0;        // full sweeps: 0 two in-place launches, 1 t-slice pipeline
                              // (parity 1 one slice behind), 2 out of place (ping-pong
                              // between the field and a second buffer of its format)
     int sites_per_thread = 1;  // tiles per workgroup (1, 2 or 4), strided over the launch
     int in_order = 0;  // fixed-link sweep in FP32-12, 2 lanes per site: the sums, and so the bits, of 1 lane
+    int backward = 0;  // link form: the odd half-sweep walks the lattice from its end
 };
 
 constexpr int kScheduleInPlace = 0, kSchedulePipeline = 1, kScheduleOutOfPlace = 2;
@@ -33,7 +34,7 @@ inline bool operator==(const SweepTuning &a, const SweepTuning &b)
 {
     return a.lanes_per_site == b.lanes_per_site && a.block == b.block && a.xcd_remap == b.xcd_remap &&
            a.nontemporal == b.nontemporal && a.schedule == b.schedule && a.sites_per_thread == b.sites_per_thread &&
-           a.in_order == b.in_order;
+           a.in_order == b.in_order && a.backward == b.backward;
 }
 
 struct SweepArgs {
@@ -65,7 +66,7 @@ hipError_t launch_sweep(int format, void *field, const Geom &g, const SweepArgs 
 // parity 0, 1 or both (which = 2: parity 0's blocks first), read only; the number
 // of partial pairs in *n_partials.
 hipError_t launch_measure(int format, const void *field, const Geom &g, int which, double *partials, int *n_partials,
-                          hipStream_t s);
+                          hipStream_t s, bool nontemporal = false);
 // The same over one parity with the 4 forward links of every site reunitarized
 // and stored first; reunit_bwd: the backward links reunitarized in registers
 // only (for the first parity pass, whose backward links are the other parity's

@@ -33,6 +33,14 @@ size_t link_bytes(int format)
 // Relaxation sweep
 // ----------------------------------------------------------------------------
 
+// the order of a launch's workgroups: contiguous ranges per XCD; from the end of
+// the lattice (the odd half-sweep, which then starts on what the even one read last)
+constexpr int kXcdRanges = 1, kBackward = 2;
+static int launch_order(const SweepTuning &t, int parity)
+{
+    return (t.xcd_remap ? kXcdRanges : 0) | (t.backward && parity ? kBackward : 0);
+}
+
 // One half-sweep: the sites [h_begin, h_end) of one parity, LPS lanes per
 // site, cut into n_tiles tiles of blockDim.x lanes.  Workgroup b takes the
 // tiles b, b + n_groups, b + 2 n_groups, ... (spt of them at most), so the
@@ -44,15 +52,15 @@ size_t link_bytes(int format)
 // would spill).
 template <int F, int LPS, bool SR> constexpr int sweep_waves() { return (F == kF64_12 && LPS == 2 && !SR) ? 2 : 1; }
 
-template <int F, int LPS, bool SR, bool NT, bool OOP, bool ACC, bool MEAS>
+template <int F, int LPS, bool SR, int NT, bool OOP, bool ACC, bool MEAS>
 __global__ void __launch_bounds__(256, (sweep_waves<F, LPS, SR>())) sweep_kernel(void *__restrict__ field, Geom g, int parity,
-                                                     RelaxArgs<typename Fmt<F>::T> a, int xcd_remap,
+                                                     RelaxArgs<typename Fmt<F>::T> a, int order,
                                                      uint32_t n_groups, uint32_t n_tiles, uint32_t spt,
                                                      uint32_t h_begin, uint32_t h_end,
                                                      void *__restrict__ out_field, double *__restrict__ partials)
 {
-    uint32_t b = blockIdx.x;
-    if (xcd_remap) {
+    uint32_t b = (order & kBackward) ? backwards(blockIdx.x, gridDim.x) : blockIdx.x;
+    if (order & kXcdRanges) {
         // workgroups are dealt to the 8 XCDs round-robin; give XCD k the
         // contiguous range [k*per, (k+1)*per) of workgroups so that
         // neighbouring tiles share its L2
@@ -82,14 +90,14 @@ __global__ void __launch_bounds__(256, (sweep_waves<F, LPS, SR>())) sweep_kernel
     if constexpr (MEAS) block_sum2_any(acc.f, acc.th, partials + 2 * b);
 }
 
-template <int F, int LPS, bool SR, bool NT, bool OOP, bool ACC, bool MEAS = false>
+template <int F, int LPS, bool SR, int NT, bool OOP, bool ACC, bool MEAS = false>
 static void launch_sweep_kernel(dim3 grid, int block, hipStream_t s, void *field, const Geom &g, int parity,
-                                const RelaxArgs<typename Fmt<F>::T> &ra, int xcd_remap, uint32_t n_groups,
+                                const RelaxArgs<typename Fmt<F>::T> &ra, int order, uint32_t n_groups,
                                 uint32_t n_tiles, uint32_t spt, uint32_t h_begin, uint32_t h_end, void *out,
                                 double *partials = nullptr)
 {
     hipLaunchKernelGGL((sweep_kernel<F, LPS, SR, NT, OOP, ACC, MEAS>), grid, dim3(block), 0, s, field, g, parity,
-                       ra, xcd_remap, n_groups, n_tiles, spt, h_begin, h_end, out, partials);
+                       ra, order, n_groups, n_tiles, spt, h_begin, h_end, out, partials);
 }
 
 uint32_t sweep_groups(const Geom &g, const SweepTuning &t)
@@ -100,7 +108,7 @@ uint32_t sweep_groups(const Geom &g, const SweepTuning &t)
     return (nb + spt - 1) / spt;
 }
 
-template <int F, int LPS, bool NT, bool OOP>
+template <int F, int LPS, int NT, bool OOP>
 static hipError_t launch_sweep_t(void *field, const Geom &g, const SweepArgs &a, const SweepTuning &t,
                                  hipStream_t s)
 {
@@ -114,6 +122,7 @@ static hipError_t launch_sweep_t(void *field, const Geom &g, const SweepArgs &a,
     const uint32_t grid = t.xcd_remap ? ((ng + 7u) / 8u) * 8u : ng;
     RelaxArgs<T> ra{(T)a.omega, (a.omega != 1.0) ? 1 : 0, 0, (uint32_t)a.seed, (uint32_t)(a.seed >> 32),
                     (uint32_t)a.sweep_index, a.instance, a.gacc, a.sweep_base};
+    const int order = launch_order(t, a.parity);
     const bool sr = a.p_sr > 0.0;
     if (sr) ra.sr_threshold = (uint64_t)floor(a.p_sr * 4294967296.0);
     if (a.meas) {
@@ -122,13 +131,13 @@ static hipError_t launch_sweep_t(void *field, const Geom &g, const SweepArgs &a,
         if (a.gacc) {
             if constexpr (F == kF32_12 || F == kF32_18)
                 launch_sweep_kernel<F, LPS, false, NT, OOP, true, true>(grid, t.block, s, field, g, a.parity, ra,
-                                                                        t.xcd_remap, ng, nb, spt, h_begin, h_end,
+                                                                        order, ng, nb, spt, h_begin, h_end,
                                                                         a.out, a.meas);
             else
                 return hipErrorInvalidValue;
         } else {
             launch_sweep_kernel<F, LPS, false, NT, OOP, false, true>(grid, t.block, s, field, g, a.parity, ra,
-                                                                     t.xcd_remap, ng, nb, spt, h_begin, h_end, a.out,
+                                                                     order, ng, nb, spt, h_begin, h_end, a.out,
                                                                      a.meas);
         }
         return hipGetLastError();
@@ -138,18 +147,18 @@ static hipError_t launch_sweep_t(void *field, const Geom &g, const SweepArgs &a,
         if constexpr (F == kF32_12 || F == kF32_18) {
             if (sr)
                 launch_sweep_kernel<F, LPS, true, NT, OOP, true>(grid, t.block, s, field, g, a.parity, ra,
-                                                                 t.xcd_remap, ng, nb, spt, h_begin, h_end, a.out);
+                                                                 order, ng, nb, spt, h_begin, h_end, a.out);
             else
                 launch_sweep_kernel<F, LPS, false, NT, OOP, true>(grid, t.block, s, field, g, a.parity, ra,
-                                                                  t.xcd_remap, ng, nb, spt, h_begin, h_end, a.out);
+                                                                  order, ng, nb, spt, h_begin, h_end, a.out);
         } else {
             return hipErrorInvalidValue;
         }
     } else if (sr) {
-        launch_sweep_kernel<F, LPS, true, NT, OOP, false>(grid, t.block, s, field, g, a.parity, ra, t.xcd_remap,
+        launch_sweep_kernel<F, LPS, true, NT, OOP, false>(grid, t.block, s, field, g, a.parity, ra, order,
                                                           ng, nb, spt, h_begin, h_end, a.out);
     } else {
-        launch_sweep_kernel<F, LPS, false, NT, OOP, false>(grid, t.block, s, field, g, a.parity, ra, t.xcd_remap,
+        launch_sweep_kernel<F, LPS, false, NT, OOP, false>(grid, t.block, s, field, g, a.parity, ra, order,
                                                            ng, nb, spt, h_begin, h_end, a.out);
     }
     return hipGetLastError();
@@ -161,18 +170,19 @@ static hipError_t launch_sweep_f(void *field, const Geom &g, const SweepArgs &a,
 {
     // out of place only with non-temporal access (the variant that can use it)
     const bool oop = a.out != nullptr;
-    if (oop && !t.nontemporal) return hipErrorInvalidValue;
-    const int key = t.lanes_per_site * 2 + (t.nontemporal ? 1 : 0);
+    if (oop && t.nontemporal != kStream) return hipErrorInvalidValue;
+    const int key = t.lanes_per_site * 4 + t.nontemporal;
     switch (key) {
-    case 2: return launch_sweep_t<F, 1, false, false>(field, g, a, t, s);
-    case 3: return oop ? launch_sweep_t<F, 1, true, true>(field, g, a, t, s)
-                       : launch_sweep_t<F, 1, true, false>(field, g, a, t, s);
-    case 4: return launch_sweep_t<F, 2, false, false>(field, g, a, t, s);
-    case 5: return oop ? launch_sweep_t<F, 2, true, true>(field, g, a, t, s)
-                       : launch_sweep_t<F, 2, true, false>(field, g, a, t, s);
-    case 8: return launch_sweep_t<F, 4, false, false>(field, g, a, t, s);
-    case 9: return oop ? launch_sweep_t<F, 4, true, true>(field, g, a, t, s)
-                       : launch_sweep_t<F, 4, true, false>(field, g, a, t, s);
+    case 4 + kCached: return launch_sweep_t<F, 1, kCached, false>(field, g, a, t, s);
+    case 4 + kStream: return oop ? launch_sweep_t<F, 1, kStream, true>(field, g, a, t, s)
+                                 : launch_sweep_t<F, 1, kStream, false>(field, g, a, t, s);
+    case 4 + kStreamStores: return launch_sweep_t<F, 1, kStreamStores, false>(field, g, a, t, s);
+    case 8 + kCached: return launch_sweep_t<F, 2, kCached, false>(field, g, a, t, s);
+    case 8 + kStream: return oop ? launch_sweep_t<F, 2, kStream, true>(field, g, a, t, s)
+                                 : launch_sweep_t<F, 2, kStream, false>(field, g, a, t, s);
+    case 16 + kCached: return launch_sweep_t<F, 4, kCached, false>(field, g, a, t, s);
+    case 16 + kStream: return oop ? launch_sweep_t<F, 4, kStream, true>(field, g, a, t, s)
+                                  : launch_sweep_t<F, 4, kStream, false>(field, g, a, t, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -214,8 +224,10 @@ __global__ void __launch_bounds__(kMeasureBlock) measure_reunit_kernel(void *__r
 // t-slice away (t) in the last-level cache.  One launch instead of one per
 // parity in the order of dispatch, with the final sum and the wait: 32^4
 // FP64-18 258 -> 128 us (604 MB: the links take 96 us at a copy's rate), 64^4
-// 3095 -> 1896, 16^4 28 -> 22, FP32-12 at 32^4 84 -> 51.
-template <int F>
+// 3095 -> 1896, 16^4 28 -> 22, FP32-12 at 32^4 84 -> 51.  NT where the sweeps
+// stream: lines left in the L2s by cached loads slow every later sweep (16^4
+// FP64-18 12.1 us, 11.6 after NT).
+template <int F, bool NT>
 __global__ void __launch_bounds__(kMeasureBlock, 2) measure_kernel(const void *__restrict__ field, Geom g, int which,
                                                                    XcdRuns runs, uint32_t n_tiles, double *partials)
 {
@@ -227,14 +239,15 @@ __global__ void __launch_bounds__(kMeasureBlock, 2) measure_kernel(const void *_
     const uint32_t h0 = tile * kMeasureBlock + threadIdx.x;
     const bool active = h0 < g.Vh;
     double f, th;
-    measure_site<F>(const_cast<void *>(field), g, parity, active ? h0 : g.Vh - 1, active, 0, 0, f, th);
+    measure_site<F, 0, NT>(const_cast<void *>(field), g, parity, active ? h0 : g.Vh - 1, active, 0, 0, f, th);
     block_sum2<kMeasureBlock>(f, th, partials + 2 * ((both && parity ? n_tiles : 0u) + tile));
 }
 
 int measure_blocks(const Geom &g) { return (int)((g.Vh + kMeasureBlock - 1) / kMeasureBlock); }
 
-hipError_t launch_measure(int format, const void *field, const Geom &g, int which, double *partials, int *n_partials,
-                          hipStream_t s)
+template <bool NT>
+static hipError_t launch_measure_t(int format, const void *field, const Geom &g, int which, double *partials,
+                                   int *n_partials, hipStream_t s)
 {
     const uint32_t nb = (uint32_t)measure_blocks(g), n = which == 2 ? 2 * nb : nb;
     *n_partials = (int)n;
@@ -242,13 +255,20 @@ hipError_t launch_measure(int format, const void *field, const Geom &g, int whic
     const XcdRuns runs = xcd_runs(n, g, link_bytes(format) * 4, &ng);
     const dim3 grid(ng), block(kMeasureBlock);
     switch (format) {
-    case kF64_18: hipLaunchKernelGGL((measure_kernel<kF64_18>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
-    case kF32_18: hipLaunchKernelGGL((measure_kernel<kF32_18>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
-    case kF32_12: hipLaunchKernelGGL((measure_kernel<kF32_12>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
-    case kF64_12: hipLaunchKernelGGL((measure_kernel<kF64_12>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    case kF64_18: hipLaunchKernelGGL((measure_kernel<kF64_18, NT>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    case kF32_18: hipLaunchKernelGGL((measure_kernel<kF32_18, NT>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    case kF32_12: hipLaunchKernelGGL((measure_kernel<kF32_12, NT>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
+    case kF64_12: hipLaunchKernelGGL((measure_kernel<kF64_12, NT>), grid, block, 0, s, field, g, which, runs, nb, partials); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_measure(int format, const void *field, const Geom &g, int which, double *partials, int *n_partials,
+                          hipStream_t s, bool nontemporal)
+{
+    return nontemporal ? launch_measure_t<true>(format, field, g, which, partials, n_partials, s)
+                       : launch_measure_t<false>(format, field, g, which, partials, n_partials, s);
 }
 
 hipError_t launch_measure_reunit(int format, void *field, const Geom &g, int parity, bool reunit_bwd,
@@ -637,14 +657,14 @@ hipError_t launch_field_to_canon(int format, const void *field, const int64_t *s
 
 namespace lgf {
 
-template <int F, int LPS, bool SR, bool NT, bool ACC = false>
+template <int F, int LPS, bool SR, int NT, bool ACC = false>
 __global__ void __launch_bounds__(256) sweep_coulomb_kernel(void *__restrict__ field, Geom g, int parity,
-                                                            RelaxArgs<typename Fmt<F>::T> a, int xcd_remap,
+                                                            RelaxArgs<typename Fmt<F>::T> a, int order,
                                                             uint32_t n_groups,
                                                             const uint8_t *__restrict__ slice_active)
 {
-    uint32_t b = blockIdx.x;
-    if (xcd_remap) {
+    uint32_t b = (order & kBackward) ? backwards(blockIdx.x, gridDim.x) : blockIdx.x;
+    if (order & kXcdRanges) {
         // a contiguous range of workgroups per XCD, as in sweep_kernel
         b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
         if (b >= n_groups) return;
@@ -656,7 +676,7 @@ __global__ void __launch_bounds__(256) sweep_coulomb_kernel(void *__restrict__ f
                                                slice_active);
 }
 
-template <int F, int LPS, bool NT>
+template <int F, int LPS, int NT>
 static hipError_t launch_sweep_coulomb_t(void *field, const Geom &g, const SweepArgs &a,
                                          const uint8_t *slice_active, const SweepTuning &t, hipStream_t s)
 {
@@ -669,7 +689,7 @@ static hipError_t launch_sweep_coulomb_t(void *field, const Geom &g, const Sweep
     if (sr) ra.sr_threshold = (uint64_t)floor(a.p_sr * 4294967296.0);
 #define LGF_SC(SRV, ACCV)                                                                                            \
     hipLaunchKernelGGL((sweep_coulomb_kernel<F, LPS, SRV, NT, ACCV>), grid, block, 0, s, field, g, a.parity, ra,     \
-                       t.xcd_remap, ng, slice_active)
+                       launch_order(t, a.parity), ng, slice_active)
     if (a.gacc) {
         // the accumulated gauge transformation belongs to the FP32 bulk only
         if constexpr (F == kF32_12 || F == kF32_18) {
@@ -691,11 +711,15 @@ template <int F>
 static hipError_t launch_sweep_coulomb_f(void *field, const Geom &g, const SweepArgs &a, const uint8_t *slice_active,
                                          const SweepTuning &t, hipStream_t s)
 {
-    if (t.lanes_per_site == 2)
-        return t.nontemporal ? launch_sweep_coulomb_t<F, 2, true>(field, g, a, slice_active, t, s)
-                             : launch_sweep_coulomb_t<F, 2, false>(field, g, a, slice_active, t, s);
-    return t.nontemporal ? launch_sweep_coulomb_t<F, 1, true>(field, g, a, slice_active, t, s)
-                         : launch_sweep_coulomb_t<F, 1, false>(field, g, a, slice_active, t, s);
+    const bool two = t.lanes_per_site == 2;
+    switch (t.nontemporal) {
+    case kCached: return two ? launch_sweep_coulomb_t<F, 2, kCached>(field, g, a, slice_active, t, s)
+                             : launch_sweep_coulomb_t<F, 1, kCached>(field, g, a, slice_active, t, s);
+    case kStream: return two ? launch_sweep_coulomb_t<F, 2, kStream>(field, g, a, slice_active, t, s)
+                             : launch_sweep_coulomb_t<F, 1, kStream>(field, g, a, slice_active, t, s);
+    case kStreamStores: if (!two) return launch_sweep_coulomb_t<F, 1, kStreamStores>(field, g, a, slice_active, t, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_sweep_coulomb(int format, void *field, const Geom &g, const SweepArgs &a,

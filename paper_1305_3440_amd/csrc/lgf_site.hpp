@@ -165,7 +165,7 @@ __device__ __forceinline__ typename Fmt<F>::V *site_field_ptr(void *field, uint3
 // and the site's F and theta contributions are taken from them: the forward
 // links' Re tr into acc->f and tr[Delta Delta^dag] of x, from the new links
 // around it (every one of them written by this update), into acc->th.
-template <int F, int LPS, bool SR, bool NT, int MU0 = 0, bool OOP = false, bool ACC = false, bool MEAS = false>
+template <int F, int LPS, bool SR, int NT, int MU0 = 0, bool OOP = false, bool ACC = false, bool MEAS = false>
 __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom &g, int parity, uint32_t h,
                                             int lane, bool active, const RelaxArgs<typename Fmt<F>::T> &a,
                                             const uint8_t *__restrict__ slice_active = nullptr,
@@ -187,8 +187,8 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
     for (int k = 0; k < NL; ++k) {
         const int mu = lane + k * LPS;
         hb[k] = back_half(g, c, h, mu);
-        load_link<F, NT>(uf[k], block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
-        load_link<F, NT>(ub[k], block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, hb[k]);
+        load_link<F, NT == kStream>(uf[k], block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
+        load_link<F, NT == kStream>(ub[k], block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, hb[k]);
     }
 
     mat3<T> K;
@@ -275,8 +275,8 @@ __device__ __forceinline__ void update_site(void *__restrict__ field, const Geom
                 add_fwd_bwd(Kn, df, db);
             }
         }
-        store_link<F, NT>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity, mu), g.Vh, hs, r);
-        store_link<F, NT>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity ^ 1, mu), g.Vh, hb[k], rb);
+        store_link<F, NT != kCached>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity, mu), g.Vh, hs, r);
+        store_link<F, NT != kCached>(block_ptr<F>(OOP ? out_field : field, g.Vh, parity ^ 1, mu), g.Vh, hb[k], rb);
     }
     if constexpr (MEAS) {
         if constexpr (LPS != 2) lane_sum<LPS>(Kn);
@@ -704,7 +704,7 @@ __device__ __forceinline__ void block_sum2(double a, double b, double *out)
 // links).  Inactive lanes return zeros and store nothing.  MU0 = 1 measures
 // the Coulomb-gauge functional and precision (spatial links only), while the
 // temporal forward links are still reunitarized when asked.
-template <int F, int MU0 = 0>
+template <int F, int MU0 = 0, bool NT = false>
 __device__ __forceinline__ void measure_site(void *__restrict__ field, const Geom &g, int parity, uint32_t h,
                                              bool active, int reunit_fwd, int reunit_bwd, double &f, double &th)
 {
@@ -717,7 +717,7 @@ __device__ __forceinline__ void measure_site(void *__restrict__ field, const Geo
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
         mat3<T> ut, vt;
-        load_link<F>(ut, block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
+        load_link<F, NT>(ut, block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
         mat3<double> u, v;
         convert(u, ut);
         if (mu < MU0) {
@@ -729,7 +729,7 @@ __device__ __forceinline__ void measure_site(void *__restrict__ field, const Geo
             }
             continue;
         }
-        load_link<F>(vt, block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, back_half(g, c, h, mu));
+        load_link<F, NT>(vt, block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, back_half(g, c, h, mu));
         convert(v, vt);
         // Reunitarized links are measured exactly as they will be stored and
         // read back (rounded to the storage precision, row 2 rebuilt for the

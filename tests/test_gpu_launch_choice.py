@@ -18,11 +18,12 @@ def lgf():
     return lib
 
 
-# volumes on both sides of 40000 and 65536 sites, fields of 20, 24, 47, 49 MB (FP64-18 or FP64-12) and beyond 380 MB
+# volumes on both sides of 40000 and 65536 sites, fields of 20, 24, 47, 49 MB (FP64-18 or FP64-12), around 380 and
+# beyond 420 MB
 LINK_CASES = [((2, 2, 2, 2), 0), ((4, 4, 6, 10), 1), ((4, 4, 6, 10), 2), ((6, 2, 4, 14), 3), ((14, 14, 14, 14), 0),
               ((14, 14, 14, 16), 0), ((16, 16, 16, 16), 2), ((16, 16, 18, 16), 2), ((18, 16, 20, 14), 0),
               ((18, 16, 20, 16), 0), ((22, 24, 22, 10), 3), ((28, 28, 28, 30), 3), ((28, 28, 28, 32), 0),
-              ((34, 32, 32, 32), 2), ((34, 34, 34, 34), 1)]
+              ((34, 32, 32, 32), 2), ((34, 34, 34, 34), 1), ((34, 38, 34, 30), 1), ((34, 32, 38, 34), 3)]
 
 
 @pytest.mark.parametrize("dims,fmt", LINK_CASES)
