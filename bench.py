@@ -213,8 +213,8 @@ def summarize_traffic(fetch_dir, write_dir, dims, command):
     import csv
     per = {}
     fixed_seq = {}  # (counter, format, lanes, layout) -> plain fixed-sweep readings in dispatch order
-    # fixed_sweep_kernel<format, lanes, SR, post, mu0, records (, in order)>: the plain Landau instances
-    fixed_pat = re.compile(r"fixed_sweep_kernel<(\d+),\s*(\d+),\s*false,\s*0,\s*0,\s*(true|false)(?:,\s*false)?>")
+    # fixed_sweep_kernel<format, lanes, SR, post, mu0, records (, in order, cached links)>: the plain Landau instances
+    fixed_pat = re.compile(r"fixed_sweep_kernel<(\d+),\s*(\d+),\s*false,\s*0,\s*0,\s*(true|false)(?:,\s*false)*>")
     for counter, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         with open(_find(d, "counter_collection.csv")) as f:
             rows = [r for r in csv.DictReader(f) if r.get("Counter_Name") == counter]
@@ -236,7 +236,7 @@ def summarize_traffic(fetch_dir, write_dir, dims, command):
                                        "bytes_per_counter_unit": scale[counter]}
     # sweep_kernel<format, lanes per site, SR, non-temporal, out of place,
     # accumulate g, fused measurement>: the plain sweep instances
-    pat = re.compile(r"sweep_kernel<(\d+),\s*(\d+),\s*(true|false),\s*(true|false),\s*(true|false),"
+    pat = re.compile(r"sweep_kernel<(\d+),\s*(\d+),\s*(true|false),\s*(true|false|0|1),\s*(true|false),"
                      r"\s*false,\s*false>")
     Vh = dims[0] * dims[1] * dims[2] * dims[3] // 2
     for (counter, kname), vals in per.items():
@@ -244,7 +244,7 @@ def summarize_traffic(fetch_dir, write_dir, dims, command):
         if not m:
             continue
         fmt, lanes = int(m.group(1)), int(m.group(2))
-        key = traffic_key(fmt, lanes, m.group(4) == "true", 2 if m.group(5) == "true" else 0, dims)
+        key = traffic_key(fmt, lanes, m.group(4) in ("true", "1"), 2 if m.group(5) == "true" else 0, dims)
         e = out["kernels"].setdefault(key, {"kernel": kname, "format": fmt})
         e[counter.lower() + "_bytes_per_launch"] = sum(vals) / len(vals) * scale[counter]
         e[counter.lower() + "_dispatches"] = len(vals)

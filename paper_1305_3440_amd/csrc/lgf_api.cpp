@@ -650,10 +650,10 @@ bool pick_variant(const std::vector<lgf::SweepTuning> &variants, const lgf::Swee
 // transformation g, a site field in the sweep's format.
 // ----------------------------------------------------------------------------
 
-// Lattices from this many sites on read per-site link records by default:
-// measured faster from 24^4 up (FP64-12 4-6 % at 24^4 and 32^4), slower at
-// 16^4, where a half-sweep takes about 10 us and the records' larger
-// footprint costs more than their layout returns.
+// Lattices from this many sites on have per-site link records in the starting
+// tuning: streamed past the caches they are faster than the streamed link field
+// from 24^4 up (FP64-12 4-6 % at 24^4 and 32^4) and slower at 16^4, where a
+// half-sweep takes about 10 us.  (Untuned launches: launch_fixed_tuning.)
 constexpr int64_t kRecordsMinSites = 1 << 18;
 
 // Starting tuning of the fixed-link sweep (the fastest measured at 64^4):
@@ -682,6 +682,11 @@ lgf::SweepTuning default_fixed_tuning(int format, int64_t V)
     return t;
 }
 
+// format of the gauge transformation of a fixed-link sweep format (FP64-12
+// for the split links) and its site field
+int gf_format(int format) { return format == LGF_FP64_12S ? LGF_FP64_12 : format; }
+void *gfix_of(lgf_lattice *h, int format) { return h->gfix[gf_format(format)]; }
+
 // The tuning of the fixed-link sweeps' launches: the handle's where it was
 // set or autotuned, else chosen by the lattice's size, with the same bits.  Up
 // to 2 million sites a contiguous range of tiles per XCD (order 1) beats the
@@ -690,23 +695,32 @@ lgf::SweepTuning default_fixed_tuning(int format, int64_t V)
 // FP64-18 181 -> 147; at 40^4 (2.56 million) 251 against 245 us.  Small lattices
 // take 64-lane workgroups to reach more CUs, and FP32-12 two lanes per site up
 // to 80000 sites, adding the terms of M in the order of one: 12^4 6.7 -> 5.4 us.
+// While links and g together take up to 400 MB the links are the link field,
+// read through the caches, the odd half-sweep from the end: the 256 MB last-level
+// cache keeps much or all of it from one half-sweep to the next, where the
+// records, streamed past it, are twice as large.  16^4 FP64-12 9.2 -> 8.3 us,
+// 24^4 35.0 -> 32.3 (FP32-12 21.1 -> 17.3), 36 x 20 x 28 x 24 FP32-12 26.9 -> 23.0,
+// 48 x 24^3 FP64-12 (318 MB with g) 66.3 -> 59.2, 30^4 (389 MB) 80.7 -> 78.6; at
+// 403 MB (32^4 split, 36^4 FP32-12) 90.6 against 88.5 and 80.4 against 81.0, 32^4
+// FP64-12 (503 MB) 101.6 against 99.2, 36^4 174.6 against 159.8.
 lgf::SweepTuning launch_fixed_tuning(const lgf_lattice *h, int format)
 {
     lgf::SweepTuning t = h->tune_fixed[format];
     if (h->tuned_fixed[format] || h->V > 2000000) return t;
     t.xcd_remap = 1;
     t.block = (h->V <= kRecordsMinSites) ? 64 : 128;
+    const double link = format == LGF_FP64_12S ? 72.0 : (double)lgf::link_bytes(format);
+    if (1e-6 * (double)h->V * (4.0 * link + (double)lgf::link_bytes(gf_format(format))) <= 400.0) {
+        t.schedule = lgf::kLayoutPlanes;
+        t.nontemporal = lgf::kCached;
+        t.backward = 1;
+    }
     if (format == LGF_FP32_12 && h->V <= 80000) {
         t.lanes_per_site = 2;
         t.in_order = 1;
     }
     return t;
 }
-
-// format of the gauge transformation of a fixed-link sweep format (FP64-12
-// for the split links) and its site field
-int gf_format(int format) { return format == LGF_FP64_12S ? LGF_FP64_12 : format; }
-void *gfix_of(lgf_lattice *h, int format) { return h->gfix[gf_format(format)]; }
 
 bool valid_fixed_format(int f) { return valid_format(f) || f == LGF_FP64_12S; }
 
@@ -755,7 +769,7 @@ lgf_status links_in_format(lgf_lattice *h, int format, void **links)
 // whether the Landau fixed-link sweeps in `format` read per-site link records
 bool fixed_records(const lgf_lattice *h, int format)
 {
-    return h->tune_fixed[format].schedule == lgf::kLayoutRecords;
+    return launch_fixed_tuning(h, format).schedule == lgf::kLayoutRecords;
 }
 
 // the per-site link records of format (a 12-real format) built from its link

@@ -43,6 +43,7 @@ struct TileOrder {
     uint32_t lB, nzb;      // log2 of the block extents in t and z; Lz >> lB
     uint32_t tpb;          // tiles per block, P << 2 lB
     FastDiv dtpb, dnzb, dG;  // division by tpb, nzb and P / 8
+    uint32_t backward;       // the tiles from the last one on
 };
 
 // One half-sweep over all Vh sites of a parity, LPS lanes per site; POST as
@@ -50,14 +51,14 @@ struct TileOrder {
 // when POST == 2.  MU0 = 1: Coulomb gauge, with the timeslice flags
 // slice_active.  REC: the links are per-site link records.  SEQ: 2 lanes per
 // site with the sums of one lane per site.
-template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false, bool SEQ = false>
+template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false, bool SEQ = false, bool CACHED = false>
 __global__ void __launch_bounds__(256, (fixed_waves<F, LPS, POST>())) fixed_sweep_kernel(const void *__restrict__ links, void *__restrict__ gf,
                                                           Geom g, int parity, RelaxArgs<typename Fmt<F>::T> a,
                                                           TileOrder o, uint32_t n_groups,
                                                           double *__restrict__ partials,
                                                           const uint8_t *__restrict__ slice_active)
 {
-    const uint32_t b = blockIdx.x;
+    const uint32_t b = o.backward ? backwards(blockIdx.x, gridDim.x) : blockIdx.x;
     uint32_t h0;        // first site of the tile (Vh <= 2^30, LPS <= 4)
     uint32_t slot = b;  // partial-sum slot: the tile's index, < n_groups, so
                         // that the final sum does not depend on the order
@@ -83,7 +84,7 @@ __global__ void __launch_bounds__(256, (fixed_waves<F, LPS, POST>())) fixed_swee
     const uint32_t grp = h0 + threadIdx.x / LPS;
     const bool active = grp < g.Vh;
     MeasAcc acc;
-    update_site_fixed<F, LPS, SR, POST, MU0, REC, SEQ>(
+    update_site_fixed<F, LPS, SR, POST, MU0, REC, SEQ, CACHED>(
         links, gf, g, parity, active ? grp : g.Vh - 1, (int)(threadIdx.x % LPS), active, a, &acc, slice_active);
     if constexpr (POST == 2) block_sum2_any(acc.f, acc.th, partials + 2 * slot);
 }
@@ -139,13 +140,14 @@ bool fixed_order_admitted(const Geom &g, const SweepTuning &t, int order)
     return (int)tile_order(g, b).mode == order;
 }
 
-template <int F, int LPS, bool REC, bool SEQ = false>
+template <int F, int LPS, bool REC, bool SEQ = false, bool CACHED = false>
 static hipError_t launch_fixed_t(const void *links, void *gf, const Geom &g, const SweepArgs &a, const SweepTuning &t,
                                  int post, const uint8_t *slices, bool coulomb, hipStream_t s)
 {
     using T = typename Fmt<F>::T;
     const uint32_t ng = fixed_sweep_groups(g, t);
-    const TileOrder o = tile_order(g, t);
+    TileOrder o = tile_order(g, t);
+    o.backward = (t.backward && a.parity) ? 1u : 0u;
     const dim3 grid(o.mode == 1 ? ((ng + 7u) / 8u) * 8u : ng), block(t.block);
     RelaxArgs<T> ra{(T)a.omega, (a.omega != 1.0) ? 1 : 0, 0, (uint32_t)a.seed, (uint32_t)(a.seed >> 32),
                     (uint32_t)a.sweep_index, a.instance, nullptr, a.sweep_base};
@@ -154,10 +156,10 @@ static hipError_t launch_fixed_t(const void *links, void *gf, const Geom &g, con
     double *m = a.meas;
     if (post == 2 && (!m || coulomb)) return hipErrorInvalidValue;
 #define LGF_FIX_LAUNCH(SRV, P) \
-    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 0, REC, SEQ>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
+    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 0, REC, SEQ, CACHED>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
                        ng, m, nullptr)
 #define LGF_FIX_LAUNCH_C(SRV, P) \
-    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 1, REC, SEQ>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
+    hipLaunchKernelGGL((fixed_sweep_kernel<F, LPS, SRV, P, 1, REC, SEQ, CACHED>), grid, block, 0, s, links, gf, g, a.parity, ra, o, \
                        ng, nullptr, slices)
     if (coulomb) {
         if (sr) {
@@ -187,25 +189,27 @@ bool fixed_records_format(int format) { return format == kF32_12 || format == kF
 // registers and runs one wave per SIMD, slower than two lanes per site)
 bool fixed_one_lane_format(int format) { return format == kF32_12 || format == kF32_18; }
 
-template <int F, bool REC>
+template <int F, bool REC, bool CACHED = false>
 static hipError_t launch_fixed_r(const void *links, void *gf, const Geom &g, const SweepArgs &a, const SweepTuning &t,
                                  int post, const uint8_t *slices, bool coulomb, hipStream_t s)
 {
     switch (t.lanes_per_site) {
     case 1:
         if constexpr (F == kF32_12 || F == kF32_18)
-            return launch_fixed_t<F, 1, REC>(links, gf, g, a, t, post, slices, coulomb, s);
+            return launch_fixed_t<F, 1, REC, false, CACHED>(links, gf, g, a, t, post, slices, coulomb, s);
         else
             return hipErrorInvalidValue;
     case 2:
         if (t.in_order) {
             if constexpr (F == kF32_12)
-                return launch_fixed_t<F, 2, REC, true>(links, gf, g, a, t, post, slices, coulomb, s);
+                return launch_fixed_t<F, 2, REC, true, CACHED>(links, gf, g, a, t, post, slices, coulomb, s);
             else
                 return hipErrorInvalidValue;
         }
-        return launch_fixed_t<F, 2, REC>(links, gf, g, a, t, post, slices, coulomb, s);
-    case 4: return launch_fixed_t<F, 4, REC>(links, gf, g, a, t, post, slices, coulomb, s);
+        return launch_fixed_t<F, 2, REC, false, CACHED>(links, gf, g, a, t, post, slices, coulomb, s);
+    case 4:
+        if constexpr (!CACHED) return launch_fixed_t<F, 4, REC>(links, gf, g, a, t, post, slices, coulomb, s);
+        else return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
 }
@@ -220,6 +224,8 @@ static hipError_t launch_fixed_f(const void *links, void *gf, const Geom &g, con
         else
             return hipErrorInvalidValue;
     }
+    if (t.nontemporal == kCached)
+        return launch_fixed_r<F, false, true>(links, gf, g, a, t, post, slices, coulomb, s);
     return launch_fixed_r<F, false>(links, gf, g, a, t, post, slices, coulomb, s);
 }
 

@@ -433,12 +433,12 @@ __device__ __forceinline__ void meas_term_bwd(mat3<double> &acc, const mat3<T> &
 
 // link mu of parity-`parity` site h for the fixed-link sweep in format F
 // (kF64_12S: from the split storage; row 2 left unset)
-template <int F>
+template <int F, bool NT>
 __device__ __forceinline__ void load_fixed_link(mat3<typename Fmt<F>::T> &u, void *links, uint32_t Vh, int parity,
                                                 int mu, uint32_t h)
 {
-    if constexpr (F == kF64_12S) load_link_split<true>(u, links, Vh, parity, mu, h);
-    else load_link<F, true, false>(u, block_ptr<F>(links, Vh, parity, mu), Vh, h);
+    if constexpr (F == kF64_12S) load_link_split<NT>(u, links, Vh, parity, mu, h);
+    else load_link<F, NT, false>(u, block_ptr<F>(links, Vh, parity, mu), Vh, h);
 }
 
 // Waves per SIMD that a fixed-link sweep kernel is compiled for: three for
@@ -467,7 +467,8 @@ template <int F, int LPS, int POST> constexpr int fixed_waves()
 // SEQ (2 lanes, FP32): the terms of M are added direction by direction, as one
 // lane per site adds them, so the two forms give the same bits; otherwise each
 // lane adds its own terms and the lanes' sums are added.
-template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false, bool SEQ = false>
+// CACHED: the link field goes through the caches (records never do).
+template <int F, int LPS, bool SR, int POST, int MU0 = 0, bool REC = false, bool SEQ = false, bool CACHED = false>
 __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links, void *__restrict__ gf,
                                                   const Geom &g, int parity, uint32_t h, int lane, bool active,
                                                   const RelaxArgs<typename Fmt<F>::T> &a, MeasAcc *acc,
@@ -508,7 +509,7 @@ __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links
         if (mu >= MU0) {
             mat3<T> u, y;
             if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, rp);
-            else load_fixed_link<F>(u, U, g.Vh, parity, mu, h);
+            else load_fixed_link<F, !CACHED>(u, U, g.Vh, parity, mu, h);
             load_link<F, false, false>(y, gn, g.Vh, fwd_half(g, c, h, mu));
             if constexpr (R == 2) row2_fma(y);
             mul_dag_fma<R>(pf, u, y);
@@ -520,7 +521,7 @@ __device__ __forceinline__ void update_site_fixed(const void *__restrict__ links
             }
             const uint32_t hb = back_half(g, c, h, mu);
             if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, rp);
-            else load_fixed_link<F>(u, U, g.Vh, parity ^ 1, mu, hb);
+            else load_fixed_link<F, !CACHED>(u, U, g.Vh, parity ^ 1, mu, hb);
             load_link<F, false, false>(y, gn, g.Vh, hb);
             if constexpr (R == 2) row2_fma(u);
             mul_fma<R>(pb, y, u);
@@ -622,13 +623,13 @@ __device__ __forceinline__ void measure_site_fixed(const void *__restrict__ link
         if (mu < MU0) continue;
         mat3<T> u, y;
         if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, mu, rp);
-        else load_fixed_link<F>(u, U, g.Vh, parity, mu, h);
+        else load_fixed_link<F, false>(u, U, g.Vh, parity, mu, h);
         load_link<F, false, false>(y, gn, g.Vh, fwd_half(g, c, h, mu));
         if constexpr (R == 2) row2_fma(y);
         meas_term_fwd<R>(Mf, u, y);
         const uint32_t hb = back_half(g, c, h, mu);
         if constexpr (REC) load_link_rec<F>(u, U, g.Vh, parity, 4 + mu, rp);
-        else load_fixed_link<F>(u, U, g.Vh, parity ^ 1, mu, hb);
+        else load_fixed_link<F, false>(u, U, g.Vh, parity ^ 1, mu, hb);
         load_link<F, false, false>(y, gn, g.Vh, hb);
         if constexpr (R == 2) row2_fma(u);
         meas_term_bwd<R>(Mb, y, u);

@@ -50,7 +50,8 @@ def test_link_sweeps_do_not_depend_on_the_choice(lgf, dims, fmt):
 
 
 FIXED_CASES = [(dims, fmt) for dims in ((2, 2, 2, 2), (4, 4, 6, 10), (6, 2, 4, 14), (14, 14, 18, 22), (14, 14, 18, 24))
-               for fmt in (2, 3, 4)] + [((4, 4, 6, 10), 0), ((4, 4, 6, 10), 1), ((16, 16, 32, 34), 3)]
+               for fmt in (2, 3, 4)] + [((4, 4, 6, 10), 0), ((4, 4, 6, 10), 1), ((16, 16, 32, 34), 3), ((28, 30, 32, 30), 4),
+                                                           ((32, 30, 32, 34), 3), ((24, 24, 26, 28), 1)]
 
 
 @pytest.mark.parametrize("gauge", ["landau", "coulomb"])
