@@ -29,6 +29,8 @@ constexpr int kEnsFixedLanes = 2;
 struct EnsTile {        // `tile` consecutive half indices of one configuration
     uint32_t cfg;
     uint32_t h0;
+    uint32_t slot;      // its place in the order of the configurations and their sites: the partial sums' slot
+    uint32_t pad;       // one 16-byte load
 };
 
 struct EnsSpan {        // the tiles [first, first + count) of configuration cfg
@@ -49,6 +51,7 @@ struct EnsLaunch {      // device pointers of one ensemble's work list
     const EnsCfg *cfgs;
     const EnsTile *tiles;
     const uint32_t *n_tiles;
+    uint32_t max_tiles; // entries allocated at tiles (>= 1)
     const uint64_t *sweep_base;
     uint32_t grid;      // persistent workgroups
     uint32_t tile;      // sites per tile = lanes per workgroup (64, 128 or 256)
@@ -70,16 +73,21 @@ int ensemble_persistent_grid(int fa, int fb, bool sr, bool nt, int tile, int gri
 // updated; post as launch_fixed_sweep: 0 plain, 1 g reunitarized as stored,
 // 2 also the per-tile (F, theta) sums in the second-pass slots of meas) and
 // its read-only measurement pass (one workgroup per listed tile).  Format
-// pairs: ensemble_fixed_pair.  rec: every listed configuration reads its
-// links from cfgs[].rec (pairs of ensemble_fixed_records_pair only).
+// pairs: ensemble_fixed_pair.  src: where the links of every listed
+// configuration come from.
+enum EnsLinks {
+    kEnsStream,   // the link fields, past the caches
+    kEnsRecords,  // cfgs[].rec (pairs of ensemble_fixed_records_pair only)
+    kEnsCached    // the link fields, through the caches
+};
 bool ensemble_fixed_pair(int fa, int fb);
 bool ensemble_fixed_records_pair(int fa, int fb);
 hipError_t launch_ensemble_fixed_sweep(int fa, int fb, const EnsLaunch &L, int parity, const EnsRelax &r,
                                        uint32_t sweep_offset, bool sr, int post, double *meas, hipStream_t s,
-                                       bool rec);
+                                       EnsLinks src);
 hipError_t launch_ensemble_fixed_measure(int fa, int fb, const EnsLaunch &L, uint32_t n_tiles, int parity,
-                                         double *partials, hipStream_t s, bool rec);
-int ensemble_fixed_grid(int fa, int fb, bool sr, int tile, int grid_mult, bool rec);
+                                         double *partials, hipStream_t s, EnsLinks src);
+int ensemble_fixed_grid(int fa, int fb, bool sr, int tile, int grid_mult, EnsLinks src);
 // *p = v, as a one-lane kernel on the stream (safe inside a captured graph)
 hipError_t launch_set_u64(uint64_t *p, uint64_t v, hipStream_t s);
 

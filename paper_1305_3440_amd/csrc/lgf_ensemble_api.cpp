@@ -32,7 +32,7 @@ struct EnsGraph {
     int tile, grid_mult;
     bool fused;
     bool fixed;  // fixed-link form
-    bool rec;    // fixed-link form on per-site link records
+    lgf::EnsLinks src;  // fixed-link form: where the links come from
     hipGraphExec_t exec;
 };
 
@@ -138,12 +138,25 @@ lgf_status ensure_gfix(lgf_ensemble *e, int fmt)
 
 void *rec_of(lgf_ensemble *e, int fmt, int i) { return (char *)e->rec[fmt] + e->rec_off[fmt][i]; }
 
+// Whether the fixed-link sweeps read the link fields through the caches: while
+// the links and g of the whole ensemble in format f (in FP64-12 for every format
+// with records) take up to 400 MB, the line of the single lattice's sweeps for
+// the same reason.  Six configurations of 4096 to 20736 sites, per launch:
+// 7.6 -> 6.3 us (FP64-12), 10.4 -> 8.6 (both precisions), 8.1 -> 6.9 (FP32-12),
+// with the tiles in XCD ranges and their first loads in one latency.
+bool fixed_cached(const lgf_ensemble *e, int f)
+{
+    int64_t V = 0;
+    for (int64_t v : e->V) V += v;
+    return (f == LGF_FP64_18 ? 720e-6 : 480e-6) * (double)V <= 400.0;
+}
+
 // per-site link records of format fmt for every configuration; false (and
 // nothing allocated) for a format without records or without device memory
 // for them: the sweeps then read the link fields
 bool ensure_rec(lgf_ensemble *e, int fmt)
 {
-    if (!lgf::fixed_records_format(fmt)) return false;
+    if (!lgf::fixed_records_format(fmt) || fixed_cached(e, fmt)) return false;
     if (e->rec[fmt]) return true;
     std::vector<size_t> off(e->n);
     size_t total = 0;
@@ -160,11 +173,12 @@ bool ensure_rec(lgf_ensemble *e, int fmt)
     return true;
 }
 
-// whether the fixed-link sweeps of the format pair (fa, fb) read per-site
-// records: both formats have them, and both are allocated
-bool fixed_on_records(const lgf_ensemble *e, int fa, int fb)
+// where the fixed-link sweeps of the format pair (fa, fb) get the links:
+// per-site records where both formats have them and both are allocated
+lgf::EnsLinks fixed_source(const lgf_ensemble *e, int fa, int fb)
 {
-    return lgf::ensemble_fixed_records_pair(fa, fb) && e->rec[fa] && e->rec[fb];
+    if (fixed_cached(e, fa)) return lgf::kEnsCached;
+    return (lgf::ensemble_fixed_records_pair(fa, fb) && e->rec[fa] && e->rec[fb]) ? lgf::kEnsRecords : lgf::kEnsStream;
 }
 
 lgf_status ensure_work(lgf_ensemble *e, int fmt)
@@ -201,6 +215,7 @@ uint32_t build_work(lgf_ensemble *e, const std::vector<int> &phase, const std::v
                     bool include_done, std::vector<int> &listed, int sites = 0, bool fixed = false)
 {
     uint32_t nt = 0;
+    std::vector<lgf::EnsTile> order(e->max_tiles);
     listed.clear();
     for (int i = 0; i < e->n; ++i) {
         e->h_cfgs[i].g = e->geom[i];
@@ -213,10 +228,13 @@ uint32_t build_work(lgf_ensemble *e, const std::vector<int> &phase, const std::v
         const uint32_t w = (uint32_t)(sites > 0 ? sites : e->tile);
         const uint32_t tiles = (e->geom[i].Vh + w - 1) / w;
         e->h_spans[listed.size()] = lgf::EnsSpan{(uint32_t)i, nt, tiles, (double)e->V[i]};
-        for (uint32_t t = 0; t < tiles; ++t) e->h_tiles[nt + t] = lgf::EnsTile{(uint32_t)i, t * w};
+        for (uint32_t t = 0; t < tiles; ++t) order[nt + t] = lgf::EnsTile{(uint32_t)i, t * w, nt + t, 0u};
         nt += tiles;
         listed.push_back(i);
     }
+    // workgroup b runs on XCD b % 8: neighbouring tiles share an XCD and its L2
+    for (uint32_t x = 0, k = 0; x < 8; ++x)
+        for (uint32_t b = x; b < nt; b += 8) e->h_tiles[b] = order[k++];
     *e->h_n_tiles = nt;
     return nt;
 }
@@ -233,7 +251,7 @@ lgf_status upload_work(lgf_ensemble *e, uint32_t nt, size_t n_spans)
 
 lgf::EnsLaunch launch_desc(lgf_ensemble *e, int fa, int fb, bool sr)
 {
-    return lgf::EnsLaunch{e->d_cfgs, e->d_tiles, e->d_n_tiles, e->d_sweep_base,
+    return lgf::EnsLaunch{e->d_cfgs, e->d_tiles, e->d_n_tiles, e->max_tiles, e->d_sweep_base,
                           (uint32_t)lgf::ensemble_persistent_grid(fa, fb, sr, e->nontemporal != 0, e->tile,
                                                                   e->grid_mult),
                           (uint32_t)e->tile};
@@ -299,7 +317,7 @@ lgf_status run_chunk(lgf_ensemble *e, int fa, int fb, int n, double omega, doubl
         (void)hipGraphExecDestroy(e->graphs.front().exec);
         e->graphs.erase(e->graphs.begin());
     }
-    e->graphs.push_back(EnsGraph{fa, fb, n, omega, p_sr, seed, nt, e->tile, e->grid_mult, fused, false, false, exec});
+    e->graphs.push_back(EnsGraph{fa, fb, n, omega, p_sr, seed, nt, e->tile, e->grid_mult, fused, false, lgf::kEnsStream, exec});
     LGF_HIP(hipGraphLaunch(exec, e->stream));
     return LGF_OK;
 }
@@ -339,9 +357,9 @@ lgf_status run_chunk_fixed(lgf_ensemble *e, int fa, int fb, int n, double omega,
     const bool sr = p_sr > 0.0;
     if (sr) LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep0, e->stream));
     const lgf::EnsRelax r = relax_args(omega, p_sr, seed);
-    const bool rec = fixed_on_records(e, fa, fb);
+    const lgf::EnsLinks src = fixed_source(e, fa, fb);
     lgf::EnsLaunch L = launch_desc(e, fa, fb, sr);
-    L.grid = (uint32_t)lgf::ensemble_fixed_grid(fa, fb, sr, e->tile, e->grid_mult, rec);
+    L.grid = (uint32_t)lgf::ensemble_fixed_grid(fa, fb, sr, e->tile, e->grid_mult, src);
     auto issue = [&]() -> hipError_t {
         hipError_t err = hipSuccess;
         for (int k = 0; k < n && err == hipSuccess; ++k)
@@ -349,7 +367,7 @@ lgf_status run_chunk_fixed(lgf_ensemble *e, int fa, int fb, int n, double omega,
                 const bool last = (k == n - 1);
                 const int post = last ? ((parity == 1 && fused) ? 2 : 1) : 0;
                 err = lgf::launch_ensemble_fixed_sweep(fa, fb, L, parity, r, (uint32_t)k, sr, post,
-                                                       post == 2 ? e->d_partials : nullptr, e->stream, rec);
+                                                       post == 2 ? e->d_partials : nullptr, e->stream, src);
             }
         return err;
     };
@@ -361,7 +379,7 @@ lgf_status run_chunk_fixed(lgf_ensemble *e, int fa, int fb, int n, double omega,
     for (auto &g : e->graphs)
         if (g.fa == fa && g.fb == fb && g.n_sweeps == n && g.omega == omega && g.p_sr == p_sr &&
             (!sr || g.seed == seed) && g.nt == nt && g.tile == e->tile && g.grid_mult == e->grid_mult &&
-            g.fused == fused && g.fixed && g.rec == rec) {
+            g.fused == fused && g.fixed && g.src == src) {
             LGF_HIP(hipGraphLaunch(g.exec, e->stream));
             return LGF_OK;
         }
@@ -381,7 +399,7 @@ lgf_status run_chunk_fixed(lgf_ensemble *e, int fa, int fb, int n, double omega,
         (void)hipGraphExecDestroy(e->graphs.front().exec);
         e->graphs.erase(e->graphs.begin());
     }
-    e->graphs.push_back(EnsGraph{fa, fb, n, omega, p_sr, seed, nt, e->tile, e->grid_mult, fused, true, rec, exec});
+    e->graphs.push_back(EnsGraph{fa, fb, n, omega, p_sr, seed, nt, e->tile, e->grid_mult, fused, true, src, exec});
     LGF_HIP(hipGraphLaunch(exec, e->stream));
     return LGF_OK;
 }
@@ -394,10 +412,10 @@ lgf_status measure_listed_fixed(lgf_ensemble *e, int fa, int fb, uint32_t nt, co
 {
     if (nt == 0) return LGF_OK;
     const lgf::EnsLaunch L = launch_desc(e, fa, fb, false);
-    const bool rec = fixed_on_records(e, fa, fb);
-    LGF_HIP(lgf::launch_ensemble_fixed_measure(fa, fb, L, nt, 0, e->d_partials, e->stream, rec));
+    const lgf::EnsLinks src = fixed_source(e, fa, fb);
+    LGF_HIP(lgf::launch_ensemble_fixed_measure(fa, fb, L, nt, 0, e->d_partials, e->stream, src));
     if (!fused)
-        LGF_HIP(lgf::launch_ensemble_fixed_measure(fa, fb, L, nt, 1, e->d_partials + 2 * (size_t)nt, e->stream, rec));
+        LGF_HIP(lgf::launch_ensemble_fixed_measure(fa, fb, L, nt, 1, e->d_partials + 2 * (size_t)nt, e->stream, src));
     LGF_HIP(lgf::launch_ensemble_finish(e->d_partials, nt, e->d_spans, (uint32_t)listed.size(), e->h_out, e->stream));
     return LGF_OK;
 }

@@ -18,6 +18,19 @@
 
 namespace lgf {
 
+// The first tile of a workgroup and the number of tiles listed, in one memory
+// latency: at a few microseconds per launch the chain of loads before the first
+// link (tile count, tile, configuration, links) counts.  Entries beyond the
+// list are read but not used.
+__device__ __forceinline__ EnsTile first_tile(const EnsTile *__restrict__ tiles, uint32_t max_tiles,
+                                              const uint32_t *__restrict__ n_tiles, uint32_t &n)
+{
+    EnsTile w = tiles[blockIdx.x < max_tiles ? blockIdx.x : max_tiles - 1u];
+    n = *n_tiles;
+    asm volatile("" : "+s"(w.cfg), "+s"(w.h0), "+s"(w.slot), "+s"(n));
+    return w;
+}
+
 template <int F, bool SR, bool NT, bool MEAS>
 __device__ __forceinline__ void ensemble_site(const EnsCfg &c, int parity, uint32_t h, bool active,
                                               const EnsRelax &r, uint32_t sweep, MeasAcc *acc)
@@ -28,21 +41,21 @@ __device__ __forceinline__ void ensemble_site(const EnsCfg &c, int parity, uint3
 }
 
 // FA, FB: the (at most two) storage formats the launch may meet.  MEAS: the
-// links are reunitarized as they are written and each tile t leaves its
-// sites' (F, theta) sums in partials[2 (n + t)], the second-pass slots of the
+// links are reunitarized as they are written and each tile leaves its
+// sites' (F, theta) sums in partials[2 (n + slot)], the second-pass slots of the
 // ensemble measurement's layout (n = the listed tiles).
 template <int FA, int FB, bool SR, bool NT, bool MEAS = false>
 __global__ void __launch_bounds__(kEnsMaxTile) ensemble_sweep_kernel(const EnsCfg *__restrict__ cfgs,
                                                                    const EnsTile *__restrict__ tiles,
-                                                                   const uint32_t *__restrict__ n_tiles,
+                                                                   const uint32_t *__restrict__ n_tiles, uint32_t max_tiles,
                                                                    const uint64_t *__restrict__ sweep_base,
                                                                    int parity, EnsRelax r, uint32_t sweep_offset,
                                                                    double *__restrict__ partials)
 {
-    const uint32_t n = *n_tiles;
+    uint32_t n;
+    EnsTile w = first_tile(tiles, max_tiles, n_tiles, n);
     const uint32_t sweep = (uint32_t)(*sweep_base + sweep_offset);
-    for (uint32_t t = blockIdx.x; t < n; t += gridDim.x) {
-        const EnsTile w = tiles[t];
+    for (uint32_t t = blockIdx.x; t < n;) {
         const EnsCfg c = cfgs[w.cfg];
         const uint32_t h0 = w.h0 + threadIdx.x;
         const bool active = h0 < c.g.Vh;
@@ -51,9 +64,11 @@ __global__ void __launch_bounds__(kEnsMaxTile) ensemble_sweep_kernel(const EnsCf
         if (c.fmt == FA) ensemble_site<FA, SR, NT, MEAS>(c, parity, h, active, r, sweep, &acc);
         else if (FB != FA && c.fmt == FB) ensemble_site<FB, SR, NT, MEAS>(c, parity, h, active, r, sweep, &acc);
         if constexpr (MEAS) {
-            block_sum2_any(acc.f, acc.th, partials + 2 * ((size_t)n + t));
+            block_sum2_any(acc.f, acc.th, partials + 2 * ((size_t)n + w.slot));
             __syncthreads();  // the block sum's shared slots are reused by the next tile
         }
+        t += gridDim.x;
+        if (t < n) w = tiles[t];
     }
 }
 
@@ -71,7 +86,7 @@ __global__ void __launch_bounds__(kEnsMaxTile) ensemble_measure_kernel(const Ens
     double f = 0.0, th = 0.0;
     if (c.fmt == FA) measure_site<FA>(as_global(c.field), c.g, parity, h, active, reunit_fwd, reunit_bwd, f, th);
     else if (FB != FA && c.fmt == FB) measure_site<FB>(as_global(c.field), c.g, parity, h, active, reunit_fwd, reunit_bwd, f, th);
-    block_sum2_any(f, th, partials + 2 * blockIdx.x);
+    block_sum2_any(f, th, partials + 2 * w.slot);
 }
 
 // One workgroup per listed configuration: the sums of its tiles' partials
@@ -102,42 +117,44 @@ __global__ void __launch_bounds__(256) ensemble_finish_kernel(const double *__re
 // transformation cfgs[].gf is updated (update_site_fixed, 2 lanes per site).
 // ----------------------------------------------------------------------------
 
-// REC: the links come from the configuration's per-site records
-template <int F, bool SR, int POST, bool REC>
+template <int F, bool SR, int POST, EnsLinks SRC>
 __device__ __forceinline__ void ensemble_site_fixed(const EnsCfg &c, int parity, uint32_t h, int lane, bool active,
                                                     const EnsRelax &r, uint32_t sweep, MeasAcc *acc)
 {
     using T = typename Fmt<F>::T;
     const RelaxArgs<T> a{(T)r.omega, r.overrelax, r.sr_threshold, r.key0, r.key1, sweep, c.instance};
-    update_site_fixed<F, kEnsFixedLanes, SR, POST, 0, REC>(as_global(REC ? c.rec : c.field), as_global(c.gf), c.g,
-                                                          parity, h, lane, active, a, acc);
+    constexpr bool REC = SRC == kEnsRecords;
+    update_site_fixed<F, kEnsFixedLanes, SR, POST, 0, REC, false, SRC == kEnsCached>(
+        as_global(REC ? c.rec : c.field), as_global(c.gf), c.g, parity, h, lane, active, a, acc);
 }
 
-template <int FA, int FB, bool SR, int POST, bool REC>
+template <int FA, int FB, bool SR, int POST, EnsLinks SRC>
 __global__ void __launch_bounds__(kEnsMaxTile) ensemble_fixed_kernel(const EnsCfg *__restrict__ cfgs,
                                                                    const EnsTile *__restrict__ tiles,
-                                                                   const uint32_t *__restrict__ n_tiles,
+                                                                   const uint32_t *__restrict__ n_tiles, uint32_t max_tiles,
                                                                    const uint64_t *__restrict__ sweep_base,
                                                                    int parity, EnsRelax r, uint32_t sweep_offset,
                                                                    double *__restrict__ partials)
 {
-    const uint32_t n = *n_tiles;
+    uint32_t n;
+    EnsTile w = first_tile(tiles, max_tiles, n_tiles, n);
     const uint32_t sweep = (uint32_t)(*sweep_base + sweep_offset);
     const int lane = (int)(threadIdx.x % kEnsFixedLanes);
-    for (uint32_t t = blockIdx.x; t < n; t += gridDim.x) {
-        const EnsTile w = tiles[t];
+    for (uint32_t t = blockIdx.x; t < n;) {
         const EnsCfg c = cfgs[w.cfg];
         const uint32_t h0 = w.h0 + threadIdx.x / kEnsFixedLanes;
         const bool active = h0 < c.g.Vh;
         const uint32_t h = active ? h0 : c.g.Vh - 1;
         MeasAcc acc;
-        if (c.fmt == FA) ensemble_site_fixed<FA, SR, POST, REC>(c, parity, h, lane, active, r, sweep, &acc);
+        if (c.fmt == FA) ensemble_site_fixed<FA, SR, POST, SRC>(c, parity, h, lane, active, r, sweep, &acc);
         else if (FB != FA && c.fmt == FB)
-            ensemble_site_fixed<FB, SR, POST, REC>(c, parity, h, lane, active, r, sweep, &acc);
+            ensemble_site_fixed<FB, SR, POST, SRC>(c, parity, h, lane, active, r, sweep, &acc);
         if constexpr (POST == 2) {
-            block_sum2_any(acc.f, acc.th, partials + 2 * ((size_t)n + t));
+            block_sum2_any(acc.f, acc.th, partials + 2 * ((size_t)n + w.slot));
             __syncthreads();  // the block sum's shared slots are reused by the next tile
         }
+        t += gridDim.x;
+        if (t < n) w = tiles[t];
     }
 }
 
@@ -157,7 +174,7 @@ __global__ void __launch_bounds__(kEnsMaxTile) ensemble_fixed_measure_kernel(con
     if (c.fmt == FA) measure_site_fixed<FA, kEnsFixedLanes, 0, REC>(links, as_global(c.gf), c.g, parity, h, lane, active, f, th);
     else if (FB != FA && c.fmt == FB)
         measure_site_fixed<FB, kEnsFixedLanes, 0, REC>(links, as_global(c.gf), c.g, parity, h, lane, active, f, th);
-    block_sum2_any(f, th, partials + 2 * blockIdx.x);
+    block_sum2_any(f, th, partials + 2 * w.slot);
 }
 
 // ----------------------------------------------------------------------------
@@ -178,13 +195,13 @@ static hipError_t launch_ens_sweep_t(const EnsLaunch &L, int parity, const EnsRe
     if (meas) {
         // the fused measurement: overrelaxation with non-temporal access only
         if (sr || !nt) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, false, true, true>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.sweep_base, parity, r, sweep_offset, meas);
+        hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, false, true, true>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.max_tiles, L.sweep_base, parity, r, sweep_offset, meas);
     } else if (sr) {
-        if (nt) hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, true, true>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
-        else hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, true, false>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
+        if (nt) hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, true, true>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.max_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
+        else hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, true, false>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.max_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
     } else {
-        if (nt) hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, false, true>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
-        else hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, false, false>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
+        if (nt) hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, false, true>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.max_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
+        else hipLaunchKernelGGL((ensemble_sweep_kernel<FA, FB, false, false>), grid, block, 0, s, L.cfgs, L.tiles, L.n_tiles, L.max_tiles, L.sweep_base, parity, r, sweep_offset, nullptr);
     }
     return hipGetLastError();
 }
@@ -262,14 +279,14 @@ bool ensemble_fixed_records_pair(int fa, int fb)
     return ensemble_fixed_pair(fa, fb) && has_records(fa) && has_records(fb);
 }
 
-template <int FA, int FB, bool REC>
+template <int FA, int FB, EnsLinks SRC>
 static hipError_t launch_ens_fixed_r(const EnsLaunch &L, int parity, const EnsRelax &r, uint32_t sweep_offset,
                                      bool sr, int post, double *meas, hipStream_t s)
 {
     const dim3 grid(L.grid), block(L.tile);
 #define LGF_EF(SRV, P)                                                                                          \
-    hipLaunchKernelGGL((ensemble_fixed_kernel<FA, FB, SRV, P, REC>), grid, block, 0, s, L.cfgs, L.tiles,         \
-                       L.n_tiles, L.sweep_base, parity, r, sweep_offset, meas)
+    hipLaunchKernelGGL((ensemble_fixed_kernel<FA, FB, SRV, P, SRC>), grid, block, 0, s, L.cfgs, L.tiles,         \
+                       L.n_tiles, L.max_tiles, L.sweep_base, parity, r, sweep_offset, meas)
     if (post == 2 && !meas) return hipErrorInvalidValue;
     if (sr) {
         if (post == 0) LGF_EF(true, 0);
@@ -286,25 +303,27 @@ static hipError_t launch_ens_fixed_r(const EnsLaunch &L, int parity, const EnsRe
 
 template <int FA, int FB>
 static hipError_t launch_ens_fixed_t(const EnsLaunch &L, int parity, const EnsRelax &r, uint32_t sweep_offset,
-                                     bool sr, int post, double *meas, hipStream_t s, bool rec)
+                                     bool sr, int post, double *meas, hipStream_t s, EnsLinks src)
 {
-    if (rec) {
+    if (src == kEnsCached)
+        return launch_ens_fixed_r<FA, FB, kEnsCached>(L, parity, r, sweep_offset, sr, post, meas, s);
+    if (src == kEnsRecords) {
         if constexpr (kRecPair<FA, FB>)
-            return launch_ens_fixed_r<FA, FB, true>(L, parity, r, sweep_offset, sr, post, meas, s);
+            return launch_ens_fixed_r<FA, FB, kEnsRecords>(L, parity, r, sweep_offset, sr, post, meas, s);
         else
             return hipErrorInvalidValue;
     }
-    return launch_ens_fixed_r<FA, FB, false>(L, parity, r, sweep_offset, sr, post, meas, s);
+    return launch_ens_fixed_r<FA, FB, kEnsStream>(L, parity, r, sweep_offset, sr, post, meas, s);
 }
 
 hipError_t launch_ensemble_fixed_sweep(int fa, int fb, const EnsLaunch &L, int parity, const EnsRelax &r,
                                        uint32_t sweep_offset, bool sr, int post, double *meas, hipStream_t s,
-                                       bool rec)
+                                       EnsLinks src)
 {
     if (post < 0 || post > 2 || L.tile % 64 != 0) return hipErrorInvalidValue;
     if (fa > fb) { const int t = fa; fa = fb; fb = t; }
 #define LGF_CASE(A, B)                                                                                       \
-    if (fa == A && fb == B) return launch_ens_fixed_t<A, B>(L, parity, r, sweep_offset, sr, post, meas, s, rec);
+    if (fa == A && fb == B) return launch_ens_fixed_t<A, B>(L, parity, r, sweep_offset, sr, post, meas, s, src);
     LGF_ENS_FIXED_PAIRS(LGF_CASE)
 #undef LGF_CASE
     return hipErrorInvalidValue;
@@ -312,9 +331,9 @@ hipError_t launch_ensemble_fixed_sweep(int fa, int fb, const EnsLaunch &L, int p
 
 template <int FA, int FB>
 static hipError_t launch_ens_fixed_measure_t(const EnsLaunch &L, uint32_t n_tiles, int parity, double *partials,
-                                             hipStream_t s, bool rec)
+                                             hipStream_t s, EnsLinks src)
 {
-    if (rec) {
+    if (src == kEnsRecords) {
         if constexpr (kRecPair<FA, FB>)
             hipLaunchKernelGGL((ensemble_fixed_measure_kernel<FA, FB, true>), dim3(n_tiles), dim3(L.tile), 0, s,
                                L.cfgs, L.tiles, parity, partials);
@@ -328,34 +347,39 @@ static hipError_t launch_ens_fixed_measure_t(const EnsLaunch &L, uint32_t n_tile
 }
 
 hipError_t launch_ensemble_fixed_measure(int fa, int fb, const EnsLaunch &L, uint32_t n_tiles, int parity,
-                                         double *partials, hipStream_t s, bool rec)
+                                         double *partials, hipStream_t s, EnsLinks src)
 {
     if (n_tiles == 0) return hipSuccess;
     if (fa > fb) { const int t = fa; fa = fb; fb = t; }
 #define LGF_CASE(A, B) \
-    if (fa == A && fb == B) return launch_ens_fixed_measure_t<A, B>(L, n_tiles, parity, partials, s, rec);
+    if (fa == A && fb == B) return launch_ens_fixed_measure_t<A, B>(L, n_tiles, parity, partials, s, src);
     LGF_ENS_FIXED_PAIRS(LGF_CASE)
 #undef LGF_CASE
     return hipErrorInvalidValue;
 }
 
-template <int FA, int FB>
-static const void *fixed_symbol(bool sr, bool rec)
+template <int FA, int FB, EnsLinks SRC>
+static const void *fixed_symbol_of(bool sr)
 {
-    if constexpr (kRecPair<FA, FB>)
-        if (rec)
-            return sr ? reinterpret_cast<const void *>(&ensemble_fixed_kernel<FA, FB, true, 0, true>)
-                      : reinterpret_cast<const void *>(&ensemble_fixed_kernel<FA, FB, false, 0, true>);
-    return sr ? reinterpret_cast<const void *>(&ensemble_fixed_kernel<FA, FB, true, 0, false>)
-              : reinterpret_cast<const void *>(&ensemble_fixed_kernel<FA, FB, false, 0, false>);
+    return sr ? reinterpret_cast<const void *>(&ensemble_fixed_kernel<FA, FB, true, 0, SRC>)
+              : reinterpret_cast<const void *>(&ensemble_fixed_kernel<FA, FB, false, 0, SRC>);
 }
 
-int ensemble_fixed_grid(int fa, int fb, bool sr, int tile, int grid_mult, bool rec)
+template <int FA, int FB>
+static const void *fixed_symbol(bool sr, EnsLinks src)
+{
+    if (src == kEnsCached) return fixed_symbol_of<FA, FB, kEnsCached>(sr);
+    if constexpr (kRecPair<FA, FB>)
+        if (src == kEnsRecords) return fixed_symbol_of<FA, FB, kEnsRecords>(sr);
+    return fixed_symbol_of<FA, FB, kEnsStream>(sr);
+}
+
+int ensemble_fixed_grid(int fa, int fb, bool sr, int tile, int grid_mult, EnsLinks src)
 {
     if (fa > fb) { const int t = fa; fa = fb; fb = t; }
     const void *fn = nullptr;
 #define LGF_CASE(A, B) \
-    if (fa == A && fb == B) fn = fixed_symbol<A, B>(sr, rec);
+    if (fa == A && fb == B) fn = fixed_symbol<A, B>(sr, src);
     LGF_ENS_FIXED_PAIRS(LGF_CASE)
 #undef LGF_CASE
     int dev = 0, cus = 256, per_cu = 1;
