@@ -18,14 +18,11 @@
 // The heat-bath arithmetic is FP64 and the kernel is instantiated for the FP64
 // storage formats only: its accept-reject decisions must be the ones an FP64
 // computation takes.  Like the relaxation sweep the update reads and writes
-// the 8 links of a site once (HBM bound for the links; the transcendental
-// functions of 1-2 trials per subgroup add ~20 % arithmetic).  The heat bath
-// is the arithmetic of a whole site, so every lane that shares a site repeats
-// it: on FP64-12 links one lane holds all 8 links of its site (96 VGPRs of
-// rows 0 and 1; the kernel runs one wave per SIMD with part of its state in
-// the accumulation registers) and the heat bath is paid once per site, 1.4-1.5x
-// faster than two lanes per site; the 8 FP64-18 links do not fit one lane, so
-// that format keeps two lanes per site, each holding two directions.
+// the 8 links of a site once.  The heat bath is the arithmetic of a whole site,
+// so every lane that shares a site repeats it: on FP64-12 links one lane holds
+// all 8 links of its site and the heat bath is paid once per site (two lanes
+// take 84 against 59 us at 24^4); the 8 FP64-18 links do not fit one lane, so that
+// format has two lanes per site, each holding two directions.
 #include <type_traits>
 
 #include "lgf_device.hpp"
@@ -38,7 +35,6 @@ namespace {
 
 constexpr uint32_t kSaTrials = 64;
 constexpr double kSaSwitch = 0.7;
-constexpr double kTwoPi = 2.0 * 3.14159265358979323846;
 
 __device__ __forceinline__ double unit_uniform(uint32_t w) { return ((double)w + 0.5) * 0x1p-32; }
 
@@ -59,7 +55,7 @@ __device__ __forceinline__ uint32_t heatbath_x0(double alpha, const SaKey &key, 
             // lambda^2 = l ~ Gamma(3/2, rate 2 alpha), accepted with
             // probability sqrt(1 - l); x0 = 1 - 2 l
             const double u3 = unit_uniform(w.z), u4 = unit_uniform(w.w);
-            const double c = cos(kTwoPi * u2);
+            const double c = cospi(2.0 * u2);
             const double l = -(log(u1) + c * c * log(u3)) / (2.0 * alpha);
             if (u4 * u4 <= 1.0 - l) {
                 x0 = 1.0 - 2.0 * l;
@@ -99,10 +95,11 @@ __device__ __forceinline__ uint32_t heatbath_step(mat3<double> &W, mat3<double> 
     const uint4 v = philox4x32_10(make_uint4(key.site, key.sweep, key.instance, sa_tag(K_IDX, 0xFFFFu)), key.k0,
                                   key.k1);
     const double ct = 2.0 * unit_uniform(v.x) - 1.0;
-    const double phi = kTwoPi * unit_uniform(v.y);
+    double sphi, cphi;
+    sincospi(2.0 * unit_uniform(v.y), &sphi, &cphi);  // of 2 pi u: 2 u is exact
     const double st = sqrt(1.0 - ct * ct);
     const double rad = sqrt(fmax(0.0, 1.0 - x0 * x0));
-    const double x1 = rad * st * cos(phi), x2 = rad * st * sin(phi), x3 = rad * ct;
+    const double x1 = rad * st * cphi, x2 = rad * st * sphi, x3 = rad * ct;
     // r = x b as quaternions: s(r) = s(x) s(b)
     const double r0 = x0 * b0 - (x1 * b1 + x2 * b2 + x3 * b3);
     const double r1 = x0 * b1 + b0 * x1 - (x2 * b3 - x3 * b2);
@@ -126,7 +123,34 @@ __device__ __forceinline__ uint32_t heatbath_step(mat3<double> &W, mat3<double> 
 
 // lanes per site: 1 on FP64-12 links, 2 on FP64-18 links
 template <int F> constexpr int sa_lanes() { return F == kF64_12 ? 1 : 2; }
-constexpr int kSaBlock = 128;  // lanes per workgroup
+constexpr int kSaBlock = 64;  // lanes per workgroup
+// waves per SIMD: the links of FP64-12 on one lane spill at two (24^4 72 us against 59)
+template <int F> constexpr int sa_waves() { return F == kF64_12 ? 1 : 2; }
+
+// The rows of a link that its storage holds, kept in LDS over the heat bath: one
+// slot per link, 16 bytes per lane in a row.
+template <int R>
+__device__ __forceinline__ void stash(double2 *slot, const mat3<double> &u)
+{
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            slot[(3 * i + j) * kSaBlock + threadIdx.x] = make_double2(u.e[i][j].re, u.e[i][j].im);
+}
+
+template <int R>
+__device__ __forceinline__ void fetch(mat3<double> &u, const double2 *slot)
+{
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double2 v = slot[(3 * i + j) * kSaBlock + threadIdx.x];
+            u.e[i][j] = {v.x, v.y};
+        }
+    if constexpr (R == 2) rebuild_row2(u);
+}
 
 // One annealing half-sweep over the sites of one parity, LANES lanes per site
 // (lane l gathers and stores directions l, l + LANES, ...).  With two lanes
@@ -134,36 +158,66 @@ constexpr int kSaBlock = 128;  // lanes per workgroup
 // so they hold the same G.  trials (may be NULL) accumulates the
 // accept-reject trials of the launch: a wave sum, then one 64-bit atomic add
 // per wave.
-template <int F>
-__global__ void __launch_bounds__(kSaBlock) anneal_kernel(void *__restrict__ field, Geom g, int parity, double temp,
+//
+// A wave is one long chain of FP64 instructions (logarithms, a cosine, square
+// roots and divisions per trial), so what bounds the launch is how many of them
+// there are and how many waves a SIMD can alternate between.  The links that only
+// come back after the heat bath wait in LDS (18 KB per wave, 8 waves in a CU's
+// 160 KB): FP64-18 runs two waves per SIMD instead of one, FP64-12 keeps 328
+// registers instead of 498.  cospi(2 u) instead of cos(2 pi u) saves the
+// reduction of a general argument, a quarter of the kernel's instructions.  NT and
+// order are those of the relaxation sweep's launches.  Per launch at T = 0.05 and
+// 2: 24^4 FP64-12 68 -> 59 and 94 -> 83 us, FP64-18 103 -> 91 and 142 -> 102;
+// 32^4 FP64-12 178 -> 151 and 234 -> 204.
+template <int F, int NT>
+__global__ void __launch_bounds__(kSaBlock, sa_waves<F>()) anneal_kernel(void *__restrict__ field, Geom g, int parity, double temp,
                                                           uint32_t sweep, uint32_t instance, uint32_t k0, uint32_t k1,
+                                                          int order, uint32_t n_groups,
                                                           unsigned long long *__restrict__ trials)
 {
     static_assert(std::is_same<typename Fmt<F>::T, double>::value, "the heat bath runs on FP64 links");
     using S = Fmt<F>;
     constexpr int LANES = sa_lanes<F>();
     constexpr int NL = 4 / LANES;
-    // Vh <= 2^30, so blockIdx * blockDim + lane < 2^32
-    const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int FIRST = NL == 4 ? 1 : 0;  // forward links FIRST, FIRST + 1, ... are in LDS
+    __shared__ double2 held[(NL - FIRST) * 3 * S::R * kSaBlock];
+    const uint32_t b = launch_place(blockIdx.x, gridDim.x, order);
+    if (b >= n_groups) return;  // the whole workgroup
+    // Vh <= 2^30, so block * lanes < 2^32
+    const uint32_t tid = b * kSaBlock + threadIdx.x;
     const uint32_t grp = tid / LANES;
     const int lane = (int)(tid % LANES);
     const bool active = grp < g.Vh;
     const uint32_t h = active ? grp : g.Vh - 1;
     const Site c = decode(g, parity, h);
 
-    mat3<double> uf[NL], ub[NL];
+    mat3<double> uf[NL], ub[NL];  // the stored rows; row 2 of a 12-real link is rebuilt where it is used
     uint32_t hb[NL];
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
         const int mu = lane + k * LANES;
+        load_link<F, NT == kStream, false>(uf[k], block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
+        if (k >= FIRST) stash<S::R>(held + (k - FIRST) * 3 * S::R * kSaBlock, uf[k]);
+    }
+    // a lane reads only what it wrote: no barrier, but no forwarding in registers either
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int mu = lane + k * LANES;
         hb[k] = back_half(g, c, h, mu);
-        load_link<F, true>(uf[k], block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
-        load_link<F, true>(ub[k], block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, hb[k]);
+        load_link<F, NT == kStream, false>(ub[k], block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, hb[k]);
     }
     mat3<double> K;
     set_zero(K);
 #pragma unroll
-    for (int k = 0; k < NL; ++k) add_fwd_bwd(K, uf[k], ub[k]);
+    for (int k = 0; k < NL; ++k) {
+        mat3<double> u = uf[k], v = ub[k];
+        if (k >= FIRST) fetch<S::R>(u, held + (k - FIRST) * 3 * S::R * kSaBlock);
+        else if constexpr (S::R == 2) rebuild_row2(u);
+        if constexpr (S::R == 2) rebuild_row2(v);
+        add_fwd_bwd(K, u, v);
+        asm volatile("" ::: "memory");
+    }
     lane_sum<LANES>(K);
 
     const SaKey key{lex_index(g, c), sweep, instance, k0, k1};
@@ -173,15 +227,25 @@ __global__ void __launch_bounds__(kSaBlock) anneal_kernel(void *__restrict__ fie
     n += heatbath_step<0, 2, 1, true>(K, G, temp, key);
     n += heatbath_step<1, 2, 2, false>(K, G, temp, key);
 
+    uint32_t hs = h;
+    forget(hs);
     if (active) {
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
             const int mu = lane + k * LANES;
-            mat3<double> r, rb;
-            left_mul<S::R>(r, G, uf[k]);
+            mat3<double> u, r, rb;
+            forget(hb[k]);
+            if (k >= FIRST) {
+                fetch<S::R>(u, held + (k - FIRST) * 3 * S::R * kSaBlock);
+            } else {
+                u = uf[k];
+                if constexpr (S::R == 2) rebuild_row2(u);
+            }
+            left_mul<S::R>(r, G, u);
             right_mul_dag<S::R>(rb, ub[k], G);
-            store_link<F, true>(block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h, r);
-            store_link<F, true>(block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, hb[k], rb);
+            store_link<F, NT != kCached>(block_ptr<F>(field, g.Vh, parity, mu), g.Vh, hs, r);
+            store_link<F, NT != kCached>(block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, hb[k], rb);
+            asm volatile("" ::: "memory");
         }
     }
     if (trials) {
@@ -194,24 +258,35 @@ __global__ void __launch_bounds__(kSaBlock) anneal_kernel(void *__restrict__ fie
 
 template <int F>
 hipError_t launch_anneal_f(void *field, const Geom &g, int parity, double temp, uint64_t seed, uint64_t sweep,
-                           uint32_t instance, unsigned long long *trials, hipStream_t s)
+                           uint32_t instance, unsigned long long *trials, const SweepTuning &t, hipStream_t s)
 {
     const uint64_t threads = (uint64_t)g.Vh * sa_lanes<F>();
-    const uint32_t nb = (uint32_t)((threads + kSaBlock - 1) / kSaBlock);
-    hipLaunchKernelGGL((anneal_kernel<F>), dim3(nb), dim3(kSaBlock), 0, s, field, g, parity, temp, (uint32_t)sweep,
-                       instance, (uint32_t)seed, (uint32_t)(seed >> 32), trials);
+    const uint32_t ng = (uint32_t)((threads + kSaBlock - 1) / kSaBlock);
+    const int order = launch_order(t, parity);
+    const dim3 grid((order & kXcdRanges) ? (ng + 7u) / 8u * 8u : ng), block(kSaBlock);
+#define LGF_SA(NT)                                                                                                    \
+    hipLaunchKernelGGL((anneal_kernel<F, NT>), grid, block, 0, s, field, g, parity, temp, (uint32_t)sweep, instance,  \
+                       (uint32_t)seed, (uint32_t)(seed >> 32), order, ng, trials)
+    switch (t.nontemporal) {
+    case kCached: LGF_SA(kCached); break;
+    case kStream: LGF_SA(kStream); break;
+    case kStreamStores: LGF_SA(kStreamStores); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef LGF_SA
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_anneal(int format, void *field, const Geom &g, int parity, double temp, uint64_t seed,
-                         uint64_t sweep, uint32_t instance, unsigned long long *trials, hipStream_t s)
+                         uint64_t sweep, uint32_t instance, unsigned long long *trials, const SweepTuning &t,
+                         hipStream_t s)
 {
     if (!(temp > 0.0)) return hipErrorInvalidValue;
     switch (format) {
-    case kF64_18: return launch_anneal_f<kF64_18>(field, g, parity, temp, seed, sweep, instance, trials, s);
-    case kF64_12: return launch_anneal_f<kF64_12>(field, g, parity, temp, seed, sweep, instance, trials, s);
+    case kF64_18: return launch_anneal_f<kF64_18>(field, g, parity, temp, seed, sweep, instance, trials, t, s);
+    case kF64_12: return launch_anneal_f<kF64_12>(field, g, parity, temp, seed, sweep, instance, trials, t, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1762,7 +1762,8 @@ lgf_status lgf_anneal_sweep(lgf_lattice *h, int parity, double T, uint64_t seed,
     if (ctr) LGF_HIP(lgf::launch_set_u64(reinterpret_cast<uint64_t *>(ctr), 0, h->stream));
     for (int p = 0; p < 2; ++p)
         if (parity == 2 || parity == p)
-            LGF_HIP(lgf::launch_anneal(h->format, h->field, h->geom, p, T, seed, sweep_index, 0u, ctr, h->stream));
+            LGF_HIP(lgf::launch_anneal(h->format, h->field, h->geom, p, T, seed, sweep_index, 0u, ctr,
+                                       launch_tuning(h, h->format), h->stream));
     if (trials) LGF_TRY(read_trials(h, trials));
     return LGF_OK;
 }
@@ -1782,7 +1783,7 @@ lgf_status lgf_anneal(lgf_lattice *h, int64_t n_sweeps, double T_start, double T
         const double T = anneal_temperature(n, n_sweeps, T_start, T_end);
         for (int p = 0; p < 2; ++p)
             LGF_HIP(lgf::launch_anneal(h->format, h->field, h->geom, p, T, seed, sweep0 + (uint64_t)n, 0u,
-                                       h->d_trials, h->stream));
+                                       h->d_trials, launch_tuning(h, h->format), h->stream));
         if ((n + 1) % 20 == 0 || n + 1 == n_sweeps)
             LGF_HIP(lgf::launch_convert(h->format, h->field, h->format, h->field, h->geom, true, h->stream));
     }

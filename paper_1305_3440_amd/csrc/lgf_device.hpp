@@ -469,6 +469,16 @@ __device__ __forceinline__ uint32_t backwards(uint32_t b, uint32_t n)
     return (n & 7u) ? n - 1u - b : n - 8u - (b & ~7u) + (b & 7u);
 }
 
+// The order of a link sweep's workgroups: contiguous ranges per XCD (the grid a
+// multiple of 8); from the end of the lattice (the odd half-sweep, which then
+// starts on what the even one read last).
+constexpr int kXcdRanges = 1, kBackward = 2;
+__device__ __forceinline__ uint32_t launch_place(uint32_t b, uint32_t n, int order)
+{
+    if (order & kBackward) b = backwards(b, n);
+    return (order & kXcdRanges) ? (b & 7u) * (n >> 3) + (b >> 3) : b;
+}
+
 // Runs for n items over the lattice g whose sites take site_bytes each (0 for
 // items that share nothing across t), and the grid they need (items at n and beyond are to be left out by the kernel).  One
 // run per XCD while the 8 t-slices that are then read at a time stay in the

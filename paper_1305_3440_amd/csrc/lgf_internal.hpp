@@ -26,6 +26,12 @@ struct SweepTuning {
     int backward = 0;  // link form: the odd half-sweep walks the lattice from its end
 };
 
+// the order of a link sweep's workgroups (kXcdRanges, kBackward)
+inline int launch_order(const SweepTuning &t, int parity)
+{
+    return (t.xcd_remap ? kXcdRanges : 0) | (t.backward && parity ? kBackward : 0);
+}
+
 constexpr int kScheduleInPlace = 0, kSchedulePipeline = 1, kScheduleOutOfPlace = 2;
 // the fixed-link sweep's `schedule`: layout of the links it reads
 constexpr int kLayoutPlanes = 0, kLayoutRecords = 1;
@@ -168,8 +174,10 @@ hipError_t launch_split_links(int fs, const void *src, void *dst, const Geom &g,
 
 // Simulated annealing: one heat-bath half-sweep of the link-rewriting form at
 // temperature temp > 0 (FP64 formats only).  trials (device counter, may be
-// NULL) accumulates the accept-reject trials of the launch.
+// NULL) accumulates the accept-reject trials of the launch.  Of the tuning:
+// xcd_remap, nontemporal, backward.
 hipError_t launch_anneal(int format, void *field, const Geom &g, int parity, double temp, uint64_t seed,
-                         uint64_t sweep, uint32_t instance, unsigned long long *trials, hipStream_t s);
+                         uint64_t sweep, uint32_t instance, unsigned long long *trials, const SweepTuning &t,
+                         hipStream_t s);
 
 }  // namespace lgf

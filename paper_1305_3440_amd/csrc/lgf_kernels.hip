@@ -33,14 +33,6 @@ size_t link_bytes(int format)
 // Relaxation sweep
 // ----------------------------------------------------------------------------
 
-// the order of a launch's workgroups: contiguous ranges per XCD; from the end of
-// the lattice (the odd half-sweep, which then starts on what the even one read last)
-constexpr int kXcdRanges = 1, kBackward = 2;
-static int launch_order(const SweepTuning &t, int parity)
-{
-    return (t.xcd_remap ? kXcdRanges : 0) | (t.backward && parity ? kBackward : 0);
-}
-
 // One half-sweep: the sites [h_begin, h_end) of one parity, LPS lanes per
 // site, cut into n_tiles tiles of blockDim.x lanes.  Workgroup b takes the
 // tiles b, b + n_groups, b + 2 n_groups, ... (spt of them at most), so the
@@ -59,15 +51,8 @@ __global__ void __launch_bounds__(256, (sweep_waves<F, LPS, SR>())) sweep_kernel
                                                      uint32_t h_begin, uint32_t h_end,
                                                      void *__restrict__ out_field, double *__restrict__ partials)
 {
-    uint32_t b = (order & kBackward) ? backwards(blockIdx.x, gridDim.x) : blockIdx.x;
-    if (order & kXcdRanges) {
-        // workgroups are dealt to the 8 XCDs round-robin; give XCD k the
-        // contiguous range [k*per, (k+1)*per) of workgroups so that
-        // neighbouring tiles share its L2
-        const uint32_t per = gridDim.x >> 3;
-        b = (b & 7u) * per + (b >> 3);
-        if (b >= n_groups) return;  // the whole workgroup: no partials slot
-    }
+    const uint32_t b = launch_place(blockIdx.x, gridDim.x, order);
+    if (b >= n_groups) return;  // the whole workgroup: no partials slot
     MeasAcc acc;
     auto one_tile = [&](uint32_t tile) {
         // Vh <= 2^30 and LPS <= 4, so tile * blockDim + lane < 2^32
@@ -663,12 +648,8 @@ __global__ void __launch_bounds__(256) sweep_coulomb_kernel(void *__restrict__ f
                                                             uint32_t n_groups,
                                                             const uint8_t *__restrict__ slice_active)
 {
-    uint32_t b = (order & kBackward) ? backwards(blockIdx.x, gridDim.x) : blockIdx.x;
-    if (order & kXcdRanges) {
-        // a contiguous range of workgroups per XCD, as in sweep_kernel
-        b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
-        if (b >= n_groups) return;
-    }
+    const uint32_t b = launch_place(blockIdx.x, gridDim.x, order);
+    if (b >= n_groups) return;
     const uint32_t tid = b * blockDim.x + threadIdx.x;
     const uint32_t h0 = tid / LPS;
     const bool active = h0 < g.Vh;

@@ -95,3 +95,24 @@ def test_normalisation_over_the_whole_range(lgf, scale):
     # one more rounding of 1 / |a| on either side of the estimate's range, amplified up to 40 times on
     # ill-conditioned sites, over two half-sweeps: 2 * 3 * 40 * 2^-52
     assert np.abs(got[1] - got[0]).max() <= 240 * 2.0 ** -52
+
+
+@pytest.mark.parametrize("dims,fmt", [((2, 2, 2, 2), 0), ((4, 4, 6, 10), 3), ((16, 16, 16, 14), 0), ((22, 14, 14, 18), 3),
+                                      ((34, 32, 30, 30), 0)])
+def test_annealing_does_not_depend_on_the_choice(lgf, dims, fmt):
+    """Untuned annealing launches (cached, streamed, stores streamed; XCD ranges; odd half-sweeps from the end) against
+    streamed launches in the plain order: the same links and trials."""
+    import torch
+    print(f"[gpu-case] choice anneal {dims} {fmt}", flush=True)
+    V = int(np.prod(dims))
+    out = []
+    for tuned in (False, True):
+        buf = torch.empty(V * 4 * lgf.lgf.LINK_BYTES[fmt] // 4, dtype=torch.float32, device="cuda")
+        with lgf.Lattice(dims, fmt, device_buf=buf) as lat:
+            if tuned:
+                lgf.lgf_set_tuning(lat.h, fmt, 1, 128, 0, 1, 0, 1)
+            lat.generate(5, 0.3)
+            trials = [lat.anneal_sweep(2, T, 8, 3) for T in (0.05, 3.0)]
+            lgf.lgf_synchronize(lat.h)
+            out.append((buf.clone().view(torch.int32), trials))
+    assert torch.equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
