@@ -777,8 +777,9 @@ bool fixed_records(const lgf_lattice *h, int format)
 lgf_status build_records(lgf_lattice *h, int format, bool *built)
 {
     *built = false;
-    void *planes = nullptr;
-    LGF_TRY(links_in_format(h, format, &planes));
+    void *planes = h->field;
+    const bool direct = lgf::record_links_from(h->format, format);
+    if (!direct) LGF_TRY(links_in_format(h, format, &planes));
     if (!h->rec[format]) {
         const size_t bytes = lgf::record_links_bytes(format, h->geom);
         if (bytes == 0) return fail(LGF_EINVAL, "format %d has no per-site link records", format);
@@ -788,7 +789,7 @@ lgf_status build_records(lgf_lattice *h, int format, bool *built)
             return LGF_OK;
         }
     }
-    LGF_HIP(lgf::launch_record_links(format, planes, h->rec[format], h->geom, h->stream));
+    LGF_HIP(lgf::launch_record_links(direct ? h->format : format, format, planes, h->rec[format], h->geom, h->stream));
     *built = true;
     return LGF_OK;
 }

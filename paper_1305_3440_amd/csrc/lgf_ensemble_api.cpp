@@ -486,7 +486,7 @@ lgf_status fixed_links_to(lgf_ensemble *e, int i, int f)
                                         false, e->stream));
     }
     if (ensure_rec(e, f))
-        LGF_HIP(lgf::launch_record_links(f, field_of(e, f, i), rec_of(e, f, i), e->geom[i], e->stream));
+        LGF_HIP(lgf::launch_record_links(f, f, field_of(e, f, i), rec_of(e, f, i), e->geom[i], e->stream));
     return LGF_OK;
 }
 

@@ -409,28 +409,35 @@ hipError_t launch_site_convert(int fs, const void *src, int fd, void *dst, const
     }
 }
 
-// A link field of the 12-real format F (planes) into per-site link records:
-// one lane per (site, parity); the stores of a wavefront are contiguous.
-template <int F>
+// A link field (planes) of the 12-real format F, or of FP64-18 for FP64-12 (the
+// rows 0 and 1 of which it holds as they are), into per-site link records: one
+// lane per (site, parity); the stores of a wavefront are contiguous.  HBM bound:
+// the tiles of both parities go in runs per XCD, so that a link's second reading
+// comes from a cache.  64^4 FP64-12 from FP64-18 3.5 ms (22.5 GB), before by way
+// of an FP64-12 field, in the order of dispatch, 2.5 + 5.0 ms.
+template <int F, int FS>
 __global__ void __launch_bounds__(256) record_links_kernel(const void *__restrict__ src, void *__restrict__ rec,
-                                                           Geom g)
+                                                           Geom g, XcdRuns runs, uint32_t n_tiles)
 {
+    static_assert(F == FS || (F == kF64_12 && FS == kF64_18), "the source's first vectors are the record's");
     using V = typename Fmt<F>::V;
     constexpr int NV = Fmt<F>::NV;
-    const uint32_t h = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t item = xcd_item(blockIdx.x, runs);
+    if ((item >> 1) >= n_tiles) return;
+    const uint32_t h = (item >> 1) * 256 + threadIdx.x;
     if (h >= g.Vh) return;
-    const int parity = blockIdx.y;
+    const int parity = (int)(item & 1u);
     const Site c = decode(g, parity, h);
     void *L = const_cast<void *>(src);
     V *out = const_cast<V *>(rec_ptr<F>(rec, g.Vh, parity, 0, rec_pos<false>(h)));
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
-        const V *f = block_ptr<F>(L, g.Vh, parity, mu) + h;
-        const V *b = block_ptr<F>(L, g.Vh, parity ^ 1, mu) + back_half(g, c, h, mu);
+        const V *f = block_ptr<FS>(L, g.Vh, parity, mu) + h;
+        const V *b = block_ptr<FS>(L, g.Vh, parity ^ 1, mu) + back_half(g, c, h, mu);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
-            out[((size_t)mu * NV + k) * kRecTile] = f[(size_t)k * g.Vh];
-            out[((size_t)(4 + mu) * NV + k) * kRecTile] = b[(size_t)k * g.Vh];
+            vstore<true>(out + ((size_t)mu * NV + k) * kRecTile, f[(size_t)k * g.Vh]);
+            vstore<true>(out + ((size_t)(4 + mu) * NV + k) * kRecTile, b[(size_t)k * g.Vh]);
         }
     }
 }
@@ -474,13 +481,22 @@ size_t record_links_bytes(int format, const Geom &g)
     return (size_t)2 * rec_tiles(g.Vh) * kRecTile * 8 * link;
 }
 
-hipError_t launch_record_links(int format, const void *src, void *rec, const Geom &g, hipStream_t s)
+bool record_links_from(int fs, int format) { return fs == format || (fs == kF64_18 && format == kF64_12); }
+
+hipError_t launch_record_links(int fs, int format, const void *src, void *rec, const Geom &g, hipStream_t s)
 {
-    const dim3 grid((g.Vh + 255) / 256, 2), block(256);
+    if (!record_links_from(fs, format)) return hipErrorInvalidValue;
+    const uint32_t nt = (g.Vh + 255) / 256;
+    uint32_t ng = 0;
+    const XcdRuns runs = xcd_runs(2 * nt, g, 4 * link_bytes(fs), &ng);
+    const dim3 grid(ng), block(256);
     switch (format) {
-    case kF32_12: hipLaunchKernelGGL((record_links_kernel<kF32_12>), grid, block, 0, s, src, rec, g); break;
-    case kF64_12: hipLaunchKernelGGL((record_links_kernel<kF64_12>), grid, block, 0, s, src, rec, g); break;
-    case kF64_12S: hipLaunchKernelGGL(record_split_links_kernel, grid, block, 0, s, src, rec, g); break;
+    case kF32_12: hipLaunchKernelGGL((record_links_kernel<kF32_12, kF32_12>), grid, block, 0, s, src, rec, g, runs, nt); break;
+    case kF64_12:
+        if (fs == kF64_18) hipLaunchKernelGGL((record_links_kernel<kF64_12, kF64_18>), grid, block, 0, s, src, rec, g, runs, nt);
+        else hipLaunchKernelGGL((record_links_kernel<kF64_12, kF64_12>), grid, block, 0, s, src, rec, g, runs, nt);
+        break;
+    case kF64_12S: hipLaunchKernelGGL(record_split_links_kernel, dim3(nt, 2), block, 0, s, src, rec, g); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -149,7 +149,9 @@ bool fixed_one_lane_format(int format);
 // the per-site link records of a 12-real link field src (format, planes):
 // record_links_bytes(format, g) bytes at rec (0 for other formats)
 size_t record_links_bytes(int format, const Geom &g);
-hipError_t launch_record_links(int format, const void *src, void *rec, const Geom &g, hipStream_t s);
+// src in format fs, of those that record_links_from admits
+bool record_links_from(int fs, int format);
+hipError_t launch_record_links(int fs, int format, const void *src, void *rec, const Geom &g, hipStream_t s);
 // Coulomb gauge in the fixed-link form (post 0 or 1; slice_active: device
 // array of Lt flags)
 hipError_t launch_fixed_sweep_coulomb(int format, const void *links, void *gf, const Geom &g, const SweepArgs &a,
