@@ -108,9 +108,9 @@ typedef struct {
                               below theta_target, the sweeps go on in FP64-12 from the transformed
                               links (g restarting at 1) while max_sweeps allows.  FP64-12 and
                               LGF_FP64_12S may be paired as bulk and finish in either order.  In
-                              FP32-12, FP64-12 and LGF_FP64_12S the sweeps read the links from per-site records
-                              by default (an exact copy laid out for the access pattern; see
-                              lgf_set_fixed_tuning), built when the run starts and at the switch.
+                              FP32-12, FP64-12 and LGF_FP64_12S the sweeps of larger lattices read the links
+                              from per-site records by default (an exact copy laid out for the access
+                              pattern; see lgf_set_fixed_tuning), built when the run starts and at the switch.
                               0 (default): the sweeps rewrite the links. */
     int64_t max_sweeps;    /* give up after this many full sweeps (default 100000) */
     uint64_t seed;         /* key of the stochastic-relaxation Philox stream */
@@ -390,7 +390,8 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials);
  * lanes, 64-lane workgroups, order 2, layout 0; FP32-18 2 lanes, 256-lane
  * workgroups, order 0, layout 0.  Until a tuning is set or autotuned, launches on
  * lattices of up to 2 million sites choose workgroup, order 1 and lanes by the
- * size, with the same bits.  LGF_EINVAL on other values.  Setting a
+ * size, and while links and g take up to 400 MB read the link field, with the
+ * same bits.  LGF_EINVAL on other values.  Setting a
  * tuning closes an open stepwise session (lgf_fix_begin) without applying g. */
 lgf_status lgf_set_fixed_tuning(lgf_lattice *h, int format, const lgf_sweep_tuning *tuning);
 lgf_status lgf_get_fixed_tuning(const lgf_lattice *h, int format, lgf_sweep_tuning *tuning);
@@ -503,8 +504,8 @@ lgf_status lgf_ensemble_measure(lgf_ensemble *e, double *F, double *theta);
  * FP64-12 or FP64-12S, or one of them, or FP64-18 alone: LGF_EINVAL
  * otherwise; a configuration whose last sweeps ran in FP64-12S gets its F,
  * theta and status from one more measurement of its FP64 home links; in
- * FP32-12, FP64-12 and FP64-12S the launches read each configuration's links
- * from its per-site records (see lgf_set_fixed_tuning), built when its links
+ * FP32-12, FP64-12 and FP64-12S the launches of an ensemble of more than 400 MB
+ * of links and g read each configuration's links from its per-site records (see lgf_set_fixed_tuning), built when its links
  * are prepared in that format and kept, twice the links' size, until
  * lgf_ensemble_destroy; without device memory for them the link fields:
  * the same bits either way); accumulate_g is rejected. */
