@@ -175,8 +175,12 @@ lgf_status use_device(const lgf_lattice *h)
     return LGF_OK;
 }
 
+// Forget the captured chunks.  One of them may have been launched and not yet
+// waited for (the drivers wait once per check interval), so this waits first.
 void drop_graphs(lgf_lattice *h)
 {
+    if (h->graphs.empty()) return;
+    (void)hipStreamSynchronize(h->stream);
     for (auto &g : h->graphs) (void)hipGraphExecDestroy(g.exec);
     h->graphs.clear();
 }
@@ -551,6 +555,7 @@ lgf_status run_captured(lgf_lattice *h, const GraphEntry &key, uint64_t sweep0, 
     (void)hipGraphDestroy(graph);
     if (e != hipSuccess) return fail(LGF_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
     if (h->graphs.size() >= 8) {
+        // (its last launch ended with its own check interval)
         (void)hipGraphExecDestroy(h->graphs.front().exec);
         h->graphs.erase(h->graphs.begin());
     }
@@ -821,9 +826,12 @@ lgf_status run_chunk_fixed(lgf_lattice *h, int format, const void *links, void *
                            bool coulomb = false)
 {
     const lgf::SweepTuning t = launch_fixed_tuning(h, format);
-    if (fused)
-        LGF_TRY(ensure_fused_cap(h, (size_t)lgf::fixed_sweep_groups(h->geom, t) +
-                                        (size_t)lgf::fixed_measure_blocks(h->geom)));
+    // room for the partial sums of the measurement that follows, fused or in two
+    // passes, before the chunk is captured: growth drops the graphs
+    if (!coulomb) {
+        const size_t pass = (size_t)lgf::fixed_measure_blocks(h->geom);
+        LGF_TRY(ensure_fused_cap(h, std::max((size_t)lgf::fixed_sweep_groups(h->geom, t), pass) + pass));
+    }
     const bool sr = p_sr > 0.0;
     auto issue = [&](bool captured) -> lgf_status {
         for (int k = 0; k < n; ++k) {

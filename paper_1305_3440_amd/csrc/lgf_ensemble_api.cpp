@@ -200,8 +200,11 @@ lgf_status ensure_work(lgf_ensemble *e, int fmt)
     return LGF_OK;
 }
 
+// (one of them may have been launched and not yet waited for)
 void drop_graphs(lgf_ensemble *e)
 {
+    if (e->graphs.empty()) return;
+    (void)hipStreamSynchronize(e->stream);
     for (auto &g : e->graphs) (void)hipGraphExecDestroy(g.exec);
     e->graphs.clear();
 }

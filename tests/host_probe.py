@@ -1,0 +1,51 @@
+"""What the host side of liblgf.so does, seen without a GPU: runs the library on the stand-in for the HIP runtime of
+fake_hip.cpp and prints the result of one probe as JSON.
+
+    python host_probe.py <fake_hip.so> <probe> <arguments as a JSON list>
+
+Run in a process of its own (test_host_drivers.py): the stand-in takes the place of the runtime for the whole process.
+"""
+import ctypes
+import json
+import os
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+
+
+class Fake:
+    def __init__(self, path):
+        self.lib = ctypes.CDLL(path, mode=ctypes.RTLD_GLOBAL)
+        self.lib.fake_log.restype = ctypes.c_char_p
+        self.lib.fake_result.argtypes = [ctypes.c_double] * 3
+        self.lib.fake_memory.argtypes = [ctypes.c_uint64]
+        self.lib.fake_fast.argtypes = [ctypes.c_char_p]
+        self.lib.fake_new_bytes.restype = ctypes.c_size_t
+
+    def lines(self, call):
+        """the log of one call, a list of words per line"""
+        self.lib.fake_clear()
+        call()
+        return [line.split() for line in self.lib.fake_log().decode().splitlines()]
+
+
+def fix_log(fake, lgf, dims, fmt, calls, theta_factor):
+    """the log of several gauge fixings on one handle; every measurement finds theta_factor times the last one's theta"""
+    with lgf.Lattice(dims, fmt) as lat:
+        fake.lib.fake_result(0.5, 1.0, theta_factor)
+        def run():
+            for gauge, kw in calls:
+                (lat.gauge_fix if gauge == "landau" else lat.coulomb_gauge_fix)(**kw)
+        return fake.lines(run)
+
+
+def main():
+    fake = Fake(sys.argv[1])
+    import paper_1305_3440_amd as lgf
+    lgf.load_library()
+    print(json.dumps(globals()[sys.argv[2]](fake, lgf, *json.loads(sys.argv[3]))))
+
+
+if __name__ == "__main__":
+    main()
