@@ -217,8 +217,8 @@ void drop_graphs(lgf_ensemble *e)
 uint32_t build_work(lgf_ensemble *e, const std::vector<int> &phase, const std::vector<int> &fmt_of,
                     bool include_done, std::vector<int> &listed, int sites = 0, bool fixed = false)
 {
+    const uint32_t w = (uint32_t)(sites > 0 ? sites : e->tile);
     uint32_t nt = 0;
-    std::vector<lgf::EnsTile> order(e->max_tiles);
     listed.clear();
     for (int i = 0; i < e->n; ++i) {
         e->h_cfgs[i].g = e->geom[i];
@@ -228,16 +228,21 @@ uint32_t build_work(lgf_ensemble *e, const std::vector<int> &phase, const std::v
         e->h_cfgs[i].rec = (fixed && e->rec[fmt_of[i]]) ? rec_of(e, fmt_of[i], i) : nullptr;
         e->h_cfgs[i].instance = (uint32_t)i;
         if (!include_done && phase[i] == kDone) continue;
-        const uint32_t w = (uint32_t)(sites > 0 ? sites : e->tile);
         const uint32_t tiles = (e->geom[i].Vh + w - 1) / w;
         e->h_spans[listed.size()] = lgf::EnsSpan{(uint32_t)i, nt, tiles, (double)e->V[i]};
-        for (uint32_t t = 0; t < tiles; ++t) order[nt + t] = lgf::EnsTile{(uint32_t)i, t * w, nt + t, 0u};
         nt += tiles;
         listed.push_back(i);
     }
     // workgroup b runs on XCD b % 8: neighbouring tiles share an XCD and its L2
-    for (uint32_t x = 0, k = 0; x < 8; ++x)
-        for (uint32_t b = x; b < nt; b += 8) e->h_tiles[b] = order[k++];
+    uint32_t xcd = 0, b = 0;
+    for (size_t k = 0; k < listed.size(); ++k) {
+        const lgf::EnsSpan &s = e->h_spans[k];
+        for (uint32_t t = 0; t < s.count; ++t) {
+            e->h_tiles[b] = lgf::EnsTile{s.cfg, t * w, s.first + t, 0u};
+            b += 8;
+            if (b >= nt) b = ++xcd;
+        }
+    }
     *e->h_n_tiles = nt;
     return nt;
 }

@@ -37,8 +37,18 @@ uint64_t next_address = 1ull << 40, next_object = 1, free_bytes = 1ull << 50;
 std::map<void *, uint64_t> sizes;
 std::string fast, last_sweep;
 size_t new_bytes = 0;
+int own = 0;  // inside the stand-in, whose own strings do not count
+struct Own {
+    Own() { ++own; }
+    ~Own() { --own; }
+};
+std::map<size_t, std::string> copied;  // the last host-to-device copy of a size
 
-void line(const std::string &s) { text += s + "\n"; }
+void line(const std::string &s)
+{
+    Own guard;
+    text += s + "\n";
+}
 std::string num(const void *p) { return std::to_string((uintptr_t)p); }
 
 // n 32-bit words of an argument
@@ -57,7 +67,7 @@ std::string words(const void *arg, int n)
 // what the library's own C++ allocations take
 void *operator new(size_t n)
 {
-    new_bytes += n;
+    if (!own) new_bytes += n;
     if (void *p = std::malloc(n ? n : 1)) return p;
     throw std::bad_alloc();
 }
@@ -71,6 +81,7 @@ void fake_clear() { text.clear(); }
 void fake_result(double F, double theta, double f) { result[0] = F; result[1] = theta; factor = f; }
 void fake_memory(uint64_t bytes) { free_bytes = bytes; }
 void fake_fast(const char *s) { fast = s; }
+const char *fake_copied(size_t n) { return copied.count(n) ? copied[n].data() : nullptr; }
 size_t fake_new_bytes() { const size_t n = new_bytes; new_bytes = 0; return n; }
 
 void **__hipRegisterFatBinary(const void *) { static void *module = nullptr; return &module; }
@@ -110,6 +121,7 @@ int __hipPopCallConfiguration(Dim *grid, Dim *block, size_t *lds, void **stream)
 }
 int hipLaunchKernel(const void *f, Dim grid, Dim block, void **args, size_t, void *)
 {
+    Own guard;
     const std::string &k = kernels[f];
     std::string s = std::string(capturing ? "record " : "launch ") + k + " grid " + std::to_string(grid.x) + " " +
                     std::to_string(grid.y) + " block " + std::to_string(block.x);
@@ -139,6 +151,7 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size
 
 int hipMalloc(void **p, size_t n)
 {
+    Own guard;
     if (n > free_bytes) return 2;
     free_bytes -= n;
     *p = (void *)next_address;
@@ -149,6 +162,7 @@ int hipMalloc(void **p, size_t n)
 }
 int hipFree(void *p)
 {
+    Own guard;
     line("free " + num(p));
     if (sizes.count(p)) free_bytes += sizes[p];
     sizes.erase(p);
@@ -156,9 +170,11 @@ int hipFree(void *p)
 }
 int hipHostMalloc(void **p, size_t n, unsigned) { *p = std::calloc(1, n); return *p ? 0 : 2; }
 int hipHostFree(void *p) { std::free(p); return 0; }
-int hipMemcpyAsync(void *dst, const void *, size_t n, int kind, void *)
+int hipMemcpyAsync(void *dst, const void *src, size_t n, int kind, void *)
 {
+    Own guard;
     line("copy " + std::to_string(n) + " kind " + std::to_string(kind));
+    if (kind == 1) copied[n] = std::string((const char *)src, n);
     if (kind == 2) std::memset(dst, 0, n);
     return 0;
 }

@@ -22,6 +22,8 @@ class Fake:
         self.lib.fake_memory.argtypes = [ctypes.c_uint64]
         self.lib.fake_fast.argtypes = [ctypes.c_char_p]
         self.lib.fake_new_bytes.restype = ctypes.c_size_t
+        self.lib.fake_copied.argtypes = [ctypes.c_size_t]
+        self.lib.fake_copied.restype = ctypes.c_void_p
 
     def lines(self, call):
         """the log of one call, a list of words per line"""
@@ -38,6 +40,18 @@ def fix_log(fake, lgf, dims, fmt, calls, theta_factor):
             for gauge, kw in calls:
                 (lat.gauge_fix if gauge == "landau" else lat.coulomb_gauge_fix)(**kw)
         return fake.lines(run)
+
+
+def ensemble_work(fake, lgf, dims, tile):
+    """the tile list of a sweep of the whole ensemble, its spans, and the bytes the call took from the C++ heap"""
+    ens = lgf.Ensemble(dims, 2)
+    lgf.lgf_ensemble_set_tuning(ens.e, tile, 1, 1)
+    n = sum((v // 2 + tile - 1) // tile for v in ens.V)
+    fake.lib.fake_new_bytes()
+    ens.sweep(2, 1.7)
+    heap = fake.lib.fake_new_bytes()
+    tiles = (ctypes.c_uint32 * (4 * n)).from_address(fake.lib.fake_copied(16 * n))
+    return {"tiles": [tiles[4 * k:4 * k + 3] for k in range(n)], "heap": heap}
 
 
 def main():

@@ -64,3 +64,18 @@ def test_graphs_outlive_their_launches(probe, name):
         elif words[0] == "graph_destroy":
             assert words[1] not in launched, f"graph {words[1]} destroyed while it may run: {log[launched[words[1]]:i + 1]}"
     assert 0 < made <= needed
+
+
+@pytest.mark.parametrize("dims,tile", [([[2, 2, 2, 2]], 64), ([[4, 4, 6, 10], [2, 2, 2, 2], [6, 2, 4, 14]], 64),
+                                       ([[8, 8, 8, 8]] * 5 + [[4, 4, 6, 10]], 128), ([[16, 16, 16, 16]] * 24, 64)])
+def test_ensemble_tile_list(probe, dims, tile):
+    """Every tile of every configuration once, consecutive ones on one XCD (workgroup b runs on XCD b % 8), and no
+    copy of the list on the heap of each call."""
+    got = probe("ensemble_work", dims, tile)
+    want = []
+    for i, d in enumerate(dims):
+        half = d[0] * d[1] * d[2] * d[3] // 2
+        want += [[i, h0, len(want) + h0 // tile] for h0 in range(0, half, tile)]
+    # (len(want) is read before the extension)
+    assert [t for x in range(8) for t in got["tiles"][x::8]] == want
+    assert got["heap"] <= 4096 + 64 * len(dims)
