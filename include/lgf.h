@@ -325,15 +325,18 @@ lgf_status lgf_synchronize(lgf_lattice *h);
  * second buffer of the same size, parity 1 writes them back (needs
  * nontemporal = 1; the library allocates the buffer here, LGF_ENOMEM if it
  * cannot).  Every schedule gives bit-identical links; single half-sweeps
- * (lgf_sweep with parity 0 or 1) always run in place.  A new handle starts at 1
- * lane, 1 tile, 128 lanes, no remap, non-temporal, in place -- except FP64-12,
- * which starts out of place (its second buffer allocated before its first full
- * sweep; without memory for it the format falls back to in place).  Until a
- * tuning is set or autotuned, that start is what lgf_get_tuning reports, and
- * launches choose lanes, workgroup, remap, non-temporal access and schedule by
- * the size of the field, with the same bits.
+ * (lgf_sweep with parity 0 or 1) always run in place.  On a new handle launches
+ * choose all of it by the size of the field, with the same bits.  Fields of up
+ * to 1.6 GB are swept in place; larger ones with 1 tile, no remap, non-temporal,
+ * FP64-12 out of place (its second buffer allocated before its first full sweep;
+ * without memory for it the format falls back to in place).  The choice also
+ * fixes the direction of the odd half-sweep and may stream the stores alone,
+ * which a set tuning cannot (streamed stores are reported as nontemporal 1).
  * lgf_set_tuning copies *tuning (LGF_EINVAL on a value outside these sets);
- * lgf_get_tuning fills *tuning with the current values. */
+ * lgf_get_tuning fills *tuning with the current values.  Set again, on this
+ * handle or another of the same extents and format, they give the same
+ * launches: the values reported while launches are chosen by size mean that
+ * choice. */
 typedef struct {
     int lanes_per_site;
     int sites_per_thread;
@@ -352,7 +355,8 @@ lgf_status lgf_get_tuning(const lgf_lattice *h, int format, lgf_sweep_tuning *tu
  * and keep the fastest.  The variants sweep the buffer that lgf_gauge_fix
  * sweeps in that format (the handle's field, saved to a temporary copy first
  * and restored afterwards, or the handle's working copy in another format), so
- * the links are left as they were.  trials = timed full sweeps per variant in
+ * the links are left as they were.  Launches stay chosen by size unless a
+ * variant is 1 % faster than those.  trials = timed full sweeps per variant in
  * the first round (>= 1); the fastest few are re-timed over longer runs. */
 lgf_status lgf_autotune(lgf_lattice *h, int format, int trials);
 
@@ -388,10 +392,11 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials);
  * records; FP32-12 1 lane, 128-lane workgroups, order 0, records (all three
  * on the link field for lattices of fewer than 2^18 sites); FP64-18 2
  * lanes, 64-lane workgroups, order 2, layout 0; FP32-18 2 lanes, 256-lane
- * workgroups, order 0, layout 0.  Until a tuning is set or autotuned, launches on
+ * workgroups, order 0, layout 0.  While the default is in force, launches on
  * lattices of up to 2 million sites choose workgroup, order 1 and lanes by the
  * size, and while links and g take up to 400 MB read the link field, with the
- * same bits.  LGF_EINVAL on other values.  Setting a
+ * same bits; lgf_get_fixed_tuning reports the default, and setting the default
+ * puts it in force again.  LGF_EINVAL on other values.  Setting a
  * tuning closes an open stepwise session (lgf_fix_begin) without applying g. */
 lgf_status lgf_set_fixed_tuning(lgf_lattice *h, int format, const lgf_sweep_tuning *tuning);
 lgf_status lgf_get_fixed_tuning(const lgf_lattice *h, int format, lgf_sweep_tuning *tuning);
@@ -401,8 +406,8 @@ lgf_status lgf_get_fixed_tuning(const lgf_lattice *h, int format, lgf_sweep_tuni
  * layout 0/1 (FP32-12, FP64-12, LGF_FP64_12S); beyond 2 million sites the FP64
  * formats keep tile order 2 wherever the lattice admits it; orders the lattice does not admit are
  * left out): each timed over `trials` full sweeps, the fastest again over ten
- * times as many in five interleaved rounds; the default stays unless another
- * is 1 % faster.  The sweeps read the handle's links (or their copy in
+ * times as many in five interleaved rounds; the default (launches chosen by
+ * size) stays unless another is 1 % faster.  The sweeps read the handle's links (or their copy in
  * `format`, and its per-site records) and write only the gauge
  * transformation, which lgf_gauge_fix resets: the links are untouched.  Needs
  * an FP64 handle.  Synchronises. */

@@ -280,8 +280,8 @@ lgf::SweepTuning default_tuning(int format)
 }
 
 // The tuning of the link sweeps' launches: the handle's where it was set or
-// autotuned, else chosen by the size of the field.  The bits do not depend on
-// it.  Measured per half-sweep launch, defaults above -> chosen:
+// autotuned (launch_tuning), else chosen from its starting tuning t by the size
+// of the field.  The bits do not depend on it.  Measured per half-sweep launch, defaults above -> chosen:
 //  - Fields of up to 420 MB stay in the 256 MB last-level cache from one
 //    half-sweep to the next, wholly or, since the odd half-sweep walks the lattice
 //    from its end and starts on what the even one read last, in part; but only if
@@ -306,10 +306,8 @@ lgf::SweepTuning default_tuning(int format)
 //    them throughout, two waves per SIMD instead of one: 24^4 42.3 -> 39.4 us.
 //  - Beyond: 256-lane workgroups in FP32 (64^4 FP32-18 1749 -> 1695 us) and two
 //    lanes per site in FP32-12 (1157 -> 1111, 48^4 382 -> 374).
-lgf::SweepTuning launch_tuning(const lgf_lattice *h, int format)
+lgf::SweepTuning size_tuning(const lgf_lattice *h, int format, lgf::SweepTuning t)
 {
-    lgf::SweepTuning t = h->tune[format];
-    if (h->tuned[format]) return t;
     const double mb = 4e-6 * (double)h->V * (double)lgf::link_bytes(format);
     if (mb <= 420.0) {
         t.schedule = lgf::kScheduleInPlace;
@@ -328,6 +326,22 @@ lgf::SweepTuning launch_tuning(const lgf_lattice *h, int format)
         t.block = 256;
         if (format == LGF_FP32_12) t.lanes_per_site = 2;
     }
+    return t;
+}
+
+lgf::SweepTuning launch_tuning(const lgf_lattice *h, int format)
+{
+    const lgf::SweepTuning &t = h->tune[format];
+    return h->tuned[format] ? t : size_tuning(h, format, t);
+}
+
+// A link-sweep tuning as lgf_sweep_tuning has it: without the direction, and
+// with streamed stores as streamed.  Launches chosen by size can have both, set
+// or autotuned ones neither.
+lgf::SweepTuning as_set(lgf::SweepTuning t)
+{
+    t.nontemporal = t.nontemporal != lgf::kCached ? 1 : 0;
+    t.backward = 0;
     return t;
 }
 
@@ -1256,8 +1270,7 @@ lgf_status lgf_create(const int dims[4], int format, void *stream, void *device_
     h->geom = make_geom(dims);
     h->format = format;
     h->field_bytes = need;
-    // defaults: one lane per site, 128-thread workgroups, non-temporal
-    // streaming (fastest measured at 64^4 for every format)
+    // starting tunings (the fastest measured at 64^4); launches choose by size from them
     for (int f = 0; f < 4; ++f) h->tune[f] = default_tuning(f);
     for (int f = 0; f <= LGF_FP64_12S; ++f) h->tune_fixed[f] = default_fixed_tuning(f, h->V);
 
@@ -2093,9 +2106,13 @@ lgf_status lgf_set_tuning(lgf_lattice *h, int format, const lgf_sweep_tuning *t)
         LGF_TRY(use_device(h));
         LGF_TRY(ensure_partner(h, format));
     }
-    h->tune[format] = lgf::SweepTuning{u.lanes_per_site, u.block,      u.xcd_remap ? 1 : 0, u.nontemporal ? 1 : 0,
-                                       u.schedule,       u.sites_per_thread};
-    h->tuned[format] = true;
+    const lgf::SweepTuning n{u.lanes_per_site, u.block,      u.xcd_remap ? 1 : 0, u.nontemporal ? 1 : 0,
+                             u.schedule,       u.sites_per_thread};
+    // what lgf_get_tuning reports while launches are chosen by size leaves, or
+    // makes, them so: the struct has no room for all that the choice fixes
+    const lgf::SweepTuning start = h->tuned[format] ? default_tuning(format) : h->tune[format];
+    h->tuned[format] = !(n == as_set(size_tuning(h, format, start)));
+    h->tune[format] = h->tuned[format] ? n : start;
     drop_graphs(h);
     return LGF_OK;
 }
@@ -2104,7 +2121,7 @@ lgf_status lgf_get_tuning(const lgf_lattice *h, int format, lgf_sweep_tuning *t)
 {
     if (!h || !t) return fail(LGF_EINVAL, "NULL handle or tuning");
     if (!valid_format(format)) return fail(LGF_EINVAL, "unknown format %d", format);
-    const lgf::SweepTuning &u = h->tune[format];
+    const lgf::SweepTuning u = as_set(launch_tuning(h, format));
     t->lanes_per_site = u.lanes_per_site;
     t->sites_per_thread = u.sites_per_thread;
     t->block = u.block;
@@ -2136,10 +2153,15 @@ lgf_status lgf_set_fixed_tuning(lgf_lattice *h, int format, const lgf_sweep_tuni
     // an open stepwise session holds its links in the layout of the old
     // tuning: it is closed (without applying g)
     h->fix_on = false;
+    // the starting tuning, which lgf_get_fixed_tuning reports while launches are
+    // chosen by size, leaves, or makes, them so (so does the link field in place of
+    // records for which there was no memory)
+    const bool start = n == default_fixed_tuning(format, h->V) ||
+                       (!h->tuned_fixed[format] && n == h->tune_fixed[format]);
     h->tune_fixed[format] = n;
-    h->tuned_fixed[format] = true;
+    h->tuned_fixed[format] = !start;
     drop_graphs(h);
-    if (h->rec[format] && n.schedule != lgf::kLayoutRecords) {
+    if (h->rec[format] && !fixed_records(h, format)) {
         // the link field from now on: the records' memory goes back
         (void)hipFree(h->rec[format]);
         h->rec[format] = nullptr;
@@ -2240,6 +2262,8 @@ lgf_status lgf_autotune_fixed(lgf_lattice *h, int format, int trials)
                 for (int layout : {lgf::kLayoutPlanes, lgf::kLayoutRecords}) {
                     if (layout == lgf::kLayoutRecords && !records) continue;
                     t.schedule = layout;
+                    // (set again, the starting tuning means the default)
+                    if (t == untuned && !(t == dflt)) continue;
                     variants.push_back(t);
                 }
             }
@@ -2304,11 +2328,9 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials)
     const lgf::SweepTuning saved = h->tune[format];
     const bool was_tuned = h->tuned[format];
     // the default: what untuned launches of this lattice run
-    h->tune[format] = default_tuning(format);
-    h->tuned[format] = false;
-    lgf::SweepTuning dflt = launch_tuning(h, format);
-    if (!can_oop && dflt.schedule == lgf::kScheduleOutOfPlace) dflt.schedule = lgf::kScheduleInPlace;
-    h->tune[format] = saved;
+    lgf::SweepTuning untuned = default_tuning(format);
+    if (!can_oop) untuned.schedule = lgf::kScheduleInPlace;
+    const lgf::SweepTuning dflt = size_tuning(h, format, untuned);
     h->tuned[format] = true;  // while the variants are timed
     lgf_status st = LGF_OK;
     // time n full sweeps of one variant after one untimed full sweep
@@ -2349,7 +2371,10 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials)
                 if (sched == lgf::kSchedulePipeline || spt > 4) continue;
                 if (sched == lgf::kScheduleOutOfPlace && (!nt || !can_oop)) continue;
                 if (spt > 1 && xcd) continue;
-                variants.push_back(lgf::SweepTuning{lps_list[li], block_list[bi], xcd, nt, sched, spt});
+                const lgf::SweepTuning t{lps_list[li], block_list[bi], xcd, nt, sched, spt};
+                // (set again, the default's own fields mean the default)
+                if (t == as_set(dflt) && !(t == dflt)) continue;
+                variants.push_back(t);
             }
     lgf::SweepTuning best = saved;
     if (e == hipSuccess && st == LGF_OK)
@@ -2363,10 +2388,10 @@ lgf_status lgf_autotune(lgf_lattice *h, int format, int trials)
     (void)hipStreamSynchronize(h->stream);
     if (backup) (void)hipFree(backup);
     if (st == LGF_OK && e == hipSuccess) {
-        h->tune[format] = best;
-        h->tuned[format] = true;
+        h->tuned[format] = !(best == dflt);
+        h->tune[format] = h->tuned[format] ? best : untuned;
     }
-    if (!had_partner && h->partner[format] && h->tune[format].schedule != lgf::kScheduleOutOfPlace) {
+    if (!had_partner && h->partner[format] && launch_tuning(h, format).schedule != lgf::kScheduleOutOfPlace) {
         (void)hipFree(h->partner[format]);
         h->partner[format] = nullptr;
     }

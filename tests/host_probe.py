@@ -1,7 +1,7 @@
 """What the host side of liblgf.so does, seen without a GPU: runs the library on the stand-in for the HIP runtime of
-fake_hip.cpp and prints the result of one probe as JSON.
+fake_hip.cpp and prints the results of a probe, for one list of arguments after the other, as a JSON list.
 
-    python host_probe.py <fake_hip.so> <probe> <arguments as a JSON list>
+    python host_probe.py <fake_hip.so> <probe> < <a JSON list of argument lists>
 
 Run in a process of its own (test_host_drivers.py): the stand-in takes the place of the runtime for the whole process.
 """
@@ -42,6 +42,62 @@ def fix_log(fake, lgf, dims, fmt, calls, theta_factor):
         return fake.lines(run)
 
 
+def sweeps_of(fake, lat, form, fmt):
+    """the sweep launches of one full sweep on the handle as it is tuned"""
+    if form == "link":
+        log = fake.lines(lambda: (lat.sweep(2, 1.7), lat.sweep_coulomb(2, 1.7)))
+    else:
+        lat.fix_begin(fmt)
+        log = fake.lines(lambda: lat.fix_chunk(1, 1.7, use_graph=0))
+    return [line[1:] for line in log if line[0] == "launch" and "sweep" in line[1]]
+
+
+def tuning_flows(fake, lgf, dims, fmt, form, other, fast):
+    """The sweep launches after several uses of the tuning calls (other: some set tuning, fast: text of the launches
+    that the autotuner finds faster), and the tunings that were reported."""
+    get, set_, tune = {"link": (lgf.lgf_get_tuning, lgf.lgf_set_tuning, lgf.lgf_autotune),
+                       "fixed": (lgf.lgf_get_fixed_tuning, lgf.lgf_set_fixed_tuning, lgf.lgf_autotune_fixed)}[form]
+    home = fmt if form == "link" else 0
+    out = {}
+
+    def note(name, lat):
+        out[name] = [list(get(lat.h, fmt)), sweeps_of(fake, lat, form, fmt)]
+
+    with lgf.Lattice(dims, home) as lat:
+        note("fresh", lat)
+        start = get(lat.h, fmt)
+        set_(lat.h, fmt, *start)
+        note("got and set", lat)
+        set_(lat.h, fmt, *other)
+        note("other", lat)
+        set_(lat.h, fmt, *start)
+        note("put back", lat)
+        tune(lat.h, fmt, 1)
+        note("tuned, default kept", lat)
+        kept = get(lat.h, fmt)
+        set_(lat.h, fmt, *kept)
+        note("tuned, got and set", lat)
+        fake.lib.fake_fast(fast.encode())
+        tune(lat.h, fmt, 1)
+        fake.lib.fake_fast(b"")
+        note("tuned, another", lat)
+        found = get(lat.h, fmt)
+        set_(lat.h, fmt, *found)
+        note("another, got and set", lat)
+    for name, t in (("kept, set on a new handle", kept), ("another, set on a new handle", found)):
+        with lgf.Lattice(dims, home) as lat:
+            set_(lat.h, fmt, *t)
+            note(name, lat)
+    return out
+
+
+def explicit_launch(fake, lgf, dims, fmt, tuning):
+    """the sweep launches of a handle with this link-sweep tuning"""
+    with lgf.Lattice(dims, fmt) as lat:
+        lgf.lgf_set_tuning(lat.h, fmt, *tuning)
+        return sweeps_of(fake, lat, "link", fmt)
+
+
 def ensemble_work(fake, lgf, dims, tile):
     """the tile list of a sweep of the whole ensemble, its spans, and the bytes the call took from the C++ heap"""
     ens = lgf.Ensemble(dims, 2)
@@ -58,7 +114,7 @@ def main():
     fake = Fake(sys.argv[1])
     import paper_1305_3440_amd as lgf
     lgf.load_library()
-    print(json.dumps(globals()[sys.argv[2]](fake, lgf, *json.loads(sys.argv[3]))))
+    print(json.dumps([globals()[sys.argv[2]](fake, lgf, *args) for args in json.load(sys.stdin)]))
 
 
 if __name__ == "__main__":

@@ -16,9 +16,10 @@ def probe(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"), "-o", so],
                    check=True)
 
-    def run(name, *args):
-        out = subprocess.run([sys.executable, os.path.join(HERE, "host_probe.py"), so, name, json.dumps(args)],
-                             check=True, capture_output=True, text=True)
+    def run(name, cases):
+        """the probe's result for every list of arguments, from one process"""
+        out = subprocess.run([sys.executable, os.path.join(HERE, "host_probe.py"), so, name], check=True,
+                             input=json.dumps(cases), capture_output=True, text=True)
         return json.loads(out.stdout)
     return run
 
@@ -47,12 +48,17 @@ GRAPH_RUNS = {
 }
 
 
+@pytest.fixture(scope="module")
+def graph_logs(probe):
+    cases = [((24, 24, 24, 24), 0, calls, factor) for calls, factor, _ in GRAPH_RUNS.values()]
+    return dict(zip(GRAPH_RUNS, probe("fix_log", cases)))
+
+
 @pytest.mark.parametrize("name", GRAPH_RUNS)
-def test_graphs_outlive_their_launches(probe, name):
+def test_graphs_outlive_their_launches(graph_logs, name):
     """A captured graph is destroyed only once the stream has been waited for since its last launch, and the chunks of
     one length replay one graph."""
-    calls, factor, needed = GRAPH_RUNS[name]
-    log = probe("fix_log", (24, 24, 24, 24), 0, calls, factor)
+    log, needed = graph_logs[name], GRAPH_RUNS[name][2]
     launched, made = {}, 0
     for i, words in enumerate(log):
         if words[0] == "graph_new":
@@ -71,7 +77,7 @@ def test_graphs_outlive_their_launches(probe, name):
 def test_ensemble_tile_list(probe, dims, tile):
     """Every tile of every configuration once, consecutive ones on one XCD (workgroup b runs on XCD b % 8), and no
     copy of the list on the heap of each call."""
-    got = probe("ensemble_work", dims, tile)
+    got, = probe("ensemble_work", [(dims, tile)])
     want = []
     for i, d in enumerate(dims):
         half = d[0] * d[1] * d[2] * d[3] // 2
@@ -79,3 +85,54 @@ def test_ensemble_tile_list(probe, dims, tile):
     # (len(want) is read before the extension)
     assert [t for x in range(8) for t in got["tiles"][x::8]] == want
     assert got["heap"] <= 4096 + 64 * len(dims)
+
+
+# fields of both formats' sizes between and beyond all lines of the choice (link form: 22, 48, 280, 420 MB and 1.6 GB;
+# fixed-link form: 80000, 2^18 and 2 million sites, 400 MB)
+LINK_DIMS = [(8, 8, 8, 8), (16, 16, 16, 16), (20, 20, 20, 20), (28, 28, 28, 28), (32, 32, 32, 32), (40, 40, 40, 40),
+             (64, 64, 64, 64)]
+FIXED_DIMS = [(8, 8, 8, 8), (20, 20, 20, 20), (24, 24, 24, 24), (32, 32, 32, 32), (48, 48, 48, 48)]
+
+
+TUNING_CASES = [("link", d, f) for d in LINK_DIMS for f in range(4)] + [("fixed", d, f) for d in FIXED_DIMS for f in range(5)]
+OTHER = {"link": (4, 256, 0, 1, 0, 2), "fixed": (4, 256, 0, 0)}
+
+
+@pytest.fixture(scope="module")
+def tuning_flows(probe):
+    flows = probe("tuning_flows", [(d, f, form, OTHER[form], f"sweep_kernel<{f},_4,") for form, d, f in TUNING_CASES])
+    return dict(zip(TUNING_CASES, flows))
+
+
+@pytest.mark.parametrize("form,dims,fmt", TUNING_CASES)
+def test_tunings_come_back_as_they_were_reported(tuning_flows, form, dims, fmt):
+    """Setting what was reported changes no launch, on this handle or a new one: before any tuning, after the autotuner
+    kept the default (launches chosen by size), after it found something else; and what is reported is within the
+    documented values.  A start put back after another tuning is the start again."""
+    got = tuning_flows[form, dims, fmt]
+    for name in ("got and set", "put back", "tuned, default kept", "tuned, got and set", "kept, set on a new handle"):
+        assert got[name] == got["fresh"], name
+    assert got["other"][0] == list(OTHER[form]) and got["other"] != got["fresh"]
+    assert f"sweep_kernel<{fmt},_4," in got["tuned, another"][1][0][0]
+    for name in ("another, got and set", "another, set on a new handle"):
+        assert got[name] == got["tuned, another"], name
+    for t, _ in got.values():
+        lanes, block, order = t[:3]
+        assert lanes in (1, 2, 4) and block in (64, 128, 256)
+        if form == "link":
+            nt, schedule, sites = t[3:]
+            assert order in (0, 1) and nt in (0, 1) and schedule in (0, 2) and sites in (1, 2, 4)
+            assert nt or schedule != 2
+        else:
+            assert order in (0, 1, 2, 3) and t[3] in (0, 1)
+
+
+def test_an_explicit_tuning_is_run_as_set(probe):
+    """One lane per site, 128-lane workgroups, streamed, plain order, in place: what new handles once ran, still to be had
+    at every size."""
+    cases = [(d, f, (1, 128, 0, 1, 0, 1)) for d in LINK_DIMS for f in range(4)]
+    for (dims, fmt, _), launch in zip(cases, probe("explicit_launch", cases)):
+        half = dims[0] * dims[1] * dims[2] * dims[3] // 2
+        for line in launch[:2]:
+            assert line[0].startswith(f"sweep_kernel<{fmt},_1,_false,_1,_false"), line
+            assert line[1:] == ["grid", str((half + 127) // 128), "1", "block", "128", "order", "0"], line
