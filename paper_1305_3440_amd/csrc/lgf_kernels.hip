@@ -973,12 +973,39 @@ hipError_t launch_site_field(int format, void *gf, const Geom &g, int mode, hipS
     return hipGetLastError();
 }
 
+// X <- g(x) of the site field gf in format FG, reunitarized
+template <int FG>
+__device__ __forceinline__ void load_transform(mat3<double> &X, const void *gf, const Geom &g, int parity, uint32_t h)
+{
+    mat3<typename Fmt<FG>::T> gx;
+    load_link<FG>(gx, site_field_ptr<FG>(const_cast<void *>(gf), g.Vh, parity), g.Vh, h);
+    convert(X, gx);
+    reunitarize(X);
+}
+
+// dst's link mu (format FD) of a site <- X src_mu(x) g(x+mu)^dag, src in format FS
+template <int FS, int FG, int FD, bool NT>
+__device__ __forceinline__ void transform_link(const void *src, const void *gf, void *dst, const Geom &g, int parity,
+                                               const Site &c, uint32_t h, int mu, const mat3<double> &X)
+{
+    mat3<typename Fmt<FS>::T> u;
+    load_link<FS, NT>(u, block_ptr<FS>(const_cast<void *>(src), g.Vh, parity, mu), g.Vh, h);
+    mat3<double> U, Y, t, r;
+    load_transform<FG>(Y, gf, g, parity ^ 1, fwd_half(g, c, h, mu));
+    convert(U, u);
+    left_mul<3>(t, X, U);
+    right_mul_dag<3>(r, t, Y);
+    mat3<typename Fmt<FD>::T> o;
+    convert(o, r);
+    store_link<FD, NT>(block_ptr<FD>(dst, g.Vh, parity, mu), g.Vh, h, o);
+}
+
 // dst (format FD) <- g(x) src_mu(x) g(x+mu)^dag, src in format FS, g in FG;
 // element-wise per link, so dst may be src when FD == FS.  HBM bound if g(x)
 // is read and reunitarized once per site and the neighbours' g stay in a cache:
 // one lane per site takes its 4 links, and the tiles of both parities go in
 // runs per XCD, as in measure_kernel.  FP64-18 with g in FP64-12, one lane per
-// link before -> now: 64^4 6.41 -> 3.99 ms (19.3 GB of links: 3.0 ms at a copy's
+// link against this: 64^4 6.41 -> 3.99 ms (19.3 GB of links: 3.0 ms at a copy's
 // rate), 48 x 24^3 178 -> 162 us; g in FP32-12, 36 x 20 x 28 x 24 107 -> 97 us.
 template <int FS, int FG, int FD>
 __global__ void __launch_bounds__(256, 2) gauge_transform_kernel(const void *src, const void *__restrict__ gf, void *dst,
@@ -990,39 +1017,53 @@ __global__ void __launch_bounds__(256, 2) gauge_transform_kernel(const void *src
     const uint32_t h = (b >> 1) * 256 + threadIdx.x;
     if (h >= g.Vh) return;
     const Site c = decode(g, parity, h);
-    mat3<typename Fmt<FG>::T> gx;
-    load_link<FG>(gx, site_field_ptr<FG>(const_cast<void *>(gf), g.Vh, parity), g.Vh, h);
     mat3<double> X;
-    convert(X, gx);
-    reunitarize(X);
+    load_transform<FG>(X, gf, g, parity, h);
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) {
-        mat3<typename Fmt<FS>::T> u;
-        mat3<typename Fmt<FG>::T> gy;
-        load_link<FS, true>(u, block_ptr<FS>(const_cast<void *>(src), g.Vh, parity, mu), g.Vh, h);
-        load_link<FG>(gy, site_field_ptr<FG>(const_cast<void *>(gf), g.Vh, parity ^ 1), g.Vh, fwd_half(g, c, h, mu));
-        mat3<double> U, Y, t, r;
-        convert(U, u);
-        convert(Y, gy);
-        reunitarize(Y);
-        left_mul<3>(t, X, U);
-        right_mul_dag<3>(r, t, Y);
-        mat3<typename Fmt<FD>::T> o;
-        convert(o, r);
-        store_link<FD, true>(block_ptr<FD>(dst, g.Vh, parity, mu), g.Vh, h, o);
+    for (int mu = 0; mu < 4; ++mu) transform_link<FS, FG, FD, true>(src, gf, dst, g, parity, c, h, mu, X);
+}
+
+// The same with one lane per link, parity and direction in blockIdx.y: where
+// the launch is too small to fill the chip its time is one wave's, and four
+// links one after the other take longer than reading g(x) four times.
+template <int FS, int FG, int FD>
+__global__ void __launch_bounds__(256) gauge_transform_link_kernel(const void *src, const void *__restrict__ gf,
+                                                                   void *dst, Geom g)
+{
+    const uint32_t h = blockIdx.x * 256 + threadIdx.x;
+    if (h >= g.Vh) return;
+    const int parity = blockIdx.y >> 2, mu = blockIdx.y & 3;
+    const Site c = decode(g, parity, h);
+    mat3<double> X;
+    load_transform<FG>(X, gf, g, parity, h);
+    transform_link<FS, FG, FD, false>(src, gf, dst, g, parity, c, h, mu, X);
+}
+
+// One lane per link up to this many sites.  The whole lgf_fix_end call, one
+// lane per site against per link, FP64-18 with g in FP64-12: 8^4 19.6 -> 15.1
+// us, 12^4 23.0 -> 19.1, 14^4 25.5 -> 21.9, 16^4 29.8 -> 26.1; at 18^4 38.2 against
+// 41.2, FP64-12 links 29.2 against 34.6.
+constexpr uint32_t kLinkTransformSites = 80000;
+
+template <int FS, int FG, int FD>
+static void launch_gt_t(const void *src, const void *gf, void *dst, const Geom &g, hipStream_t s)
+{
+    const uint32_t nt = (g.Vh + 255) / 256;
+    if (2 * g.Vh <= kLinkTransformSites) {
+        hipLaunchKernelGGL((gauge_transform_link_kernel<FS, FG, FD>), dim3(nt, 8), dim3(256), 0, s, src, gf, dst, g);
+        return;
     }
+    uint32_t ng = 0;
+    const XcdRuns runs = xcd_runs(2 * nt, g, 4 * link_bytes(FS), &ng);
+    hipLaunchKernelGGL((gauge_transform_kernel<FS, FG, FD>), dim3(ng), dim3(256), 0, s, src, gf, dst, g, runs, nt);
 }
 
 template <int FS, int FG>
 static hipError_t launch_gt_d(int fd, const void *src, const void *gf, void *dst, const Geom &g, hipStream_t s)
 {
-    const uint32_t nt = (g.Vh + 255) / 256;
-    uint32_t ng = 0;
-    const XcdRuns runs = xcd_runs(2 * nt, g, 4 * link_bytes(FS), &ng);
-    const dim3 grid(ng), block(256);
     switch (fd) {
-    case kF64_18: hipLaunchKernelGGL((gauge_transform_kernel<FS, FG, kF64_18>), grid, block, 0, s, src, gf, dst, g, runs, nt); break;
-    case kF64_12: hipLaunchKernelGGL((gauge_transform_kernel<FS, FG, kF64_12>), grid, block, 0, s, src, gf, dst, g, runs, nt); break;
+    case kF64_18: launch_gt_t<FS, FG, kF64_18>(src, gf, dst, g, s); break;
+    case kF64_12: launch_gt_t<FS, FG, kF64_12>(src, gf, dst, g, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

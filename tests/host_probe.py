@@ -98,6 +98,13 @@ def explicit_launch(fake, lgf, dims, fmt, tuning):
         return sweeps_of(fake, lat, "link", fmt)
 
 
+def session_end(fake, lgf, dims, fmt):
+    """the launches of a stepwise session's end"""
+    with lgf.Lattice(dims, 0) as lat:
+        lat.fix_begin(fmt)
+        return [line[1:] for line in fake.lines(lat.fix_end) if line[0] == "launch"]
+
+
 def ensemble_work(fake, lgf, dims, tile):
     """the tile list of a sweep of the whole ensemble, its spans, and the bytes the call took from the C++ heap"""
     ens = lgf.Ensemble(dims, 2)

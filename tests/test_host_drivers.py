@@ -136,3 +136,11 @@ def test_an_explicit_tuning_is_run_as_set(probe):
         for line in launch[:2]:
             assert line[0].startswith(f"sweep_kernel<{fmt},_1,_false,_1,_false"), line
             assert line[1:] == ["grid", str((half + 127) // 128), "1", "block", "128", "order", "0"], line
+
+
+def test_the_transformation_has_a_lane_per_link_on_small_lattices(probe):
+    cases = [((8, 8, 8, 8), 3), ((20, 20, 20, 10), 2), ((20, 20, 20, 12), 2)]
+    ends = probe("session_end", cases)
+    assert ends == [[["gauge_transform_link_kernel<0,_3,_0>", "grid", "8", "8", "block", "256"]],
+                    [["gauge_transform_link_kernel<0,_2,_0>", "grid", "157", "8", "block", "256"]],
+                    [["gauge_transform_kernel<0,_2,_0>", "grid", "376", "1", "block", "256"]]]
