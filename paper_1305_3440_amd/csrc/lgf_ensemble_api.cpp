@@ -209,15 +209,58 @@ void drop_graphs(lgf_ensemble *e)
     e->graphs.clear();
 }
 
-// Work list of the configurations not done (all with include_done), each in
-// format fmt_of[i], in tiles of `sites` sites (0: e->tile, one lane per site);
-// fixed: the descriptors also carry the gauge transformation of that format
-// and the records of its links (where allocated).
-// Fills the host mirrors and returns the tiles (upload_work sends them).
-uint32_t build_work(lgf_ensemble *e, const std::vector<int> &phase, const std::vector<int> &fmt_of,
-                    bool include_done, std::vector<int> &listed, int sites = 0, bool fixed = false)
+enum WorkFor { kForSweeps, kForFixedSweeps, kForMeasurement };
+
+// Whether the tiles of a list go to the XCDs in contiguous ranges (workgroup b
+// runs on XCD b % 8) or in the order of dispatch: `total` sites in n
+// configurations, `bytes` of links.  Time in XCD ranges over that in the order
+// of dispatch:
+//  - The link sweeps have nothing to share, so the L2s gain only on small
+//    ensembles: 48 of 8^4 (28 to 113 MB) 0.95-0.98, 24 of 12^4 FP64-12 (191 MB) 1.00, 16
+//    of 16^4 FP64-18 (604 MB) 1.08, 48 of 16^4 1.05 (FP64-12) and 1.05 (FP32-12).  From
+//    2^18 sites on a vector plane of one parity is larger than a 2 MB page, and an
+//    XCD with its own range meets fewer of them: 48 of 24^4 0.85-0.93, 8 of 32^4
+//    0.88-0.90, 12 of 64 x 32^3 0.86-0.97; 48 of 20^4 1.01-1.02.
+//  - The fixed-link sweeps share g: in ranges where links and g are cached (24
+//    of 12^4 0.73-0.84) and on small configurations beyond (30 of 14^4 0.93-0.97,
+//    12 of 20^4 0.96-0.98); but 48 of 24^4 1.03 (1.06 in FP32-12), 16 of 24^4 FP64-18
+//    1.04, 48 of 20^4 FP64-18 1.03; in FP64 formats from 32^4 on 0.93-1.00, FP32-12
+//    1.02-1.03.
+//  - The measurement in two passes: 16 of 16^4 FP32-12 (201 MB) 0.95, FP64-12 (403 MB)
+//    0.99, FP64-18 (604 MB) 1.06; 48 of 24^4 1.05 in FP32-12 and FP64-12 (64 and 127 MB
+//    each), 0.94 in FP64-18 (191 MB), 8 of 32^4 0.91-0.93.
+bool in_xcd_ranges(const lgf_ensemble *e, WorkFor what, const std::vector<int> &listed, const std::vector<int> &fmt_of)
 {
-    const uint32_t w = (uint32_t)(sites > 0 ? sites : e->tile);
+    if (listed.empty()) return false;
+    double total = 0.0, bytes = 0.0;
+    bool fp32 = false;
+    for (int i : listed) {
+        total += (double)e->V[i];
+        bytes += 4.0 * (double)e->V[i] * (fmt_of[i] == LGF_FP64_12S ? 72.0 : (double)lgf::link_bytes(fmt_of[i]));
+        fp32 = fp32 || fmt_of[i] == LGF_FP32_12;  // (the one FP32 format of fixed-link ensembles)
+    }
+    const double mean = total / (double)listed.size();
+    switch (what) {
+    case kForSweeps: return bytes <= 120e6 || mean >= 262144.0;
+    case kForFixedSweeps: {
+        const bool fp64_18 = fmt_of[listed[0]] == LGF_FP64_18;
+        if (fixed_cached(e, fmt_of[listed[0]]) || mean < (fp64_18 ? 120e3 : 200e3)) return true;
+        return !fp32 && mean >= 500e3;
+    }
+    default: return bytes <= 330e6 || bytes >= 150e6 * (double)listed.size();
+    }
+}
+
+// Work list of the configurations not done (all with include_done), each in
+// format fmt_of[i], in tiles of e->tile lanes; for the fixed-link sweeps the
+// descriptors also carry the gauge transformation of that format and the
+// records of its links (where allocated).
+// Fills the host mirrors and returns the tiles (upload_work sends them).
+uint32_t build_work(lgf_ensemble *e, WorkFor what, const std::vector<int> &phase, const std::vector<int> &fmt_of,
+                    bool include_done, std::vector<int> &listed)
+{
+    const bool fixed = what == kForFixedSweeps;
+    const uint32_t w = (uint32_t)(fixed ? e->tile / lgf::kEnsFixedLanes : e->tile);
     uint32_t nt = 0;
     listed.clear();
     for (int i = 0; i < e->n; ++i) {
@@ -233,13 +276,13 @@ uint32_t build_work(lgf_ensemble *e, const std::vector<int> &phase, const std::v
         nt += tiles;
         listed.push_back(i);
     }
-    // workgroup b runs on XCD b % 8: neighbouring tiles share an XCD and its L2
+    const uint32_t step = in_xcd_ranges(e, what, listed, fmt_of) ? 8 : 1;
     uint32_t xcd = 0, b = 0;
     for (size_t k = 0; k < listed.size(); ++k) {
         const lgf::EnsSpan &s = e->h_spans[k];
         for (uint32_t t = 0; t < s.count; ++t) {
             e->h_tiles[b] = lgf::EnsTile{s.cfg, t * w, s.first + t, 0u};
-            b += 8;
+            b += step;
             if (b >= nt) b = ++xcd;
         }
     }
@@ -525,7 +568,7 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
     std::vector<int> phase(e->n, mixed ? kBulk : kFinish), fmt(e->n, e->format), listed;
     std::vector<char> started(e->n, 0);
     // measurement 0 on the home links (g = 1)
-    uint32_t nt = build_work(e, phase, fmt, true, listed);
+    uint32_t nt = build_work(e, kForMeasurement, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     LGF_TRY(timed(t_meas, [&]() { return measure_listed(e, e->format, e->format, nt, listed, false); }));
     LGF_HIP(clock.wait());
@@ -564,11 +607,10 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
         return false;
     };
     const bool fuse = !p.separate_measure;
-    const int sites = e->tile / lgf::kEnsFixedLanes;
     bool changed = true;  // the work list, since its last upload
     while (live() && sweeps < p.max_sweeps) {
         if (changed) {
-            nt = build_work(e, phase, fmt, false, listed, sites, true);
+            nt = build_work(e, kForFixedSweeps, phase, fmt, false, listed);
             LGF_TRY(upload_work(e, nt, listed.size()));
             changed = false;
         }
@@ -639,7 +681,7 @@ lgf_status ensemble_fix_fixed(lgf_ensemble *e, const lgf_fix_params &p, int bulk
                 any = true;
             }
         if (any) {
-            nt = build_work(e, ph, fh, false, listed);
+            nt = build_work(e, kForMeasurement, ph, fh, false, listed);
             LGF_TRY(upload_work(e, nt, listed.size()));
             LGF_TRY(timed(t_meas, [&]() { return measure_listed(e, e->format, e->format, nt, listed, false); }));
             LGF_HIP(clock.wait());
@@ -837,7 +879,7 @@ lgf_status lgf_ensemble_sweep(lgf_ensemble *e, int parity, double omega, double 
     if (!(p_sr >= 0.0 && p_sr <= 1.0)) return fail(LGF_EINVAL, "p_sr %g outside [0, 1]", p_sr);
     LGF_TRY(ens_use_device(e));
     std::vector<int> phase(e->n, kFinish), fmt(e->n, e->format), listed;
-    const uint32_t nt = build_work(e, phase, fmt, true, listed);
+    const uint32_t nt = build_work(e, kForSweeps, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     const bool sr = p_sr > 0.0;
     if (sr) LGF_HIP(lgf::launch_set_u64(e->d_sweep_base, sweep_index, e->stream));
@@ -855,7 +897,7 @@ lgf_status lgf_ensemble_measure(lgf_ensemble *e, double *F, double *theta)
     if (!e) return fail(LGF_EINVAL, "ensemble is NULL");
     LGF_TRY(ens_use_device(e));
     std::vector<int> phase(e->n, kFinish), fmt(e->n, e->format), listed;
-    const uint32_t nt = build_work(e, phase, fmt, true, listed);
+    const uint32_t nt = build_work(e, kForMeasurement, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     LGF_TRY(measure_listed(e, e->format, e->format, nt, listed, false));
     LGF_HIP(hipStreamSynchronize(e->stream));
@@ -905,7 +947,7 @@ lgf_status lgf_ensemble_gauge_fix(lgf_ensemble *e, const lgf_fix_params *pp, lgf
     lgf::PhaseClock &clock = e->clock;
     clock.reset();
     // measurement 0 on the home field
-    uint32_t nt = build_work(e, phase, fmt, true, listed);
+    uint32_t nt = build_work(e, kForMeasurement, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     LGF_TRY(measure_listed(e, e->format, e->format, nt, listed, false));
     LGF_HIP(hipStreamSynchronize(e->stream));
@@ -943,7 +985,7 @@ lgf_status lgf_ensemble_gauge_fix(lgf_ensemble *e, const lgf_fix_params *pp, lgf
     bool changed = true;  // the work list, since its last upload
     while (live() && sweeps < p.max_sweeps) {
         if (changed) {
-            nt = build_work(e, phase, fmt, false, listed);
+            nt = build_work(e, kForSweeps, phase, fmt, false, listed);
             LGF_TRY(upload_work(e, nt, listed.size()));
             changed = false;
         }
@@ -1032,7 +1074,7 @@ lgf_status lgf_ensemble_time_sweeps(lgf_ensemble *e, int format, int n, double o
     LGF_TRY(make_scratch(e, format));
     std::vector<int> phase(e->n, kFinish), fmt(e->n, format), listed;
     auto timed = [&]() -> lgf_status {
-        const uint32_t nt = build_work(e, phase, fmt, true, listed);
+        const uint32_t nt = build_work(e, kForSweeps, phase, fmt, true, listed);
         LGF_TRY(upload_work(e, nt, listed.size()));
         LGF_TRY(run_chunk(e, format, format, 1, omega, p_sr, 0, 0, false));  // warm-up
         LGF_HIP(hipEventRecord(e->ev0, e->stream));
@@ -1066,7 +1108,7 @@ lgf_status lgf_ensemble_time_fixed_sweeps(lgf_ensemble *e, int format, int n, do
         LGF_HIP(lgf::launch_site_field(gf_format(format), gf_of(e, format, i), e->geom[i], 0, e->stream));
     }
     std::vector<int> phase(e->n, kFinish), fmt(e->n, format), listed;
-    const uint32_t nt = build_work(e, phase, fmt, true, listed, e->tile / lgf::kEnsFixedLanes, true);
+    const uint32_t nt = build_work(e, kForFixedSweeps, phase, fmt, true, listed);
     LGF_TRY(upload_work(e, nt, listed.size()));
     LGF_TRY(run_chunk_fixed(e, format, format, 1, omega, p_sr, 0, 0, false, false));  // warm-up
     LGF_HIP(hipEventRecord(e->ev0, e->stream));
@@ -1118,7 +1160,7 @@ lgf_status lgf_ensemble_autotune(lgf_ensemble *e, int format, int trials)
         e->tile = c.tile;
         e->grid_mult = c.mult;
         e->nontemporal = c.nt;
-        const uint32_t nt = build_work(e, phase, fmt, true, listed);
+        const uint32_t nt = build_work(e, kForSweeps, phase, fmt, true, listed);
         st = upload_work(e, nt, listed.size());
         if (st == LGF_OK) st = run_chunk(e, format, format, 1, 1.7, 0.0, 0, 0, false);
         if (st != LGF_OK) return false;

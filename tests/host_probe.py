@@ -105,13 +105,20 @@ def session_end(fake, lgf, dims, fmt):
         return [line[1:] for line in fake.lines(lat.fix_end) if line[0] == "launch"]
 
 
-def ensemble_work(fake, lgf, dims, tile):
-    """the tile list of a sweep of the whole ensemble, its spans, and the bytes the call took from the C++ heap"""
-    ens = lgf.Ensemble(dims, 2)
+def ensemble_work(fake, lgf, dims, fmt, tile, what):
+    """the tile list of a sweep, a fixed-link sweep or a measurement of the whole ensemble, and the bytes the call took
+    from the C++ heap"""
+    ens = lgf.Ensemble(dims, 0 if what == "fixed" else fmt)
     lgf.lgf_ensemble_set_tuning(ens.e, tile, 1, 1)
-    n = sum((v // 2 + tile - 1) // tile for v in ens.V)
+    sites = tile // 2 if what == "fixed" else tile
+    n = sum((v // 2 + sites - 1) // sites for v in ens.V)
     fake.lib.fake_new_bytes()
-    ens.sweep(2, 1.7)
+    if what == "sweep":
+        ens.sweep(2, 1.7)
+    elif what == "measure":
+        ens.measure()
+    else:
+        lgf.lgf_ensemble_time_fixed_sweeps(ens.e, fmt, 1, 1.7)
     heap = fake.lib.fake_new_bytes()
     tiles = (ctypes.c_uint32 * (4 * n)).from_address(fake.lib.fake_copied(16 * n))
     return {"tiles": [tiles[4 * k:4 * k + 3] for k in range(n)], "heap": heap}

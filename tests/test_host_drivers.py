@@ -72,18 +72,44 @@ def test_graphs_outlive_their_launches(graph_logs, name):
     assert 0 < made <= needed
 
 
-@pytest.mark.parametrize("dims,tile", [([[2, 2, 2, 2]], 64), ([[4, 4, 6, 10], [2, 2, 2, 2], [6, 2, 4, 14]], 64),
-                                       ([[8, 8, 8, 8]] * 5 + [[4, 4, 6, 10]], 128), ([[16, 16, 16, 16]] * 24, 64)])
-def test_ensemble_tile_list(probe, dims, tile):
-    """Every tile of every configuration once, consecutive ones on one XCD (workgroup b runs on XCD b % 8), and no
-    copy of the list on the heap of each call."""
-    got, = probe("ensemble_work", [(dims, tile)])
+def cube(L, n):
+    return [[L, L, L, L]] * n
+
+
+# configurations, format, tile, what, whether the tiles go in ranges per XCD: both sides of every line of the rule
+ENSEMBLE_LISTS = [
+    (cube(2, 1), 2, 64, "sweep", True), ([[4, 4, 6, 10], [2, 2, 2, 2], [6, 2, 4, 14]], 2, 64, "sweep", True),
+    (cube(8, 5) + [[4, 4, 6, 10]], 0, 128, "measure", True), (cube(8, 3), 3, 256, "fixed", True),
+    # link sweeps: 113 and 201 MB; 2^18 sites each
+    (cube(8, 48), 0, 128, "sweep", True), (cube(16, 16), 2, 128, "sweep", False),
+    ([[16, 16, 32, 30]] * 3, 3, 128, "sweep", False), ([[16, 16, 32, 32]] * 3, 3, 128, "sweep", True),
+    # fixed-link sweeps: links and g of 377 and 403 MB; configurations of 160000, 331776 and 1048576 sites
+    (cube(14, 20) + cube(8, 4), 3, 128, "fixed", True), (cube(20, 6), 3, 128, "fixed", True),
+    (cube(20, 6), 0, 128, "fixed", False), (cube(24, 6), 3, 128, "fixed", False), (cube(32, 2), 3, 128, "fixed", True),
+    (cube(32, 2), 0, 128, "fixed", True), (cube(32, 2), 2, 128, "fixed", False),
+    # measurement: 302 and 369 MB; 127 and 191 MB each
+    (cube(16, 8), 0, 128, "measure", True), (cube(20, 12), 2, 128, "measure", False),
+    (cube(24, 4), 3, 128, "measure", False), (cube(24, 4), 0, 128, "measure", True),
+]
+
+
+@pytest.fixture(scope="module")
+def ensemble_lists(probe):
+    return probe("ensemble_work", [case[:4] for case in ENSEMBLE_LISTS])
+
+
+@pytest.mark.parametrize("k", range(len(ENSEMBLE_LISTS)))
+def test_ensemble_tile_list(ensemble_lists, k):
+    """Every tile of every configuration once, consecutive ones on one XCD (workgroup b runs on XCD b % 8) where the rule
+    says so, else in the order of dispatch; and no copy of the list on the heap of each call."""
+    dims, _, tile, what, ranges = ENSEMBLE_LISTS[k]
+    got, sites = ensemble_lists[k], tile // 2 if what == "fixed" else tile
     want = []
     for i, d in enumerate(dims):
-        half = d[0] * d[1] * d[2] * d[3] // 2
-        want += [[i, h0, len(want) + h0 // tile] for h0 in range(0, half, tile)]
-    # (len(want) is read before the extension)
-    assert [t for x in range(8) for t in got["tiles"][x::8]] == want
+        half, first = d[0] * d[1] * d[2] * d[3] // 2, len(want)
+        want += [[i, h0, first + h0 // sites] for h0 in range(0, half, sites)]
+    in_order = [t for x in range(8) for t in got["tiles"][x::8]] if ranges else got["tiles"]
+    assert in_order == want
     assert got["heap"] <= 4096 + 64 * len(dims)
 
 
