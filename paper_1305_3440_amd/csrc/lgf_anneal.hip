@@ -123,30 +123,29 @@ __device__ __forceinline__ uint32_t heatbath_step(mat3<double> &W, mat3<double> 
 
 // lanes per site: 1 on FP64-12 links, 2 on FP64-18 links
 template <int F> constexpr int sa_lanes() { return F == kF64_12 ? 1 : 2; }
-constexpr int kSaBlock = 64;  // lanes per workgroup
 // waves per SIMD: the links of FP64-12 on one lane spill at two (24^4 72 us against 59)
 template <int F> constexpr int sa_waves() { return F == kF64_12 ? 1 : 2; }
 
 // The rows of a link that its storage holds, kept in LDS over the heat bath: one
-// slot per link, 16 bytes per lane in a row.
-template <int R>
+// slot per link, 16 bytes per lane in a row of B lanes.
+template <int R, int B>
 __device__ __forceinline__ void stash(double2 *slot, const mat3<double> &u)
 {
 #pragma unroll
     for (int i = 0; i < R; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            slot[(3 * i + j) * kSaBlock + threadIdx.x] = make_double2(u.e[i][j].re, u.e[i][j].im);
+            slot[(3 * i + j) * B + threadIdx.x] = make_double2(u.e[i][j].re, u.e[i][j].im);
 }
 
-template <int R>
+template <int R, int B>
 __device__ __forceinline__ void fetch(mat3<double> &u, const double2 *slot)
 {
 #pragma unroll
     for (int i = 0; i < R; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const double2 v = slot[(3 * i + j) * kSaBlock + threadIdx.x];
+            const double2 v = slot[(3 * i + j) * B + threadIdx.x];
             u.e[i][j] = {v.x, v.y};
         }
     if constexpr (R == 2) rebuild_row2(u);
@@ -166,25 +165,30 @@ __device__ __forceinline__ void fetch(mat3<double> &u, const double2 *slot)
 // 160 KB): FP64-18 runs two waves per SIMD instead of one, FP64-12 keeps 328
 // registers instead of 498.  cospi(2 u) instead of cos(2 pi u) saves the
 // reduction of a general argument, a quarter of the kernel's instructions.  NT and
-// order are those of the relaxation sweep's launches.  Per launch at T = 0.05 and
+// order are those of the relaxation sweep's launches, B the lanes of a workgroup
+// (lgf_api.cpp chooses them by the size).  FP64-12 in workgroups of more than one
+// wave, for fields far beyond the caches, has all 8 links in flight before the
+// first one waits in LDS (64^4 at T = 0.05 2413 -> 2311 us; 24^4, which the caches
+// hold, 51 -> 54).  Per launch at T = 0.05 and
 // 2: 24^4 FP64-12 68 -> 59 and 94 -> 83 us, FP64-18 103 -> 91 and 142 -> 102;
 // 32^4 FP64-12 178 -> 151 and 234 -> 204.
-template <int F, int NT>
-__global__ void __launch_bounds__(kSaBlock, sa_waves<F>()) anneal_kernel(void *__restrict__ field, Geom g, int parity, double temp,
+template <int F, int NT, int B>
+__global__ void __launch_bounds__(B, sa_waves<F>()) anneal_kernel(void *__restrict__ field, Geom g, int parity, double temp,
                                                           uint32_t sweep, uint32_t instance, uint32_t k0, uint32_t k1,
                                                           int order, uint32_t n_groups,
                                                           unsigned long long *__restrict__ trials)
 {
     static_assert(std::is_same<typename Fmt<F>::T, double>::value, "the heat bath runs on FP64 links");
+    constexpr bool EARLY = F == kF64_12 && B > 64;
     using S = Fmt<F>;
     constexpr int LANES = sa_lanes<F>();
     constexpr int NL = 4 / LANES;
     constexpr int FIRST = NL == 4 ? 1 : 0;  // forward links FIRST, FIRST + 1, ... are in LDS
-    __shared__ double2 held[(NL - FIRST) * 3 * S::R * kSaBlock];
+    __shared__ double2 held[(NL - FIRST) * 3 * S::R * B];
     const uint32_t b = launch_place(blockIdx.x, gridDim.x, order);
     if (b >= n_groups) return;  // the whole workgroup
     // Vh <= 2^30, so block * lanes < 2^32
-    const uint32_t tid = b * kSaBlock + threadIdx.x;
+    const uint32_t tid = b * B + threadIdx.x;
     const uint32_t grp = tid / LANES;
     const int lane = (int)(tid % LANES);
     const bool active = grp < g.Vh;
@@ -197,22 +201,27 @@ __global__ void __launch_bounds__(kSaBlock, sa_waves<F>()) anneal_kernel(void *_
     for (int k = 0; k < NL; ++k) {
         const int mu = lane + k * LANES;
         load_link<F, NT == kStream, false>(uf[k], block_ptr<F>(field, g.Vh, parity, mu), g.Vh, h);
-        if (k >= FIRST) stash<S::R>(held + (k - FIRST) * 3 * S::R * kSaBlock, uf[k]);
+        if (!EARLY && k >= FIRST) stash<S::R, B>(held + (k - FIRST) * 3 * S::R * B, uf[k]);
     }
     // a lane reads only what it wrote: no barrier, but no forwarding in registers either
-    asm volatile("" ::: "memory");
+    if constexpr (!EARLY) asm volatile("" ::: "memory");
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
         const int mu = lane + k * LANES;
         hb[k] = back_half(g, c, h, mu);
         load_link<F, NT == kStream, false>(ub[k], block_ptr<F>(field, g.Vh, parity ^ 1, mu), g.Vh, hb[k]);
     }
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int k = FIRST; k < NL; ++k) stash<S::R, B>(held + (k - FIRST) * 3 * S::R * B, uf[k]);
+        asm volatile("" ::: "memory");
+    }
     mat3<double> K;
     set_zero(K);
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
         mat3<double> u = uf[k], v = ub[k];
-        if (k >= FIRST) fetch<S::R>(u, held + (k - FIRST) * 3 * S::R * kSaBlock);
+        if (k >= FIRST) fetch<S::R, B>(u, held + (k - FIRST) * 3 * S::R * B);
         else if constexpr (S::R == 2) rebuild_row2(u);
         if constexpr (S::R == 2) rebuild_row2(v);
         add_fwd_bwd(K, u, v);
@@ -236,7 +245,7 @@ __global__ void __launch_bounds__(kSaBlock, sa_waves<F>()) anneal_kernel(void *_
             mat3<double> u, r, rb;
             forget(hb[k]);
             if (k >= FIRST) {
-                fetch<S::R>(u, held + (k - FIRST) * 3 * S::R * kSaBlock);
+                fetch<S::R, B>(u, held + (k - FIRST) * 3 * S::R * B);
             } else {
                 u = uf[k];
                 if constexpr (S::R == 2) rebuild_row2(u);
@@ -261,18 +270,20 @@ hipError_t launch_anneal_f(void *field, const Geom &g, int parity, double temp, 
                            uint32_t instance, unsigned long long *trials, const SweepTuning &t, hipStream_t s)
 {
     const uint64_t threads = (uint64_t)g.Vh * sa_lanes<F>();
-    const uint32_t ng = (uint32_t)((threads + kSaBlock - 1) / kSaBlock);
+    const int block = t.nontemporal == kStream ? t.block : 64;
+    const uint32_t ng = (uint32_t)((threads + block - 1) / block);
     const int order = launch_order(t, parity);
-    const dim3 grid((order & kXcdRanges) ? (ng + 7u) / 8u * 8u : ng), block(kSaBlock);
-#define LGF_SA(NT)                                                                                                    \
-    hipLaunchKernelGGL((anneal_kernel<F, NT>), grid, block, 0, s, field, g, parity, temp, (uint32_t)sweep, instance,  \
-                       (uint32_t)seed, (uint32_t)(seed >> 32), order, ng, trials)
-    switch (t.nontemporal) {
-    case kCached: LGF_SA(kCached); break;
-    case kStream: LGF_SA(kStream); break;
-    case kStreamStores: LGF_SA(kStreamStores); break;
-    default: return hipErrorInvalidValue;
-    }
+    const dim3 grid((order & kXcdRanges) ? (ng + 7u) / 8u * 8u : ng);
+#define LGF_SA(NT, B)                                                                                                  \
+    hipLaunchKernelGGL((anneal_kernel<F, NT, B>), grid, dim3(B), 0, s, field, g, parity, temp, (uint32_t)sweep,        \
+                       instance, (uint32_t)seed, (uint32_t)(seed >> 32), order, ng, trials)
+    if (t.nontemporal == kCached) LGF_SA(kCached, 64);
+    else if (t.nontemporal == kStreamStores) LGF_SA(kStreamStores, 64);
+    else if (t.nontemporal != kStream) return hipErrorInvalidValue;
+    else if (block == 64) LGF_SA(kStream, 64);
+    else if (block == 128) LGF_SA(kStream, 128);
+    else if (block == 256) LGF_SA(kStream, 256);
+    else return hipErrorInvalidValue;
 #undef LGF_SA
     return hipGetLastError();
 }

@@ -335,6 +335,31 @@ lgf::SweepTuning launch_tuning(const lgf_lattice *h, int format)
     return h->tuned[format] ? t : size_tuning(h, format, t);
 }
 
+// The tuning of the annealing launches: the link sweeps', with workgroups of
+// their own size.  Chosen by size, half-sweep launch at T = 0.05 and 2:
+//  - 64 lanes up to 1.6 GB.  Beyond, where a cold sweep is bound by memory, 128
+//    lanes in FP64-12 (48^4 835 and 886 us in 64 lanes -> 752 and 962, 56^4 1487 and
+//    1632 -> 1421 and 1771, 64^4 2492 and 2762 -> 2311 and 2994) and 256 in FP64-18
+//    (44^4 928 and 948 -> 903 and 935, 56^4 2410 and 2430 -> 2317 and 2337, 48 x 64^3
+//    2797 and 2831 -> 2711 and 2832; 64^4 3669 and 3704 against 3832 and 3791).
+//  - FP64-12 is streamed from 1.3 GB on: 44^4 (1.44 GB) 576 and 652 us with cached
+//    loads -> 508 and 627 (588 and 660 -> 582 and 651 in other memory); 42^4 (1.19
+//    GB) 471 and 539 streamed against 423 and 528.
+lgf::SweepTuning anneal_tuning(const lgf_lattice *h)
+{
+    lgf::SweepTuning t = launch_tuning(h, h->format);
+    if (h->tuned[h->format]) return t;
+    const bool fp64_12 = h->format == LGF_FP64_12;
+    const double mb = 4e-6 * (double)h->V * (double)lgf::link_bytes(h->format);
+    if (fp64_12 && mb > 1300.0) {
+        t.nontemporal = lgf::kStream;
+        t.xcd_remap = 0;
+        t.backward = 0;
+    }
+    t.block = mb <= 1600.0 ? 64 : (fp64_12 ? 128 : 256);
+    return t;
+}
+
 // A link-sweep tuning as lgf_sweep_tuning has it: without the direction, and
 // with streamed stores as streamed.  Launches chosen by size can have both, set
 // or autotuned ones neither.
@@ -1785,7 +1810,7 @@ lgf_status lgf_anneal_sweep(lgf_lattice *h, int parity, double T, uint64_t seed,
     for (int p = 0; p < 2; ++p)
         if (parity == 2 || parity == p)
             LGF_HIP(lgf::launch_anneal(h->format, h->field, h->geom, p, T, seed, sweep_index, 0u, ctr,
-                                       launch_tuning(h, h->format), h->stream));
+                                       anneal_tuning(h), h->stream));
     if (trials) LGF_TRY(read_trials(h, trials));
     return LGF_OK;
 }
@@ -1805,7 +1830,7 @@ lgf_status lgf_anneal(lgf_lattice *h, int64_t n_sweeps, double T_start, double T
         const double T = anneal_temperature(n, n_sweeps, T_start, T_end);
         for (int p = 0; p < 2; ++p)
             LGF_HIP(lgf::launch_anneal(h->format, h->field, h->geom, p, T, seed, sweep0 + (uint64_t)n, 0u,
-                                       h->d_trials, launch_tuning(h, h->format), h->stream));
+                                       h->d_trials, anneal_tuning(h), h->stream));
         if ((n + 1) % 20 == 0 || n + 1 == n_sweeps)
             LGF_HIP(lgf::launch_convert(h->format, h->field, h->format, h->field, h->geom, true, h->stream));
     }

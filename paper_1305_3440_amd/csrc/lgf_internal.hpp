@@ -177,7 +177,7 @@ hipError_t launch_split_links(int fs, const void *src, void *dst, const Geom &g,
 // Simulated annealing: one heat-bath half-sweep of the link-rewriting form at
 // temperature temp > 0 (FP64 formats only).  trials (device counter, may be
 // NULL) accumulates the accept-reject trials of the launch.  Of the tuning:
-// xcd_remap, nontemporal, backward.
+// block (of streamed launches; else 64), xcd_remap, nontemporal, backward.
 hipError_t launch_anneal(int format, void *field, const Geom &g, int parity, double temp, uint64_t seed,
                          uint64_t sweep, uint32_t instance, unsigned long long *trials, const SweepTuning &t,
                          hipStream_t s);

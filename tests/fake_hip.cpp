@@ -94,11 +94,10 @@ void __hipRegisterFunction(void **, const void *host, char *, const char *name, 
     char *d = abi::__cxa_demangle(name, nullptr, nullptr, &st);
     std::string s = d ? d : name;
     std::free(d);
-    s = s.substr(0, s.find(")"));   // "void lgf::kernel<...>(..."
-    const size_t open = s.find('(');
-    if (open != std::string::npos) s = s.substr(0, open);
-    const size_t ns = s.find("lgf::");
-    if (ns != std::string::npos) s = s.substr(ns + 5);
+    for (const char *prefix : {"void ", "lgf::", "(anonymous namespace)::"})
+        if (s.compare(0, std::strlen(prefix), prefix) == 0) s.erase(0, std::strlen(prefix));
+    const size_t open = s.find('(');  // "kernel<...>(arguments"
+    if (open != std::string::npos) s.erase(open);
     for (char &c : s)
         if (c == ' ') c = '_';
     kernels[host] = s;
@@ -127,6 +126,7 @@ int hipLaunchKernel(const void *f, Dim grid, Dim block, void **args, size_t, voi
                     std::to_string(grid.y) + " block " + std::to_string(block.x);
     const bool fixed = k.find("fixed_sweep_kernel") == 0;
     if (k.find("sweep_kernel") == 0 || k.find("sweep_coulomb_kernel") == 0) s += " order" + words(args[4], 1);
+    else if (k.find("anneal_kernel") != std::string::npos) s += " order" + words(args[8], 1);
     else if (fixed) s += " order" + words(args[5], 14);  // the whole TileOrder
     if (fixed || k.find("sweep") == 0) last_sweep = s;
     if (!capturing && k.find("finish_measure_kernel") == 0) {

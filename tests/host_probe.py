@@ -105,6 +105,13 @@ def session_end(fake, lgf, dims, fmt):
         return [line[1:] for line in fake.lines(lat.fix_end) if line[0] == "launch"]
 
 
+def anneal_launches(fake, lgf, dims, fmt):
+    """the launches of one annealing sweep"""
+    with lgf.Lattice(dims, fmt) as lat:
+        log = fake.lines(lambda: lat.anneal_sweep(2, 0.5, 1, 2, False))
+    return [line[1:] for line in log if line[0] == "launch"]
+
+
 def ensemble_work(fake, lgf, dims, fmt, tile, what):
     """the tile list of a sweep, a fixed-link sweep or a measurement of the whole ensemble, and the bytes the call took
     from the C++ heap"""

@@ -170,3 +170,20 @@ def test_the_transformation_has_a_lane_per_link_on_small_lattices(probe):
     assert ends == [[["gauge_transform_link_kernel<0,_3,_0>", "grid", "8", "8", "block", "256"]],
                     [["gauge_transform_link_kernel<0,_2,_0>", "grid", "157", "8", "block", "256"]],
                     [["gauge_transform_kernel<0,_2,_0>", "grid", "376", "1", "block", "256"]]]
+
+
+# dims, format: (what goes past the caches: 0 nothing, 1 all, 2 the stores; lanes of a workgroup; order of the parities)
+ANNEAL_LAUNCHES = {
+    ((8, 8, 8, 8), 0): (0, 64, "1 1"), ((16, 16, 16, 16), 3): (1, 64, "1 1"), ((24, 24, 24, 24), 0): (0, 64, "1 3"),
+    ((40, 40, 40, 40), 0): (2, 64, "1 3"), ((42, 42, 42, 42), 3): (2, 64, "1 3"), ((44, 44, 44, 44), 3): (1, 64, "0 0"),
+    ((44, 44, 44, 44), 0): (1, 256, "0 0"), ((48, 48, 48, 48), 3): (1, 128, "0 0"), ((64, 64, 64, 64), 0): (1, 256, "0 0"),
+}
+
+
+def test_annealing_launches_by_size(probe):
+    for (dims, fmt), launches in zip(ANNEAL_LAUNCHES, probe("anneal_launches", list(ANNEAL_LAUNCHES))):
+        nt, block, orders = ANNEAL_LAUNCHES[dims, fmt]
+        assert len(launches) == 2
+        for line, order in zip(launches, orders.split()):
+            assert line[0].endswith(f"anneal_kernel<{fmt},_{nt},_{block}>"), (dims, fmt, line)
+            assert line[4:] == ["block", str(block), "order", order], (dims, fmt, line)
