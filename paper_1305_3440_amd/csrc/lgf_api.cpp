@@ -551,13 +551,16 @@ lgf_status ensure_fused(lgf_lattice *h, int format)
 // F and theta after a chunk whose last half-sweep was fused: its partial sums
 // (parity-1 sites' theta, parity-1 forward links' Re tr, from the links as
 // reunitarized and stored) plus a read-only pass over the parity-0 sites.
-// Enqueued only, as measure_field.
+// Enqueued only, as measure_field.  The pass goes past the caches where anything
+// of the sweeps does: read through them it drives out what the next half-sweep
+// starts on (a check after every sweep, per sweep: 40^4 FP64-12 960 -> 932 us, 44^4
+// FP32-12 734 -> 698, 32^4 FP64-18 546 -> 516).
 lgf_status measure_fused(lgf_lattice *h, int format, void *field)
 {
     const int ng = (int)lgf::sweep_groups(h->geom, launch_tuning(h, format));
     int n0 = 0;
     LGF_HIP(lgf::launch_measure(format, field, h->geom, 0, h->d_fused + 2 * (size_t)ng, &n0, h->stream,
-                                launch_tuning(h, format).nontemporal == lgf::kStream));
+                                launch_tuning(h, format).nontemporal != lgf::kCached));
     LGF_HIP(lgf::launch_finish_measure(h->d_fused, ng + n0, (double)h->V, h->h_out, h->stream));
     return LGF_OK;
 }

@@ -187,3 +187,11 @@ def test_annealing_launches_by_size(probe):
         for line, order in zip(launches, orders.split()):
             assert line[0].endswith(f"anneal_kernel<{fmt},_{nt},_{block}>"), (dims, fmt, line)
             assert line[4:] == ["block", str(block), "order", order], (dims, fmt, line)
+
+
+def test_the_measurement_after_a_chunk_is_streamed_where_the_sweeps_are(probe):
+    """Fields of 4, 38, 191, 604 MB and 2.4 GB."""
+    cases = [((L, L, L, L), 0, [("landau", {**LINK, "max_sweeps": 20})], 1.0) for L in (8, 16, 24, 32, 48)]
+    for (dims, *_), log, streamed in zip(cases, probe("fix_log", cases), ("false", "true", "false", "true", "true")):
+        last = [line[1] for line in log if line[0] == "launch" and line[1].startswith("measure_kernel")][-1]
+        assert last == f"measure_kernel<0,_{streamed}>", dims
