@@ -201,7 +201,8 @@ static hipError_t launch_fixed_r(const void *links, void *gf, const Geom &g, con
             return hipErrorInvalidValue;
     case 2:
         if (t.in_order) {
-            if constexpr (F == kF32_12)
+            // (chosen for lattices whose FP32-12 links the caches hold)
+            if constexpr (F == kF32_12 && CACHED)
                 return launch_fixed_t<F, 2, REC, true, CACHED>(links, gf, g, a, t, post, slices, coulomb, s);
             else
                 return hipErrorInvalidValue;

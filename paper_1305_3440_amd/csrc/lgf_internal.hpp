@@ -22,8 +22,9 @@ struct SweepTuning {
                              // (parity 1 one slice behind), 2 out of place (ping-pong
                              // between the field and a second buffer of its format)
     int sites_per_thread = 1;  // tiles per workgroup (1, 2 or 4), strided over the launch
-    int in_order = 0;  // fixed-link sweep in FP32-12, 2 lanes per site: the sums, and so the bits, of 1 lane
-    int backward = 0;  // link form: the odd half-sweep walks the lattice from its end
+    int in_order = 0;  // fixed-link sweep on the cached link field in FP32-12, 2 lanes per site: the sums, and
+                       // so the bits, of 1 lane
+    int backward = 0;  // the odd half-sweep walks the lattice from its end (the fixed-link sweep's tiles too)
 };
 
 // the order of a link sweep's workgroups (kXcdRanges, kBackward)

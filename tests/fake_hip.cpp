@@ -77,6 +77,14 @@ void operator delete(void *p, size_t) noexcept { std::free(p); }
 extern "C" {
 
 const char *fake_log() { return text.c_str(); }
+// the names of the library's kernels, one a line
+const char *fake_kernels()
+{
+    static std::string all;
+    all.clear();
+    for (const auto &k : kernels) all += k.second + "\n";
+    return all.c_str();
+}
 void fake_clear() { text.clear(); }
 void fake_result(double F, double theta, double f) { result[0] = F; result[1] = theta; factor = f; }
 void fake_memory(uint64_t bytes) { free_bytes = bytes; }

@@ -18,6 +18,7 @@ class Fake:
     def __init__(self, path):
         self.lib = ctypes.CDLL(path, mode=ctypes.RTLD_GLOBAL)
         self.lib.fake_log.restype = ctypes.c_char_p
+        self.lib.fake_kernels.restype = ctypes.c_char_p
         self.lib.fake_result.argtypes = [ctypes.c_double] * 3
         self.lib.fake_memory.argtypes = [ctypes.c_uint64]
         self.lib.fake_fast.argtypes = [ctypes.c_char_p]
@@ -110,6 +111,11 @@ def anneal_launches(fake, lgf, dims, fmt):
     with lgf.Lattice(dims, fmt) as lat:
         log = fake.lines(lambda: lat.anneal_sweep(2, 0.5, 1, 2, False))
     return [line[1:] for line in log if line[0] == "launch"]
+
+
+def kernels(fake, lgf, prefix):
+    """the library's kernels whose names start so"""
+    return sorted(k for k in fake.lib.fake_kernels().decode().splitlines() if k.startswith(prefix))
 
 
 def ensemble_work(fake, lgf, dims, fmt, tile, what):

@@ -195,3 +195,14 @@ def test_the_measurement_after_a_chunk_is_streamed_where_the_sweeps_are(probe):
     for (dims, *_), log, streamed in zip(cases, probe("fix_log", cases), ("false", "true", "false", "true", "true")):
         last = [line[1] for line in log if line[0] == "launch" and line[1].startswith("measure_kernel")][-1]
         assert last == f"measure_kernel<0,_{streamed}>", dims
+
+
+def test_in_order_kernels_are_those_that_launches_choose(probe):
+    """fixed_sweep_kernel<format, lanes, SR, post, mu0, records, in order, cached links>: two lanes per site in the order of
+    one are chosen up to 80000 sites in FP32-12 only, on the cached link field."""
+    names, = probe("kernels", [("fixed_sweep_kernel",)])
+    in_order = [k for k in names if k.split("<")[1].strip(">").split(",_")[6] == "true"]
+    assert len(in_order) == 10 and all(k.startswith("fixed_sweep_kernel<2,_2,") for k in in_order)
+    assert all(k.endswith("_false,_true,_true>") for k in in_order)
+    used, = probe("tuning_flows", [((8, 8, 8, 8), 2, "fixed", (4, 256, 0, 0), "sweep_kernel<2,_4,")])
+    assert used["fresh"][1][0][0] in in_order
