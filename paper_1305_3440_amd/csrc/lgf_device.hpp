@@ -437,7 +437,10 @@ inline FastDiv make_fast_div(uint32_t d)
     return {(uint32_t)((1ull << (31 + l)) / d + 1), l};
 }
 
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f) { return __umulhi(2 * n, f.m) >> f.l; }
+__host__ __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f)
+{
+    return (uint32_t)((uint64_t)(2u * n) * f.m >> 32) >> f.l;
+}
 
 // Which of n items (workgroups' shares, ordered like the sites) workgroup b
 // takes: the dispatch deals workgroups to the 8 XCDs in turn, and each XCD
@@ -448,7 +451,7 @@ struct XcdRuns {
     FastDiv d;
 };
 
-__device__ __forceinline__ uint32_t xcd_item(uint32_t b, const XcdRuns &r)
+__host__ __device__ __forceinline__ uint32_t xcd_item(uint32_t b, const XcdRuns &r)
 {
     const uint32_t s = b >> 3, j = fast_div(s, r.d);
     return (j * 8u + (b & 7u)) * r.run + (s - j * r.run);
@@ -464,7 +467,7 @@ struct Geom {
 
 // workgroup b's place when n workgroups are walked backwards, on the XCD that has
 // it forwards where n allows
-__device__ __forceinline__ uint32_t backwards(uint32_t b, uint32_t n)
+__host__ __device__ __forceinline__ uint32_t backwards(uint32_t b, uint32_t n)
 {
     return (n & 7u) ? n - 1u - b : n - 8u - (b & ~7u) + (b & 7u);
 }
@@ -473,7 +476,7 @@ __device__ __forceinline__ uint32_t backwards(uint32_t b, uint32_t n)
 // multiple of 8); from the end of the lattice (the odd half-sweep, which then
 // starts on what the even one read last).
 constexpr int kXcdRanges = 1, kBackward = 2;
-__device__ __forceinline__ uint32_t launch_place(uint32_t b, uint32_t n, int order)
+__host__ __device__ __forceinline__ uint32_t launch_place(uint32_t b, uint32_t n, int order)
 {
     if (order & kBackward) b = backwards(b, n);
     return (order & kXcdRanges) ? (b & 7u) * (n >> 3) + (b >> 3) : b;
