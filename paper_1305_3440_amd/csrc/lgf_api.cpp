@@ -281,7 +281,8 @@ lgf::SweepTuning default_tuning(int format)
 
 // The tuning of the link sweeps' launches: the handle's where it was set or
 // autotuned (launch_tuning), else chosen from its starting tuning t by the size
-// of the field.  The bits do not depend on it.  Measured per half-sweep launch, defaults above -> chosen:
+// of the field.  The bits do not depend on it.  Measured per half-sweep launch,
+// defaults above -> chosen:
 //  - Fields of up to 420 MB stay in the 256 MB last-level cache from one
 //    half-sweep to the next, wholly or, since the odd half-sweep walks the lattice
 //    from its end and starts on what the even one read last, in part; but only if
@@ -297,15 +298,26 @@ lgf::SweepTuning default_tuning(int format)
 //    FP32-12 161 -> 150 (186).  At 1.5 GB 583 us against 598 (48^4 FP32-18), at 2 GB
 //    776 against 745 (48^4 FP64-12), at 64^4 3750 against 3380 (FP64-18).
 //  - Between 22 and 48 MB, around the L2s' 32 MB, streaming the links keeps
-//    what L2 has: 16^4 FP64-18 (38 MB) 11.5 against 12.6 us, FP64-12 (25 MB) 9.3
-//    against 10.5; below, 12^4 FP64-18 (12 MB) 7.9 against 7.5.
+//    what L2 has: FP64-18 16^4 (38 MB) 11.1 against 12.5 us, 16^3 x 18 (42 MB) 13.6
+//    against 14.8, FP64-12 18^4 (40 MB) 12.4 against 13.0, FP32-12 22^4 (45 MB) 13.6
+//    against 14.9 (FP32-18, and sizes up to 37 MB but 16^4, within 2 % either way);
+//    below, 12^4 FP64-18 (12 MB) 7.9 against 7.4, beyond, 20^4 FP64-12 (61 MB) 24.2
+//    against 20.1.
 //  - Two lanes per site where the launch is too small to fill the chip (up to
 //    40000 sites, 65536 in FP32-12) and the time is one wave's: 8^4 FP64-18 7.0
 //    (one lane, 64-lane workgroups; 8.1 in 128) -> 5.4 us, 12^4 FP32-12 5.9 -> 5.2,
-//    14^4 FP64-18 10.0 -> 9.0; 16^4 FP64-18 11.5 against 11.8.  FP64-12 keeps
-//    them throughout, two waves per SIMD instead of one: 24^4 42.3 -> 39.4 us.
-//  - Beyond: 256-lane workgroups in FP32 (64^4 FP32-18 1749 -> 1695 us) and two
-//    lanes per site in FP32-12 (1157 -> 1111, 48^4 382 -> 374).
+//    14^4 FP64-18 10.2 -> 9.3; 14^3 x 16 10.0 against 9.3, 16^4 11.2 against 11.5, 16^3 x
+//    18 13.6 against 16.8.  FP64-12 keeps them throughout, two waves per SIMD instead
+//    of one: 24^4 42.3 -> 39.4 us.
+//  - Beyond: 256-lane workgroups in FP32 (FP32-18 against 128 lanes: 54^4 1164 -> 1131
+//    us, 60^4 1600 -> 1573, 64^4 1755 -> 1690) and two lanes per site in FP32-12 (against
+//    one in 128 lanes: 56^4 736 -> 719, 48^3 x 96 776 -> 751, 48 x 64^3 878 -> 833, 64^3 x
+//    80 1501 -> 1468; 60^4 970 -> 982; 64^4 1157 -> 1111, in other memory 1155 -> 1236).
+// The Coulomb link sweeps take the same launches.  A full sweep with the upload
+// of the timeslice flags, one lane per site in 128-lane workgroups, streamed ->
+// chosen: 8^4 FP64-18 30.9 -> 25.4 us, 24^4 FP64-12 122 -> 94, 32^4 FP32-12 180 -> 132, 40^4
+// FP64-18 1184 -> 1120, 48^4 FP32-12 789 -> 723, FP32-18 1186 -> 1195, 56^4 FP32-12 1473 ->
+// 1454, 64^4 2308 -> 2241, FP64-18 7030 -> 7037.
 lgf::SweepTuning size_tuning(const lgf_lattice *h, int format, lgf::SweepTuning t)
 {
     const double mb = 4e-6 * (double)h->V * (double)lgf::link_bytes(format);

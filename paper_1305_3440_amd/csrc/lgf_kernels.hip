@@ -41,7 +41,9 @@ size_t link_bytes(int format)
 // sites' F and theta contributions in partials[2b], partials[2b + 1].
 // Two waves per SIMD for overrelaxation on FP64-12 with two lanes per site: its
 // state just fits 256 registers (with the coins of stochastic relaxation it
-// would spill).
+// would spill).  With the measurement two registers go to scratch (12 bytes per
+// lane), which costs less than the second wave gives: with a check after every
+// sweep 28^4 takes 198 us per sweep against 202 with one wave, 32^4 361 against 389.
 template <int F, int LPS, bool SR> constexpr int sweep_waves() { return (F == kF64_12 && LPS == 2 && !SR) ? 2 : 1; }
 
 template <int F, int LPS, bool SR, int NT, bool OOP, bool ACC, bool MEAS>
@@ -864,7 +866,7 @@ __device__ __forceinline__ void after(uint32_t &v, double &s) { asm volatile("" 
 // once, not once per plane, the next plane's two links are in flight while one
 // is summed, and the items go as in measure_kernel.  The products go element by
 // element, so that with the own links and two planes' neighbours in registers
-// nothing spills; FP64 runs one wave per SIMD (two waves that reload the own
+// nothing goes to scratch (FP64-18 keeps a few in the accumulation registers); FP64 runs one wave per SIMD (two waves that reload the own
 // links: 299 us at 32^4 FP64-18).  With the final sum and the wait: 32^4 FP64-18
 // 503 -> 271 us, 64^4 6561 -> 3968, FP32-12 164 -> 100 and 2125 -> 1600.
 template <int F>
